@@ -48,6 +48,7 @@ struct tt_ctx {
     float *d_Bsw = nullptr;     // Bu in MFMA lane order (16-row tiles), for the forward map
     uint16_t *d_Bsw16 = nullptr; // bf16 Bu in MFMA lane order (16-row tiles, 32-coefficient steps), forward
     uint16_t *d_BuT16 = nullptr; // bf16 [S][Cp][16]: B^T with u padded to 16, adjoint
+    uint16_t *d_Bop = nullptr;  // [S][6][Cp][8] bf16 operands of the staged adjoint (up to 8 unique segments)
     int pb = 0;                 // projections per forward batch (0: no workspace attached)
     long long vol_pad = 0;
     size_t per_proj = 0;        // bytes of one projection's mapped volume M
@@ -61,6 +62,7 @@ struct tt_ctx {
     float *d_resid = nullptr;   // [S][nj][nk][n_seg]
     float *d_M = nullptr;       // [pb][vol_pad][Up], zero border
     float *d_cT = nullptr;      // [C][V] channel-major copy of c (fused sparse forward only)
+    float *d_split = nullptr;   // coefficient volumes of the adjoint's splits (null: none)
     size_t table_bytes = 0;
     bool timing = false;
     struct Mark {
@@ -125,6 +127,7 @@ struct Tables {
     std::vector<float> bsw;        // bu in MFMA lane order: tile rt, k-step ks, lane l
     std::vector<uint16_t> bsw16;   // bf16 bu in MFMA lane order (16-row tiles, k blocks of 16)
     std::vector<uint16_t> but16;   // bf16 [S][Cp][16]: B^T with u padded to 16
+    std::vector<uint16_t> bop;     // [S][6][Cp][8]: operands of the staged adjoint
 };
 static void build_tables(const tt_ctx *c, Tables &t)
 {
@@ -158,6 +161,38 @@ static void build_tables(const tt_ctx *c, Tables &t)
         for (int i = 0; i < d.Cp; ++i)
             for (int u = 0; u < d.Up; ++u)
                 t.but16[((size_t)s * d.Cp + i) * 16 + u] = to_bf16(t.bu[((size_t)s * d.Up + u) * d.Cp + i]);
+    // Staged adjoint: six operand sets of eight k values per coefficient, from the
+    // three bf16 pieces b0 + b1 + b2 of B
+    t.bop.clear();
+    if (d.Up <= 8) {
+        t.bop.assign((size_t)S * 6 * d.Cp * 8, 0);
+        for (int s = 0; s < S; ++s)
+            for (int i = 0; i < d.Cp; ++i)
+                for (int u = 0; u < d.Up; ++u) {
+                    const float x = t.bu[((size_t)s * d.Up + u) * d.Cp + i];
+                    uint16_t b[3];
+                    float r = x;
+                    for (int p = 0; p < 3; ++p) {
+                        b[p] = to_bf16(r);
+                        const uint32_t w = (uint32_t)b[p] << 16;
+                        float v;
+                        std::memcpy(&v, &w, 4);
+                        r -= v;
+                    }
+                    auto at = [&](int set, int k) -> uint16_t & {
+                        return t.bop[(((size_t)s * 6 + set) * d.Cp + i) * 8 + k];
+                    };
+                    if (d.Up == 8) {  // sets 2 m + lane half: b0 b1 (times q0, q1), b0 b2 (times q2, q0); tier b0
+                        at(0, u) = at(2, u) = at(4, u) = b[0];
+                        at(1, u) = b[1];
+                        at(3, u) = b[2];
+                    } else {  // times [q0 | q1] twice, [q2 | q0]; tier [q0 | 0]
+                        at(0, u) = at(0, 4 + u) = at(2, u) = at(3, u) = b[0];
+                        at(1, u) = at(1, 4 + u) = b[1];
+                        at(2, 4 + u) = b[2];
+                    }
+                }
+    }
     // MFMA-ordered copy of bu: tile rt, k-step ks, lane l -> bu[16 rt + l % 16][4 ks + l / 16]
     t.bsw.assign(t.bu.size(), 0.0f);
     const int KS = d.Cp / 4;
@@ -363,9 +398,7 @@ int tt_create(const tt_geometry *geom, tt_ctx **out)
     // blocks per CU), 76 KiB for more (two blocks per CU); measured best of
     // 20-76 KiB on 100^3 x 4 and of 32-76 KiB on 128^3 and 256^3 x 8
     d.march_lds = plan_slabs(c->frames, d.Up, (d.Up == 4 ? 52 : 76) * 1024);
-    d.win_ok = backproject_window_fits(c->frames) ? 1 : 0;
-    d.pw_lds = backproject_pw_lds(c->frames, d.Up, false, d.pw_wr, d.pw_wc);
-    d.pwj_lds = backproject_pw_lds(c->frames, d.Up, true, d.pwj_wr, d.pwj_wc);
+    plan_adjoint(c->frames, d);
 
     if (hipGetDevice(&c->device) != hipSuccess) {
         delete c;
@@ -398,16 +431,19 @@ int tt_create(const tt_geometry *geom, tt_ctx **out)
         hipMalloc(&c->d_Bsw, bsw.size() * sizeof(float)) != hipSuccess ||
         hipMalloc(&c->d_Bsw16, bsw16.size() * sizeof(uint16_t)) != hipSuccess ||
         hipMalloc(&c->d_BuT16, but16.size() * sizeof(uint16_t)) != hipSuccess ||
+        (!t.bop.empty() && hipMalloc(&c->d_Bop, t.bop.size() * sizeof(uint16_t)) != hipSuccess) ||
         hipMalloc(&c->d_sp, sp_len * sizeof(int2)) != hipSuccess ||
         hipMalloc(&c->d_gtab, gtab_len * sizeof(int)) != hipSuccess)
         return cleanup(TT_ENOMEM, "device allocation failed");
-    c->table_bytes = sizeof(ProjFrame) * S + bu.size() * 10 + but16.size() * 2 + sp_len * sizeof(int2) +
+    c->table_bytes = sizeof(ProjFrame) * S + bu.size() * 10 + (but16.size() + t.bop.size()) * 2 + sp_len * sizeof(int2) +
                      gtab_len * sizeof(int);
     if (hipMemcpy(c->d_frames, c->frames.data(), sizeof(ProjFrame) * S, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(c->d_Bu, bu.data(), bu.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(c->d_Bsw, bsw.data(), bsw.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(c->d_Bsw16, bsw16.data(), bsw16.size() * sizeof(uint16_t), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(c->d_BuT16, but16.data(), but16.size() * sizeof(uint16_t), hipMemcpyHostToDevice) != hipSuccess ||
+        (!t.bop.empty() &&
+         hipMemcpy(c->d_Bop, t.bop.data(), t.bop.size() * sizeof(uint16_t), hipMemcpyHostToDevice) != hipSuccess) ||
         hipDeviceSynchronize() != hipSuccess)
         return cleanup(TT_EHIP, "device upload failed");
     *out = c;
@@ -424,6 +460,7 @@ void tt_destroy(tt_ctx *c)
     hipFree(c->d_Bsw);
     hipFree(c->d_Bsw16);
     hipFree(c->d_BuT16);
+    hipFree(c->d_Bop);
     hipFree(c->d_sp);
     hipFree(c->d_gtab);
     delete c;
@@ -462,6 +499,7 @@ int tt_set_sparse_map(tt_ctx *c, int k)
     if (!c) return fail(TT_EINVAL, "ctx is null");
     if (k < 0) return fail(TT_EINVAL, "k must be >= 0");
     const Dims &d = c->d;
+    if (k == 0 && d.sparse_k == 0) return TT_OK;  // the tables hold the exact constants
     if (k > 0 && c->precision == TT_MAP_BF16) return fail(TT_EUNSUPPORTED, "the sparse fused map runs in float32 only");
     const int kk = std::min(k, d.C);
     std::vector<int2> sp;
@@ -520,6 +558,7 @@ int tt_set_sparse_map(tt_ctx *c, int k)
     TT_HIP(hipMemcpy(c->d_Bsw, t.bsw.data(), t.bsw.size() * sizeof(float), hipMemcpyHostToDevice));
     TT_HIP(hipMemcpy(c->d_Bsw16, t.bsw16.data(), t.bsw16.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
     TT_HIP(hipMemcpy(c->d_BuT16, t.but16.data(), t.but16.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
+    if (!t.bop.empty()) TT_HIP(hipMemcpy(c->d_Bop, t.bop.data(), t.bop.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
     if (!sp.empty()) TT_HIP(hipMemcpy(c->d_sp, sp.data(), sp.size() * sizeof(int2), hipMemcpyHostToDevice));
     if (!gtab.empty()) TT_HIP(hipMemcpy(c->d_gtab, gtab.data(), gtab.size() * sizeof(int), hipMemcpyHostToDevice));
     const bool was_fused = c->d.sparse_k > 0;
@@ -584,10 +623,17 @@ int tt_sizes(const tt_ctx *c, int64_t *out8)
 
 // Workspace layout for a forward batch of pb projections (pb = 0: no mapped volumes).
 struct WsLayout {
-    size_t part, yf, resid, cT, M, total;
+    size_t part, yf, resid, cT, M, split, total;
 };
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-static WsLayout ws_layout(const tt_ctx *c, int pb)
+// Scratch of the adjoint's splits over projections (small volumes; the adjoint
+// runs without splits where a workspace has no room for it).
+static size_t split_bytes(const tt_ctx *c)
+{
+    const int ns = std::max(c->d.adj[0].splits, c->d.adj[1].splits);
+    return ns > 1 ? align256(sizeof(float) * (size_t)n_coef(c) * ns) : 0;
+}
+static WsLayout ws_layout(const tt_ctx *c, int pb, bool split = true)
 {
     WsLayout L;
     size_t off = 0;
@@ -601,6 +647,8 @@ static WsLayout ws_layout(const tt_ctx *c, int pb)
     if (c->d.sparse_k > 0 && c->d.sparse_cm) off += align256(sizeof(float) * (size_t)n_coef(c));
     L.M = off;
     off += align256(c->per_proj * (size_t)pb);
+    L.split = off;
+    if (split) off += split_bytes(c);
     L.total = off;
     return L;
 }
@@ -626,11 +674,11 @@ static int need_ws(const tt_ctx *c)
 // or the library's static array (tt_loss_grad_noalloc, untimed: no events).
 struct Scratch {
     double *part;
-    float *yf, *resid, *M, *cT;
+    float *yf, *resid, *M, *cT, *split;
     int pb;
     bool timed;
 };
-static Scratch attached(const tt_ctx *c) { return {c->d_part, c->d_yf, c->d_resid, c->d_M, c->d_cT, c->pb, true}; }
+static Scratch attached(const tt_ctx *c) { return {c->d_part, c->d_yf, c->d_resid, c->d_M, c->d_cT, c->d_split, c->pb, true}; }
 
 int64_t tt_workspace_bytes(const tt_ctx *c, int forward_batch)
 {
@@ -646,16 +694,25 @@ int tt_set_workspace(tt_ctx *c, void *work, size_t bytes)
     if (!c) return fail(TT_EINVAL, "ctx is null");
     if (!work) return fail(TT_EINVAL, "workspace is null");
     if (reinterpret_cast<uintptr_t>(work) % 256) return fail(TT_EINVAL, "workspace must be 256-byte aligned");
-    const size_t base = ws_layout(c, 0).total;
-    const long long fit = bytes > base ? (long long)((bytes - base) / c->per_proj) : 0;
-    int pb = batch_round_down(c, fit);
+    // with the scratch of the adjoint's splits where that leaves a valid workspace
+    const size_t base = ws_layout(c, 0, false).total;
+    auto fitting = [&](size_t fixed) {
+        return batch_round_down(c, bytes > fixed ? (long long)((bytes - fixed) / c->per_proj) : 0);
+    };
+    bool split = split_bytes(c) > 0 && bytes >= base + split_bytes(c);
+    int pb = fitting(split ? base + split_bytes(c) : base);
+    if (split && ws_layout(c, pb, true).total > bytes) pb = batch_round_down(c, pb - 1);  // the alignment gap
+    if (split && pb < batch_min(c) && c->d.sparse_k == 0) {
+        split = false;
+        pb = fitting(base);
+    }
     if (pb < batch_min(c)) {
         if (c->d.sparse_k == 0 || bytes < base)
             return fail(TT_EINVAL, "workspace of " + std::to_string(bytes) + " bytes is below the minimum of " +
-                                       std::to_string(c->d.sparse_k ? base : (size_t)tt_workspace_bytes(c, 1)));
+                                       std::to_string(c->d.sparse_k ? base : ws_layout(c, batch_min(c), false).total));
         pb = 0;  // the fused forward needs no mapped volumes
     }
-    const WsLayout L = ws_layout(c, pb);
+    const WsLayout L = ws_layout(c, pb, split);
     c->ws = static_cast<char *>(work);
     c->ws_bytes = bytes;
     c->pb = pb;
@@ -664,6 +721,7 @@ int tt_set_workspace(tt_ctx *c, void *work, size_t bytes)
     c->d_resid = reinterpret_cast<float *>(c->ws + L.resid);
     c->d_M = reinterpret_cast<float *>(c->ws + L.M);
     c->d_cT = reinterpret_cast<float *>(c->ws + L.cT);
+    c->d_split = split ? reinterpret_cast<float *>(c->ws + L.split) : nullptr;
     // the map writes only interior voxels: the border of every mapped volume stays zero
     if (pb > 0) TT_HIP(hipMemsetAsync(c->d_M, 0, c->per_proj * (size_t)pb, c->stream));
     return TT_OK;
@@ -779,8 +837,8 @@ static int backproject_sc(tt_ctx *c, const Scratch &sc, float *g, float beta, co
     hipError_t e;
     {
         KTimer t(c, TT_K_BACKPROJECT, sc.timed);
-        e = launch_backproject(c->d, c->d_frames, sc.yf, c->d_Bu, c->d_BuT16, c->precision == TT_MAP_BF16, g, beta,
-                               cin, partials, c->stream);
+        e = launch_backproject(c->d, c->d_frames, sc.yf, {c->d_Bu, c->d_BuT16, c->d_Bop}, sc.split,
+                               c->precision == TT_MAP_BF16, g, beta, cin, partials, c->stream);
     }
     if (e != hipSuccess) return fail(e == hipErrorNotSupported ? TT_EUNSUPPORTED : TT_EHIP,
                                      std::string("backproject: ") + hipGetErrorString(e));
@@ -842,7 +900,7 @@ int tt_loss_grad_noalloc(tt_ctx *c, const float *cin, const float *data, const f
     if (!base) return fail(TT_EHIP, "the library's static scratch is not available on device " +
                                         std::to_string(c->device));
     // same layout as an attached workspace, the batch as large as the array allows
-    WsLayout L = ws_layout(c, 0);
+    WsLayout L = ws_layout(c, 0, false);
     if (resid) {  // the residual goes to the caller's buffer: no data-sized scratch
         const size_t shift = L.cT - L.resid;
         L.cT -= shift;
@@ -850,9 +908,13 @@ int tt_loss_grad_noalloc(tt_ctx *c, const float *cin, const float *data, const f
         L.total -= shift;
     }
     const size_t cap = kStaticScratchBytes;
-    const long long fit = cap > L.total ? (long long)((cap - L.total) / c->per_proj) : 0;
     const bool fused = c->d.sparse_k > 0;  // the fused forward maps nothing
-    const int pb = fused ? 0 : batch_round_down(c, fit);
+    auto fitting = [&](size_t fixed) {
+        return fused ? 0 : batch_round_down(c, cap > fixed ? (long long)((cap - fixed) / c->per_proj) : 0);
+    };
+    int pb = fitting(L.total + split_bytes(c) + 256);  // (with the alignment gap)
+    const bool split = split_bytes(c) > 0 && L.total + split_bytes(c) <= cap && (fused || pb >= batch_min(c));
+    if (!split) pb = fitting(L.total);
     if (fused ? L.total > cap : pb < batch_min(c))
         return fail(TT_ENOMEM, "problem needs " +
                                    std::to_string(L.total + (fused ? 0 : c->per_proj * (size_t)batch_min(c))) +
@@ -864,6 +926,7 @@ int tt_loss_grad_noalloc(tt_ctx *c, const float *cin, const float *data, const f
     sc.resid = resid ? nullptr : reinterpret_cast<float *>(base + L.resid);
     sc.M = reinterpret_cast<float *>(base + L.M);
     sc.cT = reinterpret_cast<float *>(base + L.cT);
+    sc.split = split ? reinterpret_cast<float *>(base + L.M + align256(c->per_proj * (size_t)pb)) : nullptr;
     sc.pb = pb;
     sc.timed = false;
     // the map writes interior voxels only; the array holds whatever the last

@@ -219,12 +219,17 @@ void build_frames(const Geometry &g, std::vector<ProjFrame> &frames, std::vector
             f.jos_rj = (float)((std::fabs(gkB) + std::fabs(gkC)) / std::fabs(det));
             f.jos_rk = (float)((std::fabs(gjB) + std::fabs(gjC)) / std::fabs(det));
         }
+        int a0 = 0;
+        for (int a = 1; a < 3; ++a)
+            if (std::fabs(f.d[a]) > std::fabs(f.d[a0])) a0 = a;
         for (int a = 0; a < 3; ++a) {
-            f.ejf[a] = (float)f.ej[a];
-            f.ekf[a] = (float)f.ek[a];
-            f.df[a] = (float)f.d[a];
-            f.inv_df[a] = f.inv_d[a] != 0.0 ? (float)f.inv_d[a] : kFlatInv;
+            const int src = (a0 + a) % 3;
+            f.ejf[a] = (float)f.ej[src];
+            f.ekf[a] = (float)f.ek[src];
+            f.df[a] = (float)f.d[src];
         }
+        f.inv_d0 = (float)(1.0 / f.d[a0]);
+        f.n_tau = (int)std::min(1e9, std::max(1.0, std::ceil(2.0 / (std::fabs(f.d[a0]) * g.step) - 1e-5)));
         for (int c = 0; c < g.n_seg; ++c) {
             double *row = &B[((size_t)s * g.n_seg + c) * C];
             for (int m = 0; m < g.n_sub; ++m) {

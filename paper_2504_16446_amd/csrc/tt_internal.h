@@ -25,7 +25,7 @@ struct Geometry {
 // Number of basis functions of a geometry (SH count or grid size).
 int basis_count(const Geometry &g);
 
-// Stand-in for 1 / 0 in branch-free parameter ranges (see ProjFrame::inv_df).
+// Stand-in for 1 / 0 in branch-free parameter ranges (see ProjFrame::jos_igk).
 constexpr float kFlatInv = 1.0e30f;
 
 // Ray frame of one projection, float64, in centred sample coordinates.
@@ -40,12 +40,12 @@ struct ProjFrame {
     // k - b in [max_i(lo_i y + lo_i'), min_i(up_i y + up_i')] (hull[0..5] the
     // upper chain as (slope, intercept) pairs, hull[6..11] the lower chain).
     float hull[12];
-    float ejf[3], ekf[3], df[3];  // float copies for the small offsets inside the cube
-    // 1 / d_a, or kFlatInv when the ray is parallel to plane a: the adjoint's
-    // parameter range |P_a + tau d_a| < 1 then reads (-P_a - 1, -P_a + 1) *
-    // kFlatInv, which is all tau for |P_a| < 1 and empty otherwise, and some
-    // other axis (|d_b| >= 1/sqrt 3) always bounds the range.
-    float inv_df[3];
+    // Float copies for the small offsets inside the cube, the dominant axis of d
+    // first; 1 / d of that axis; and the most samples (spacing step) that a ray
+    // can have where it is within one voxel along it: ceil(2 / (|d_0| step)).
+    float ejf[3], ekf[3], df[3];
+    float inv_d0;
+    int n_tau;
     // Slab plan of the LDS-staged march (tiles of kMarchTile x kMarchTile
     // rays): slabs are planes of axis slab_a (0 = x, 1 = y); each slab holds
     // the samples whose cell lies in slab_w consecutive planes, and stages a
@@ -62,7 +62,10 @@ struct ProjFrame {
     int jos_a;
     float jos_w;
     float jos_gj[2], jos_gk[2];
-    float jos_igk[2];  // 1 / jos_gk, or kFlatInv where |jos_gk| <= 1e-6 (see inv_df)
+    // 1 / jos_gk, or kFlatInv where |jos_gk| <= 1e-6: the range |dk g + e| < 1 then
+    // reads (-e - 1, -e + 1) * kFlatInv, all dk for |e| < 1 and none otherwise (the
+    // other in-plane axis is never flat, so a non-empty range is finite)
+    float jos_igk[2];
     float jos_rj, jos_rk;
 };
 
@@ -78,6 +81,14 @@ int plan_slabs(std::vector<ProjFrame> &frames, int up, int lds_budget);
 // ---------------------------------------------------------------------------
 // Kernel launchers (tt_proj.hip, tt_vec.hip).  All asynchronous on `st`.
 // ---------------------------------------------------------------------------
+// Staged adjoint of one projector model: point-inversion pairing, dynamic LDS
+// bytes (0: not used), window rows / columns, and splits of the projections over
+// blocks (each needs a coefficient volume of scratch; 1: none).
+struct AdjointPlan {
+    int pair, lds, wr, wc, splits;
+};
+constexpr int kMaxSplits = 8;
+
 struct Dims {
     int nx, ny, nz;     // volume
     int C, Cp;          // coefficients, padded to a multiple of 16
@@ -86,14 +97,9 @@ struct Dims {
     float step;         // sample spacing of the trilinear model (1 for Joseph: no step factor)
     int march_lds;      // dynamic LDS bytes of the staged march (0: no projection staged)
     int joseph;         // 0: unit-step trilinear samples, 1: Joseph's method
-    int inv_pair;       // 1: point-inversion-symmetric geometry (no detector offsets, even nx):
-                        //    the adjoint (either model) with four or eight unique segments
-                        //    enumerates each voxel pair (v, -v) once
-    int win_ok;         // 1: every projection's residual window of a 4 x 8 x 8 brick fits the
-                        //    adjoint's LDS window (trilinear model, eight unique segments)
-    int pw_lds, pw_wr, pw_wc;  // paired + windowed adjoint: dynamic LDS bytes (0: not used) and
-                               // window rows / columns
-    int pwj_lds, pwj_wr, pwj_wc;  // the same for Joseph's method
+    int inv_pair;       // 1: point-inversion-symmetric geometry (no detector offsets, even nx): the
+                        //    adjoint (either model) enumerates each voxel pair (v, -v) once
+    AdjointPlan adj[2];  // staged adjoint of the trilinear model and of Joseph's method
     int sparse_k = 0;   // 0: exact basis constants, map + march; >= 1: kept basis functions per
                         //    (projection, segment) of the sparse map, fused forward
     int sparse_ng = 0;  // fused forward: channels per projection's list (the most any projection uses)
@@ -132,17 +138,22 @@ hipError_t launch_fold(const Dims &d, const float *y, float scale, float *yf, hi
 hipError_t launch_residual_fold(const Dims &d, const float *Ip, const float *data, const float *w,
                                 float *r, float *yf, double *partials, int nblocks, hipStream_t st);
 // g = A^T-part(yf) + beta c, with float64 partials of sum c^2 when c != null.
-// bf16 != 0: the transpose map runs on bf16 MFMA with Q rounded to bf16 and
-// BuT16[s][Cp][16] (bf16, u padded to 16 with zeros).
-hipError_t launch_backproject(const Dims &d, const ProjFrame *frames, const float *yf,
-                              const float *Bu, const uint16_t *BuT16, int bf16, float *g, float beta,
-                              const float *c, double *partials, hipStream_t st);
+// bf16 != 0: the transpose map rounds Q and B to bf16.
+struct AdjointTables {
+    const float *Bu;        // [S Up][Cp]
+    const uint16_t *BuT16;  // [S][Cp][16]: bf16 B^T, u padded with zeros
+    const uint16_t *Bop;    // [S][6][Cp][8]: operands of the staged adjoint (see build_tables)
+};
+// split: scratch of d.adj[d.joseph].splits coefficient volumes, or null (no splits).
+hipError_t launch_backproject(const Dims &d, const ProjFrame *frames, const float *yf, const AdjointTables &t,
+                              float *split, int bf16, float *g, float beta, const float *c, double *partials,
+                              hipStream_t st);
 // Blocks (= float64 partials) of the adjoint launch; the largest over the
 // adjoint variants of a geometry.
 int backproject_blocks(const Dims &d);
 int backproject_blocks_max(const Dims &d);
-bool backproject_window_fits(const std::vector<ProjFrame> &frames);
-int backproject_pw_lds(const std::vector<ProjFrame> &frames, int up, bool jos, int &wr, int &wc);
+// Sets d.adj from the ray frames (d otherwise complete).
+void plan_adjoint(const std::vector<ProjFrame> &frames, Dims &d);
 
 // Derived per-voxel quantities: out[v][kPropFields] from c[v][C] (tt_props.hip).
 constexpr int kPropFields = 22;

@@ -1202,6 +1202,61 @@ __device__ __forceinline__ float qw_at(const float *Qw, int nt, int ks, int lane
     return Qw[(nt * 16 + (lane & 15)) * (UP + 1) + ks * 4 + (lane >> 4)];
 }
 
+// Samples of one ray inside the cube of a voxel.  The dominant axis of d comes
+// first in the frame's float vectors: |P_0 + tau d_0| < 1 bounds tau to an
+// interval of length 2 / |d_0| that holds at most n_tau samples, and the tent
+// factors, clamped at 0, drop those outside the cube along the other axes.
+// So every ray evaluates the same n_tau samples (three, or four for steep
+// diagonals, at step 1) without a branch; kept as a range per ray over all
+// three axes, a loop and its exec masks, the adjoint's lanes waited for the
+// ray with the most samples at every step.
+struct TentRay {
+    float d[3], sd[3];  // ray direction, and the sample spacing along each axis
+    float ca, cb;       // first sample: n = ceil(ca P_0 + cb)
+    float step, off;    // tau = step n + off
+    int more;           // samples beyond three (uniform over the projection)
+};
+
+__device__ __forceinline__ TentRay tent_ray(const ProjFrame &f, float tr, float step, float inv_step)
+{
+    TentRay t;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        t.d[a] = f.df[a];
+        t.sd[a] = step * f.df[a];
+    }
+    t.ca = -f.inv_d0 * inv_step;
+    t.cb = tr - fabsf(f.inv_d0) * inv_step;
+    t.step = step;
+    t.off = -tr * step;
+    t.more = f.n_tau - 3;
+    return t;
+}
+
+// max(0, 1 - |x|), one instruction (clamp modifier)
+__device__ __forceinline__ float tent1(float x) { return __builtin_amdgcn_fmed3f(1.0f - fabsf(x), 0.0f, 1.0f); }
+
+__device__ __forceinline__ float ray_weight(const float P[3], const TentRay &t)
+{
+    const float tau = fmaf(ceilf(fmaf(t.ca, P[0], t.cb)), t.step, t.off);
+    float x = fmaf(tau, t.d[0], P[0]), y = fmaf(tau, t.d[1], P[1]), z = fmaf(tau, t.d[2], P[2]);
+    float w = tent1(x) * tent1(y) * tent1(z);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        x += t.sd[0];
+        y += t.sd[1];
+        z += t.sd[2];
+        w = fmaf(tent1(x) * tent1(y), tent1(z), w);
+    }
+    for (int i = 0; i < t.more; ++i) {
+        x += t.sd[0];
+        y += t.sd[1];
+        z += t.sd[2];
+        w = fmaf(tent1(x) * tent1(y), tent1(z), w);
+    }
+    return w;
+}
+
 template <int UP, int MT, bool BF16, bool JOS>
 __global__ __launch_bounds__(256) void k_backproject(const float *__restrict__ yf, const ProjFrame *__restrict__ frames,
                                                      const float *__restrict__ Bu, const s4 *__restrict__ BuT16, int S, int nx, int ny, int nz,
@@ -1323,11 +1378,7 @@ __global__ __launch_bounds__(256) void k_backproject(const float *__restrict__ y
             const double af = floor(a), bf = floor(bb), tf = floor(ts);
             const int ai = (int)af, bi = (int)bf, ti = (int)tf;
             const float ar = (float)(a - af), br = (float)(bb - bf), tr = (float)(ts - tf);
-            const float hinv[3] = {fabsf(f.inv_df[0]), fabsf(f.inv_df[1]), fabsf(f.inv_df[2])};
-            // -|1/d| per axis, held in vector registers: the range fma below
-            // already reads 1/d from a scalar register, and a VOP3 takes one
-            float nhv[3] = {-hinv[0], -hinv[1], -hinv[2]};
-            asm volatile("" : "+v"(nhv[0]), "+v"(nhv[1]), "+v"(nhv[2]));
+            const TentRay tent = tent_ray(f, tr, stepf, inv_stepf);
             const float ljf = (float)f.lj;
             const int jlo = max(0, ai + (int)ceilf(ar - ljf));
             const int jhi = valid ? min(nj - 1, ai + (int)floorf(ar + ljf)) : jlo - 1;
@@ -1355,28 +1406,7 @@ __global__ __launch_bounds__(256) void k_backproject(const float *__restrict__ y
 #pragma unroll
                     for (int u4 = 0; u4 < UP / 4; ++u4) yv[u4] = yrow[k * (UP / 4) + u4];  // in flight meanwhile
                     const float P[3] = {fmaf(dk, f.ekf[0], pj0), fmaf(dk, f.ekf[1], pj1), fmaf(dk, f.ekf[2], pj2)};
-                    // parameter range along the ray inside the open cube: |P_m + tau d_m| < 1
-                    // for every axis (branch-free: see kFlatInv for rays parallel to a face)
-                    float tlo = fmaf(-P[0], f.inv_df[0], nhv[0]), thi = fmaf(-P[0], f.inv_df[0], hinv[0]);
-#pragma unroll
-                    for (int m = 1; m < 3; ++m) {
-                        tlo = fmaxf(tlo, fmaf(-P[m], f.inv_df[m], nhv[m]));
-                        thi = fminf(thi, fmaf(-P[m], f.inv_df[m], hinv[m]));
-                    }
-                    // samples n with tau = n step - t inside (tlo, thi): n from m0 to m1
-                    // (none if the range is empty); there every |P_m + tau d_m| < 1, so
-                    // the tent factors need no clamp at 0 (a sample at the boundary
-                    // gives a factor of rounding size).  The loop runs on tau itself,
-                    // whose end is put half a step past the last sample.
-                    float wsum = 0.0f;
-                    const float m0 = ceilf(fmaf(tlo, inv_stepf, tr)), m1 = floorf(fmaf(thi, inv_stepf, tr));
-                    const float tend = (m1 - tr + 0.5f) * stepf;
-                    for (float tau = (m0 - tr) * stepf; tau < tend; tau += stepf) {
-                        const float wx = 1.0f - fabsf(fmaf(tau, f.df[0], P[0]));
-                        const float wy = 1.0f - fabsf(fmaf(tau, f.df[1], P[1]));
-                        const float wz = 1.0f - fabsf(fmaf(tau, f.df[2], P[2]));
-                        wsum = fmaf(wx * wy, wz, wsum);
-                    }
+                    const float wsum = ray_weight(P, tent);
 #pragma unroll
                     for (int u4 = 0; u4 < UP; u4 += 4) {
                         q[u4 + 0] = fmaf(wsum, yv[u4 / 4].x, q[u4 + 0]);
@@ -1462,50 +1492,191 @@ __global__ __launch_bounds__(256) void k_backproject(const float *__restrict__ y
 
 
 // ---------------------------------------------------------------------------
-// backproject, paired by point inversion (trilinear model, no detector
-// offsets, even nx, four unique segments).  The sample lattice of a projection,
-// o + j e_j + k e_k + n step d with o = -((nj-1)/2 e_j + (nk-1)/2 e_k), is
-// symmetric under x -> -x with (j, k, n) -> (nj-1-j, nk-1-k, -n); the voxel
-// grid and the tent are symmetric too.  So the weight of ray (j, k) at voxel
-// v equals the weight of ray (nj-1-j, nk-1-k) at the inverted voxel
-// v' = (nx-1-ix, ny-1-iy, nz-1-iz), and one enumeration of v's rays and
-// samples gives Q_s(v) and Q_s(v') (the second from the mirrored residual
-// rows).  Block: waves 0, 1 own x-slices 2 bx + w of the lower half
-// (ix < nx / 2) over an 8 x 8 (y, z) tile; waves 2, 3 own the inverses of
-// waves 0, 1's voxels lane by lane.  Per pair of projections (s, s + 1) the
-// lower waves enumerate s and the upper waves s + 1; each hands the
-// partner's Q through LDS, and each wave then contracts both projections'
-// Q with B^T on MFMA into its own accumulators.  Enumeration work per voxel
-// and projection is halved; the transpose maps are unchanged.
+// backproject with LDS-staged residual windows (four or eight unique segments).
+//
+// A block owns bricks of 64-voxel cubes (4 x 4 x 4, one per wave) and walks the
+// projections two at a time.  Per pair it stages two detector windows (the
+// brick's shadow widened by one voxel's reach) with gfx950's direct
+// global-to-LDS copies, every lane enumerates the rays of its voxel from LDS,
+// and each wave contracts its voxels' Q of both projections with B^T on MFMA,
+// accumulating g in registers over all projections.
+//
+// PAIR (no detector offsets, even nx): the sample lattice
+// o + j e_j + k e_k + n step d with o = -((nj-1)/2 e_j + (nk-1)/2 e_k) is
+// symmetric under x -> -x with (j, k, n) -> (nj-1-j, nk-1-k, -n), and so are
+// the voxel grid, the tent and Joseph's cuts.  So the weight of ray (j, k) at
+// voxel v is that of ray (nj-1-j, nk-1-k) at the inverted voxel v', and one
+// enumeration serves both.  Waves 0, 1 own two cubes of the lower half
+// (ix < nx / 2), waves 2, 3 their inverses lane by lane; the lower group
+// enumerates s0, the upper s0 + 1, from a window that holds each ray's own and
+// reflected residual side by side, and hands the inverse's Q to the partner
+// wave.  Without PAIR every wave enumerates both projections.
+//
+// What bounds it: VALU issue, which the MFMAs share.  Counters of the kernel
+// this one replaced (128^3, 300 projections, eight unique segments): 718 VALU
+// instructions (4 cycles each) and 48 fp32 MFMAs (32 cycles each) per wave and
+// pair, together 90% of the SIMD cycles.  Hence:
+//  - the contraction runs on 16x16x32 bf16 MFMA with B and Q in three bf16 pieces
+//    each (x = x0 + x1 + x2 to 2^-27): the six products b0q0 b0q1 b1q0 b1q1 b0q2
+//    b2q0 of two projections fill K = 32 three times (eight segments: 36 MFMAs of
+//    16 cycles per pair instead of 48 of 32).  The dropped products are below
+//    2^-26 of the result, under the rounding of an fp32 sum;
+//  - windows have one size for all projections, so a lane's place in a window and
+//    its source offset from the window origin are computed once, and a copy is
+//    one add and one instruction;
+//  - window origins (the same for all lanes) are worked out by one lane per
+//    projection, 64 pairs at a time;
+//  - the tent samples of a ray are a fixed number without branches (ray_weight).
+// Adjoint, before -> now: 256^3 / 400 projections / 8 unique segments 118.1 -> 76.3 ms;
+// 128^3 / 300 / 8 11.3 -> 7.3; 100^3 / 240 / 4 2.89 -> 2.22 (Joseph 1.95 -> 1.61);
+// 97 x 89 x 107 / 220 / 8 with detector offsets (unpaired) 4.79 -> 3.39; relative
+// error against float64 4.7e-7 -> 1.3e-7 (100^3), 7.2e-7 -> 3.9e-7 (128^3, with the
+// forward's).  Now bound by VALU issue alone (89% of the cycles at 128^3).
 // ---------------------------------------------------------------------------
-template <int UP, int MT, bool BF16, bool JOS>
-__global__ __launch_bounds__(256) void k_backproject_inv(const float *__restrict__ yf,
-                                                         const ProjFrame *__restrict__ frames,
-                                                         const float *__restrict__ Bu, const s4 *__restrict__ BuT16,
-                                                         int S, int nx, int ny, int nz, int nj, int nk, int C, int Cp,
-                                                         float step, float *__restrict__ g, float beta,
-                                                         const float *__restrict__ c, double *__restrict__ partials)
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+
+// x0 + x1 + x2 = x to 2^-27 relative, two values per word (bf16, nearest even)
+__device__ __forceinline__ void split_bf16(float a, float b, unsigned &h, unsigned &m, unsigned &l)
 {
-    constexpr int QS = 64 * (UP + 1);
-    __shared__ float Qs[4][QS];      // each wave's own Q (wave-private)
-    __shared__ float Qx[2][4][QS];   // Q handed over by the partner wave, double-buffered
+    h = __builtin_bit_cast(unsigned, __builtin_convertvector((f2{a, b}), bf2));
+    a -= __uint_as_float(h << 16);
+    b -= __uint_as_float(h & 0xffff0000u);
+    m = __builtin_bit_cast(unsigned, __builtin_convertvector((f2{a, b}), bf2));
+    a -= __uint_as_float(m << 16);
+    b -= __uint_as_float(m & 0xffff0000u);
+    l = __builtin_bit_cast(unsigned, __builtin_convertvector((f2{a, b}), bf2));
+}
+
+// Operand tiles of Q in LDS, 16 bytes per voxel: with eight segments one tile per
+// piece; with four [q0 | q1] and [q2 | q0] (bf16 tier: [q0 | 0]).  K = 32 then holds
+// one product of four projections, so two pairs share a contraction.
+// It pays from 48 padded coefficients on (fewer MFMAs and adds); below, the smaller
+// tiles leave room for more blocks.
+template <int UP, int MT>
+constexpr int kPairs = UP == 4 && MT >= 3 ? 2 : 1;
+template <int UP, bool BF16>
+constexpr int kQTiles = BF16 ? 1 : (UP == 8 ? 3 : 2);
+
+template <int UP, bool BF16>
+__device__ __forceinline__ void put_q(const float *q, uint4 *t, int stride)
+{
+    unsigned h[UP / 2], m[UP / 2], l[UP / 2];
+#pragma unroll
+    for (int i = 0; i < UP / 2; ++i) split_bf16(q[2 * i], q[2 * i + 1], h[i], m[i], l[i]);
+    if constexpr (UP == 8) {
+        t[0] = make_uint4(h[0], h[1], h[2], h[3]);
+        if constexpr (!BF16) {
+            t[stride] = make_uint4(m[0], m[1], m[2], m[3]);
+            t[2 * stride] = make_uint4(l[0], l[1], l[2], l[3]);
+        }
+    } else if constexpr (BF16) {
+        t[0] = make_uint4(h[0], h[1], 0u, 0u);
+    } else {
+        t[0] = make_uint4(h[0], h[1], m[0], m[1]);
+        t[stride] = make_uint4(l[0], l[1], h[0], h[1]);
+    }
+}
+
+constexpr int kWinCopies = 6;  // copies of 128 float4 per window and pair (at most)
+
+template <int UP, int MT, bool BF16, bool JOS, bool PAIR>
+__global__ __launch_bounds__(256, MT <= 3 ? 3 : 1) void k_backproject_win(const float *__restrict__ yf,
+                                                         const ProjFrame *__restrict__ frames,
+                                                         const uint4 *__restrict__ Bop, int S, int nx, int ny, int nz,
+                                                         int nj, int nk, int C, int Cp, float step,
+                                                         float *__restrict__ g, float beta, const float *__restrict__ c,
+                                                         double *__restrict__ partials, int WR, int WC, int s_per,
+                                                         float *__restrict__ split)
+{
+    // blockIdx.y > 0: the projections are split over blocks, each of which writes
+    // its own sum to split[blockIdx.y][V C] (added in order by k_add_splits)
+    const int s_begin = blockIdx.y * s_per, s_end = min(S, s_begin + s_per);
+    constexpr int Q = UP / 4;               // float4 per ray
+    constexpr int RW = PAIR ? 2 * Q : Q;    // float4 per staged ray: own, then reflected
+    constexpr int QT = kQTiles<UP, BF16>;
+    extern __shared__ f4 wins[];            // [2][WR * WC * RW rounded up to 128]
+    constexpr int PB = kPairs<UP, MT>;      // pairs per contraction
+    constexpr int QS = 2 * PB * 64;         // stride of the operand tiles
+    __shared__ uint4 Qt[4][QT][2 * PB][64];  // [wave][tile][projection][voxel]
+    __shared__ int2 wtab[2][64];            // window origins of the next 64 pairs
     __shared__ double ws[4];
     const int tid = threadIdx.x, lane = tid & 63;
-    // wave-uniform (scalar) wave index: the projection each wave enumerates, and
-    // hence its frame loads, stay in scalar registers
+    // wave-uniform (scalar) wave index: frames and windows stay in scalar registers
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool upper = wave >= 2;
-    const int nxh = nx >> 1;
-    const int nbx = (nxh + 1) / 2, nby = (ny + 7) / 8;
+    const int grp = wave >> 1;              // PAIR: lower / upper voxel group; also the window this wave stages
+    const bool upper = PAIR && grp == 1;
+    const int nxh = PAIR ? nx >> 1 : nx;
+    const int nbx = (nxh + 3) / 4, nby = PAIR ? (ny + 3) / 4 : (ny + 7) / 8;
     const int bid = xcd_block(blockIdx.x, gridDim.x);
     const int bx = bid % nbx, by = (bid / nbx) % nby, bz = bid / (nbx * nby);
-    // the lower-half voxel of this lane's pair, and this wave's own voxel
-    const int px = bx * 2 + (wave & 1), py = by * 8 + (lane >> 3), pz = bz * 8 + (lane & 7);
+    const int x0 = 4 * bx, y0 = PAIR ? 4 * by : 8 * by + 4 * (wave >> 1), z0 = 8 * bz + 4 * (wave & 1);
+    // this lane's voxel (PAIR: the lower voxel of its pair, then its own)
+    const int px = x0 + (lane >> 4), py = y0 + ((lane >> 2) & 3), pz = z0 + (lane & 3);
     const bool valid = px < nxh && py < ny && pz < nz;
     const int ix = upper ? nx - 1 - px : px, iy = upper ? ny - 1 - py : py, iz = upper ? nz - 1 - pz : pz;
     const double xv[3] = {ix - 0.5 * (nx - 1), iy - 0.5 * (ny - 1), iz - 0.5 * (nz - 1)};
     const double inv_step = 1.0 / (double)step;
-    const float stepf = step, inv_stepf = (float)inv_step;
+
+    // window origin of projection s: the first row and column that a voxel of the
+    // box can reach (one more for rounding), moved so that WR x WC rays fit the detector
+    auto origin = [&](int s, bool inverted) {
+        const ProjFrame &f = frames[s];
+        const double lo0[3] = {4 * bx - 0.5 * (nx - 1), (PAIR ? 4 : 8) * by - 0.5 * (ny - 1), 8 * bz - 0.5 * (nz - 1)};
+        const double hi0[3] = {min(nxh, 4 * bx + 4) - 1 - 0.5 * (nx - 1),
+                               min(ny, (PAIR ? 4 : 8) * (by + 1)) - 1 - 0.5 * (ny - 1),
+                               min(nz, 8 * bz + 8) - 1 - 0.5 * (nz - 1)};
+        double a = 0.0, b = 0.0;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const double lo = inverted ? -hi0[q] : lo0[q], hi = inverted ? -lo0[q] : hi0[q];
+            a += ((f.ej[q] >= 0.0 ? lo : hi) - f.o[q]) * f.ej[q];
+            b += ((f.ek[q] >= 0.0 ? lo : hi) - f.o[q]) * f.ek[q];
+        }
+        const double rj = JOS ? (double)f.jos_rj : f.lj, rk = JOS ? (double)f.jos_rk : f.lk;
+        return make_int2(max(0, min(nj - WR, (int)ceil(a - rj) - 1)), max(0, min(nk - WC, (int)ceil(b - rk) - 1)));
+    };
+    // origins of both windows of 64 pairs from s0 on (waves 0 and 1); the table is
+    // read only between a pair's second barrier and the next pair's first
+    auto fill_origins = [&](int s0) {
+        if (wave < 2 && s0 + 2 * lane + wave < s_end) wtab[wave][lane] = origin(s0 + 2 * lane + wave, PAIR && wave == 1);
+    };
+    int wj[2] = {0, 0}, wk[2] = {0, 0};
+    auto take_origins = [&](int s0) {
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            const int2 o = wtab[w][((s0 - s_begin) >> 1) & 63];
+            wj[w] = __builtin_amdgcn_readfirstlane(o.x);
+            wk[w] = __builtin_amdgcn_readfirstlane(o.y);
+        }
+    };
+
+    // The two waves of a group stage window grp.  Copy i moves elements
+    // (2 i + wave % 2) 64 + lane; a lane always copies the same part of a ray
+    // (64 is a multiple of RW), so its source byte offset from the projection's
+    // residual is a constant plus (own part) or minus (reflected part) the offset
+    // of the window origin.  Elements past the window repeat its last ray.
+    const int nel = WR * WC * RW, wsz = (nel + 127) & ~127;
+    const bool refl = PAIR && (lane & (RW - 1)) >= Q;
+    unsigned soff[kWinCopies];
+#pragma unroll
+    for (int i = 0; i < kWinCopies; ++i) {
+        const int e = (2 * i + (wave & 1)) * 64 + lane;
+        const int ray = min(e / RW, WR * WC - 1), part = lane & (RW - 1);
+        const int r = ray / WC, rel = r * nk + (ray - r * WC);
+        soff[i] = 16u * (unsigned)(refl ? (nj * nk - 1 - rel) * Q + part - Q : rel * Q + part);
+    }
+    auto stage = [&](int s) {
+        const char *src = reinterpret_cast<const char *>(yf) + (long long)s * nj * nk * Q * 16;
+        const int o = ((grp ? wj[1] : wj[0]) * nk + (grp ? wk[1] : wk[0])) * Q * 16;
+        const unsigned d = refl ? -(unsigned)o : (unsigned)o;
+        f4 *dst = wins + grp * wsz + (wave & 1) * 64;
+#pragma unroll
+        for (int i = 0; i < kWinCopies; ++i)
+            if (i * 128 < nel)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + (soff[i] + d)),
+                                                 (__attribute__((address_space(3))) void *)(dst + i * 128), 16, 0, 0);
+    };
 
     f4 acc[MT][4];
 #pragma unroll
@@ -1513,795 +1684,192 @@ __global__ __launch_bounds__(256) void k_backproject_inv(const float *__restrict
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = f4{0.f, 0.f, 0.f, 0.f};
 
-    // B_s^T operands of one projection in MFMA lane order (loaded at the top of
-    // an iteration, so that the enumeration hides their latency)
-    struct BOps {
-        s4 b16[BF16 ? MT : 1];
-        float f[BF16 ? 1 : UP / 4][MT];
-    };
-    auto load_ops = [&](int s, BOps &o) {
-        if constexpr (BF16) {
+    fill_origins(s_begin);
+    __syncthreads();
+    take_origins(s_begin);
+    if (s_begin + grp < s_end) stage(s_begin + grp);
+    for (int s0 = s_begin; s0 < s_end; s0 += 2) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();  // this pair's windows are staged
+#pragma unroll 1
+        for (int h = 0; h < (PAIR ? 1 : 2); ++h) {
+            const int w = PAIR ? grp : h, s = s0 + w;  // window and projection enumerated
+            float q[UP], qm[UP];
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                o.b16[mt] = BuT16[((long long)s * Cp + mt * 16 + (lane & 15)) * 4 + (lane >> 4)];
-        } else {
-            const float *Bs = Bu + (long long)s * UP * Cp;
-#pragma unroll
-            for (int ks = 0; ks < UP / 4; ++ks)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) o.f[ks][mt] = Bs[(ks * 4 + (lane >> 4)) * Cp + mt * 16 + (lane & 15)];
-        }
-    };
-    // g tile += B_s^T (coefficients x u) * Q^T (u x voxels), Q from the LDS tile Qt
-    auto contract = [&](const BOps &o, const float *Qt) {
-        if constexpr (BF16) {
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const float *qv = Qt + (nt * 16 + (lane & 15)) * (UP + 1);
-                const int u0 = 4 * (lane >> 4);
-                s4 bv;
-                bv.x = u0 + 0 < UP ? f2bf(qv[min(u0 + 0, UP - 1)]) : (short)0;
-                bv.y = u0 + 1 < UP ? f2bf(qv[min(u0 + 1, UP - 1)]) : (short)0;
-                bv.z = u0 + 2 < UP ? f2bf(qv[min(u0 + 2, UP - 1)]) : (short)0;
-                bv.w = u0 + 3 < UP ? f2bf(qv[min(u0 + 3, UP - 1)]) : (short)0;
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = mfma16x16x16bf16(o.b16[mt], bv, acc[mt][nt]);
-            }
-        } else {
-#pragma unroll
-            for (int ks = 0; ks < UP / 4; ++ks) {
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt) {
-                    const float bv = qw_at<UP>(Qt, nt, ks, lane);
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = mfma16x16x4(o.f[ks][mt], bv, acc[mt][nt]);
-                }
-            }
-        }
-    };
-
-    int buf = 0;
-    for (int s0 = 0; s0 < S; s0 += 2) {
-        const int s_own = s0 + (upper ? 1 : 0), s_oth = s0 + (upper ? 0 : 1);
-        const bool has_own = s_own < S, has_oth = s_oth < S;
-        BOps ops_own, ops_oth;
-        load_ops(has_own ? s_own : s0, ops_own);
-        load_ops(has_oth ? s_oth : s0, ops_oth);
-        float q[UP], qm[UP];
-#pragma unroll
-        for (int u = 0; u < UP; ++u) q[u] = qm[u] = 0.0f;
-        if (has_own && valid) {
-            const ProjFrame &f = frames[s_own];
-            if constexpr (JOS) {
-                // Joseph's method: the rays whose cut with the voxel's layer lies
-                // within one voxel in-plane, weight (1 - |Delta_B|)(1 - |Delta_C|) /
-                // |d_A|; the inverse voxel's cut of the mirrored ray is the negated
-                // cut point, so the same weight serves both voxels of the pair
-                const double w0 = xv[0] - f.o[0], w1 = xv[1] - f.o[1], w2 = xv[2] - f.o[2];
-                const double a = w0 * f.ej[0] + w1 * f.ej[1] + w2 * f.ej[2];
-                const double bb = w0 * f.ek[0] + w1 * f.ek[1] + w2 * f.ek[2];
-                const double af = floor(a), bf = floor(bb);
-                const int ai = (int)af, bi = (int)bf;
-                const float ar = (float)(a - af), br = (float)(bb - bf);
-                const float gjB = f.jos_gj[0], gjC = f.jos_gj[1], gkB = f.jos_gk[0], gkC = f.jos_gk[1];
-                const int jlo = max(0, ai + (int)ceilf(ar - f.jos_rj));
-                const int jhi = min(nj - 1, ai + (int)floorf(ar + f.jos_rj));
-                const f4 *ys = reinterpret_cast<const f4 *>(yf + (long long)s_own * nj * nk * UP);
-                for (int j = jlo; j <= jhi; ++j) {
-                    const float dj = (float)(j - ai) - ar;
-                    const float eB = dj * gjB, eC = dj * gjC;
-                    // dk range with |dk gk + e| < 1 on both in-plane axes (a flat
-                    // axis gives all dk or none; the other one is never flat)
-                    const float xB1 = (-1.0f - eB) * f.jos_igk[0], xB2 = (1.0f - eB) * f.jos_igk[0];
-                    const float xC1 = (-1.0f - eC) * f.jos_igk[1], xC2 = (1.0f - eC) * f.jos_igk[1];
-                    const float lo = fmaxf(fminf(xB1, xB2), fminf(xC1, xC2));
-                    const float hi = fminf(fmaxf(xB1, xB2), fmaxf(xC1, xC2));
-                    if (!(lo < hi)) continue;
-                    const int klo = max(0, bi + (int)ceilf(br + lo - 1e-4f));
-                    const int khi = min(nk - 1, bi + (int)floorf(br + hi + 1e-4f));
-                    const f4 *yrow = ys + __umul24(j, nk * (UP / 4));
-                    // mirrored ray (nj-1-j, nk-1-k): row nj-1-j read backwards from column nk-1
-                    const f4 *yrowm = ys + __umul24(nj - 1 - j, nk * (UP / 4)) + (nk - 1) * (UP / 4);
-                    for (int k = klo; k <= khi; ++k) {
-                        f4 yv[UP / 4], ym[UP / 4];
-#pragma unroll
-                        for (int u4 = 0; u4 < UP / 4; ++u4) {
-                            yv[u4] = yrow[k * (UP / 4) + u4];
-                            ym[u4] = yrowm[u4 - k * (UP / 4)];
-                        }
-                        const float dk = (float)(k - bi) - br;
-                        const float wB = fmaxf(0.0f, 1.0f - fabsf(fmaf(dk, gkB, eB)));
-                        const float wC = fmaxf(0.0f, 1.0f - fabsf(fmaf(dk, gkC, eC)));
-                        const float wt = wB * wC * f.jos_w;
-#pragma unroll
-                        for (int u4 = 0; u4 < UP; u4 += 4) {
-                            q[u4 + 0] = fmaf(wt, yv[u4 / 4].x, q[u4 + 0]);
-                            q[u4 + 1] = fmaf(wt, yv[u4 / 4].y, q[u4 + 1]);
-                            q[u4 + 2] = fmaf(wt, yv[u4 / 4].z, q[u4 + 2]);
-                            q[u4 + 3] = fmaf(wt, yv[u4 / 4].w, q[u4 + 3]);
-                            qm[u4 + 0] = fmaf(wt, ym[u4 / 4].x, qm[u4 + 0]);
-                            qm[u4 + 1] = fmaf(wt, ym[u4 / 4].y, qm[u4 + 1]);
-                            qm[u4 + 2] = fmaf(wt, ym[u4 / 4].z, qm[u4 + 2]);
-                            qm[u4 + 3] = fmaf(wt, ym[u4 / 4].w, qm[u4 + 3]);
-                        }
-                    }
-                }
-            } else {
+            for (int u = 0; u < UP; ++u) q[u] = qm[u] = 0.0f;
+            if (s < s_end && valid) {
+                const ProjFrame &f = frames[s];
+                const int j0 = w ? wj[1] : wj[0], k0 = w ? wk[1] : wk[0];
                 // voxel centre in the ray frame (float64), split into integer + fraction
                 const double w0 = xv[0] - f.o[0], w1 = xv[1] - f.o[1], w2 = xv[2] - f.o[2];
                 const double a = w0 * f.ej[0] + w1 * f.ej[1] + w2 * f.ej[2];
                 const double bb = w0 * f.ek[0] + w1 * f.ek[1] + w2 * f.ek[2];
-                const double ts = (w0 * f.d[0] + w1 * f.d[1] + w2 * f.d[2]) * inv_step;
-                const double af = floor(a), bf = floor(bb), tf = floor(ts);
-                const int ai = (int)af, bi = (int)bf;
-                const float ar = (float)(a - af), br = (float)(bb - bf), tr = (float)(ts - tf);
-                const float hinv[3] = {fabsf(f.inv_df[0]), fabsf(f.inv_df[1]), fabsf(f.inv_df[2])};
-                float nhv[3] = {-hinv[0], -hinv[1], -hinv[2]};
-                asm volatile("" : "+v"(nhv[0]), "+v"(nhv[1]), "+v"(nhv[2]));
-                // the sample step in vector registers: reloading it from the frame per
-                // ray (scalar pressure) made each ray wait on the scalar load
-                float dfv[3] = {f.df[0], f.df[1], f.df[2]};
-                asm volatile("" : "+v"(dfv[0]), "+v"(dfv[1]), "+v"(dfv[2]));
-                const float ljf = (float)f.lj;
-                const int jlo = max(0, ai + (int)ceilf(ar - ljf));
-                const int jhi = min(nj - 1, ai + (int)floorf(ar + ljf));
-                const float cu[3] = {f.hull[1] + (br + 1e-4f), f.hull[3] + (br + 1e-4f), f.hull[5] + (br + 1e-4f)};
-                const float cl[3] = {f.hull[7] + (br - 1e-4f), f.hull[9] + (br - 1e-4f), f.hull[11] + (br - 1e-4f)};
-                const f4 *ys = reinterpret_cast<const f4 *>(yf + (long long)s_own * nj * nk * UP);
-                for (int j = jlo; j <= jhi; ++j) {
-                    const float dj = (float)(j - ai) - ar;
-                    const float zmax = fminf(fminf(fmaf(f.hull[0], dj, cu[0]), fmaf(f.hull[2], dj, cu[1])),
-                                             fmaf(f.hull[4], dj, cu[2]));
-                    const float zmin = fmaxf(fmaxf(fmaf(f.hull[6], dj, cl[0]), fmaf(f.hull[8], dj, cl[1])),
-                                             fmaf(f.hull[10], dj, cl[2]));
-                    const int klo = max(0, bi + (int)ceilf(zmin));
-                    const int khi = min(nk - 1, bi + (int)floorf(zmax));
-                    const float pj0 = dj * f.ejf[0], pj1 = dj * f.ejf[1], pj2 = dj * f.ejf[2];
-                    const f4 *yrow = ys + __umul24(j, nk * (UP / 4));
-                    // mirrored ray (nj-1-j, nk-1-k): row nj-1-j read backwards from column nk-1
-                    const f4 *yrowm = ys + __umul24(nj - 1 - j, nk * (UP / 4)) + (nk - 1) * (UP / 4);
-                    float dk = (float)(klo - bi) - br;
-                    for (int k = klo; k <= khi; ++k, dk += 1.0f) {
-                        f4 yv[UP / 4], ym[UP / 4];
-#pragma unroll
-                        for (int u4 = 0; u4 < UP / 4; ++u4) {
-                            yv[u4] = yrow[k * (UP / 4) + u4];
-                            ym[u4] = yrowm[u4 - k * (UP / 4)];
-                        }
-                        const float P[3] = {fmaf(dk, f.ekf[0], pj0), fmaf(dk, f.ekf[1], pj1), fmaf(dk, f.ekf[2], pj2)};
-                        float tlo = fmaf(-P[0], f.inv_df[0], nhv[0]), thi = fmaf(-P[0], f.inv_df[0], hinv[0]);
-#pragma unroll
-                        for (int m = 1; m < 3; ++m) {
-                            tlo = fmaxf(tlo, fmaf(-P[m], f.inv_df[m], nhv[m]));
-                            thi = fminf(thi, fmaf(-P[m], f.inv_df[m], hinv[m]));
-                        }
-                        float wsum = 0.0f;
-                        const float m0 = ceilf(fmaf(tlo, inv_stepf, tr)), m1 = floorf(fmaf(thi, inv_stepf, tr));
-                        const float tend = (m1 - tr + 0.5f) * stepf;
-                        for (float tau = (m0 - tr) * stepf; tau < tend; tau += stepf) {
-                            const float wx = 1.0f - fabsf(fmaf(tau, dfv[0], P[0]));
-                            const float wy = 1.0f - fabsf(fmaf(tau, dfv[1], P[1]));
-                            const float wz = 1.0f - fabsf(fmaf(tau, dfv[2], P[2]));
-                            wsum = fmaf(wx * wy, wz, wsum);
-                        }
-#pragma unroll
-                        for (int u4 = 0; u4 < UP; u4 += 4) {
-                            q[u4 + 0] = fmaf(wsum, yv[u4 / 4].x, q[u4 + 0]);
-                            q[u4 + 1] = fmaf(wsum, yv[u4 / 4].y, q[u4 + 1]);
-                            q[u4 + 2] = fmaf(wsum, yv[u4 / 4].z, q[u4 + 2]);
-                            q[u4 + 3] = fmaf(wsum, yv[u4 / 4].w, q[u4 + 3]);
-                            qm[u4 + 0] = fmaf(wsum, ym[u4 / 4].x, qm[u4 + 0]);
-                            qm[u4 + 1] = fmaf(wsum, ym[u4 / 4].y, qm[u4 + 1]);
-                            qm[u4 + 2] = fmaf(wsum, ym[u4 / 4].z, qm[u4 + 2]);
-                            qm[u4 + 3] = fmaf(wsum, ym[u4 / 4].w, qm[u4 + 3]);
-                        }
-                    }
-                }
-            }
-        }
-        float *Qown = Qs[wave];
-        float *Qout = Qx[buf][wave ^ 2];
-#pragma unroll
-        for (int u = 0; u < UP; ++u) {
-            Qown[lane * (UP + 1) + u] = q[u];
-            Qout[lane * (UP + 1) + u] = qm[u];
-        }
-        // the partner's tile is complete; the tile of the other buffer was last
-        // read before this barrier's predecessor, so one barrier per pair suffices
-        __syncthreads();
-        if (has_own) contract(ops_own, Qown);
-        if (has_oth) contract(ops_oth, Qx[buf][wave]);
-        buf ^= 1;
-    }
-
-    // epilogue: lane holds rows (coefficients) 16 mt + 4 (lane/16) + r of voxel column 16 nt + lane % 16
-    double c2 = 0.0;
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-        const int lv = nt * 16 + (lane & 15);
-        const int qy = by * 8 + (lv >> 3), qz = bz * 8 + (lv & 7);
-        if (px < nxh && qy < ny && qz < nz) {
-            const int vx = ix, vy = upper ? ny - 1 - qy : qy, vz = upper ? nz - 1 - qz : qz;
-            const long long base = (((long long)vx * ny + vy) * nz + vz) * C;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int i = mt * 16 + 4 * (lane >> 4) + r;
-                    if (i < C) {
-                        float val = acc[mt][nt][r];
-                        if (c) {
-                            float cv = c[base + i];
-                            val += beta * cv;
-                            c2 += (double)cv * (double)cv;
-                        }
-                        g[base + i] = val;
-                    }
-                }
-            }
-        }
-    }
-    if (partials) {
-        double tot = block_sum(c2, ws);
-        if (tid == 0) partials[bid] = tot;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// backproject with the residual window staged in LDS (trilinear model).  Each
-// block's 4 x 8 x 8 voxel brick reads, per projection, only the residual rays
-// of a small detector window (its shadow widened by the cube's L1 reach); the
-// window is copied from HBM into LDS by the direct global-to-LDS loads of
-// gfx950 one projection ahead (into the other of two buffers), so that the
-// per-ray residual reads of the enumeration are LDS reads instead of
-// scattered L2 / HBM loads.  One block barrier per projection (the four
-// waves process neighbouring x-slices of the same projection).
-// ---------------------------------------------------------------------------
-constexpr int kWinMax = 22;  // window rows and columns (the host checks every projection)
-
-template <int UP, int MT, bool BF16>
-__global__ __launch_bounds__(256) void k_backproject_win(const float *__restrict__ yf,
-                                                         const ProjFrame *__restrict__ frames,
-                                                         const float *__restrict__ Bu, const s4 *__restrict__ BuT16,
-                                                         int S, int nx, int ny, int nz, int nj, int nk, int C, int Cp,
-                                                         float step, float *__restrict__ g, float beta,
-                                                         const float *__restrict__ c, double *__restrict__ partials)
-{
-    constexpr int Q = UP / 4;                 // float4 per ray
-    constexpr int WROW = kWinMax * Q;         // float4 per window row
-    __shared__ f4 winA[kWinMax * WROW];
-    __shared__ f4 winB[kWinMax * WROW];
-    __shared__ float Qs[4][64 * (UP + 1)];
-    __shared__ double ws[4];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nbx = (nx + 3) / 4, nby = (ny + 7) / 8;
-    const int bid = xcd_block(blockIdx.x, gridDim.x);
-    const int bx = bid % nbx, by = (bid / nbx) % nby, bz = bid / (nbx * nby);
-    const int ix = bx * 4 + wave, iy = by * 8 + (lane >> 3), iz = bz * 8 + (lane & 7);
-    const bool valid = ix < nx && iy < ny && iz < nz;
-    const double xv[3] = {ix - 0.5 * (nx - 1), iy - 0.5 * (ny - 1), iz - 0.5 * (nz - 1)};
-    const double inv_step = 1.0 / (double)step;
-    const float stepf = step, inv_stepf = (float)inv_step;
-
-    // detector window of projection s: rows and columns every voxel of the
-    // brick can reach (its L1 reach lj, lk around its detector position, one
-    // more on each side for rounding), clipped to the detector
-    auto window = [&](int s, int &j0, int &k0, int &nr, int &nc) {
-        const ProjFrame &f = frames[s];
-        // the brick's voxel-centre box (clipped to the volume), centred coordinates
-        const double lo3[3] = {bx * 4 - 0.5 * (nx - 1), by * 8 - 0.5 * (ny - 1), bz * 8 - 0.5 * (nz - 1)};
-        const double hi3[3] = {min(nx, bx * 4 + 4) - 1 - 0.5 * (nx - 1), min(ny, by * 8 + 8) - 1 - 0.5 * (ny - 1),
-                               min(nz, bz * 8 + 8) - 1 - 0.5 * (nz - 1)};
-        double amin = 0.0, amax = 0.0, bmin = 0.0, bmax = 0.0;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const double ea = f.ej[a], ka = f.ek[a];
-            amin += (ea >= 0.0 ? lo3[a] - f.o[a] : hi3[a] - f.o[a]) * ea;
-            amax += (ea >= 0.0 ? hi3[a] - f.o[a] : lo3[a] - f.o[a]) * ea;
-            bmin += (ka >= 0.0 ? lo3[a] - f.o[a] : hi3[a] - f.o[a]) * ka;
-            bmax += (ka >= 0.0 ? hi3[a] - f.o[a] : lo3[a] - f.o[a]) * ka;
-        }
-        const int ja = max(0, (int)ceil(amin - f.lj) - 1), jb = min(nj - 1, (int)floor(amax + f.lj) + 1);
-        const int ka0 = max(0, (int)ceil(bmin - f.lk) - 1), kb = min(nk - 1, (int)floor(bmax + f.lk) + 1);
-        j0 = __builtin_amdgcn_readfirstlane(ja);
-        k0 = __builtin_amdgcn_readfirstlane(ka0);
-        nr = __builtin_amdgcn_readfirstlane(max(0, min(kWinMax, jb - ja + 1)));
-        nc = __builtin_amdgcn_readfirstlane(max(0, min(kWinMax, kb - ka0 + 1)));
-    };
-    // asynchronous copy of projection s's window into win (rows spread over the waves)
-    auto stage = [&](int s, f4 *win, int j0, int k0, int nr, int nc) {
-        const f4 *src = reinterpret_cast<const f4 *>(yf) + (((long long)s * nj + j0) * nk + k0) * Q;
-        const int rowf4 = nc * Q;
-        for (int r = wave; r < nr; r += 4) {
-#pragma unroll
-            for (int l0 = 0; l0 < WROW; l0 += 64) {
-                if (l0 + lane < rowf4)
-                    __builtin_amdgcn_global_load_lds(
-                        (const __attribute__((address_space(1))) void *)(src + (long long)r * nk * Q + l0 + lane),
-                        (__attribute__((address_space(3))) void *)(win + r * WROW + l0), 16, 0, 0);
-            }
-        }
-    };
-
-    f4 acc[MT][4];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = f4{0.f, 0.f, 0.f, 0.f};
-    float *Qw = Qs[wave];
-
-    // projection s: enumerate from the staged window, then contract on MFMA
-    auto body = [&](int s, const f4 *win, int wj0, int wk0, int wnr, int wnc) {
-        const ProjFrame &f = frames[s];
-        s4 avb[MT];
-        float avf[UP / 4][MT];
-        if constexpr (BF16) {
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                avb[mt] = BuT16[((long long)s * Cp + mt * 16 + (lane & 15)) * 4 + (lane >> 4)];
-        } else {
-            const float *Bs = Bu + (long long)s * UP * Cp;
-#pragma unroll
-            for (int ks = 0; ks < UP / 4; ++ks)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) avf[ks][mt] = Bs[(ks * 4 + (lane >> 4)) * Cp + mt * 16 + (lane & 15)];
-        }
-        float q[UP];
-#pragma unroll
-        for (int u = 0; u < UP; ++u) q[u] = 0.0f;
-        if (valid) {
-            const double w0 = xv[0] - f.o[0], w1 = xv[1] - f.o[1], w2 = xv[2] - f.o[2];
-            const double a = w0 * f.ej[0] + w1 * f.ej[1] + w2 * f.ej[2];
-            const double bb = w0 * f.ek[0] + w1 * f.ek[1] + w2 * f.ek[2];
-            const double ts = (w0 * f.d[0] + w1 * f.d[1] + w2 * f.d[2]) * inv_step;
-            const double af = floor(a), bf = floor(bb), tf = floor(ts);
-            const int ai = (int)af, bi = (int)bf;
-            const float ar = (float)(a - af), br = (float)(bb - bf), tr = (float)(ts - tf);
-            const float hinv[3] = {fabsf(f.inv_df[0]), fabsf(f.inv_df[1]), fabsf(f.inv_df[2])};
-            float nhv[3] = {-hinv[0], -hinv[1], -hinv[2]};
-            asm volatile("" : "+v"(nhv[0]), "+v"(nhv[1]), "+v"(nhv[2]));
-            // the sample step in vector registers: reloading it from the frame per
-            // ray (scalar pressure) made each ray wait on the scalar load
-            float dfv[3] = {f.df[0], f.df[1], f.df[2]};
-            asm volatile("" : "+v"(dfv[0]), "+v"(dfv[1]), "+v"(dfv[2]));
-            const float ljf = (float)f.lj;
-            // rows and columns stay inside the staged window (it contains every ray
-            // the voxel can reach; the clamps only guard the LDS indices)
-            const int jlo = max(wj0, ai + (int)ceilf(ar - ljf));
-            const int jhi = min(wj0 + wnr - 1, ai + (int)floorf(ar + ljf));
-            const float cu[3] = {f.hull[1] + (br + 1e-4f), f.hull[3] + (br + 1e-4f), f.hull[5] + (br + 1e-4f)};
-            const float cl[3] = {f.hull[7] + (br - 1e-4f), f.hull[9] + (br - 1e-4f), f.hull[11] + (br - 1e-4f)};
-            for (int j = jlo; j <= jhi; ++j) {
-                const float dj = (float)(j - ai) - ar;
-                const float zmax = fminf(fminf(fmaf(f.hull[0], dj, cu[0]), fmaf(f.hull[2], dj, cu[1])),
-                                         fmaf(f.hull[4], dj, cu[2]));
-                const float zmin = fmaxf(fmaxf(fmaf(f.hull[6], dj, cl[0]), fmaf(f.hull[8], dj, cl[1])),
-                                         fmaf(f.hull[10], dj, cl[2]));
-                const int klo = max(wk0, bi + (int)ceilf(zmin));
-                const int khi = min(wk0 + wnc - 1, bi + (int)floorf(zmax));
-                const float pj0 = dj * f.ejf[0], pj1 = dj * f.ejf[1], pj2 = dj * f.ejf[2];
-                const f4 *wrow = win + (j - wj0) * WROW - wk0 * Q;
-                float dk = (float)(klo - bi) - br;
-                for (int k = klo; k <= khi; ++k, dk += 1.0f) {
-                    f4 yv[Q];
-#pragma unroll
-                    for (int u4 = 0; u4 < Q; ++u4) yv[u4] = wrow[k * Q + u4];
-                    const float P[3] = {fmaf(dk, f.ekf[0], pj0), fmaf(dk, f.ekf[1], pj1), fmaf(dk, f.ekf[2], pj2)};
-                    float tlo = fmaf(-P[0], f.inv_df[0], nhv[0]), thi = fmaf(-P[0], f.inv_df[0], hinv[0]);
-#pragma unroll
-                    for (int m = 1; m < 3; ++m) {
-                        tlo = fmaxf(tlo, fmaf(-P[m], f.inv_df[m], nhv[m]));
-                        thi = fminf(thi, fmaf(-P[m], f.inv_df[m], hinv[m]));
-                    }
-                    float wsum = 0.0f;
-                    const float m0 = ceilf(fmaf(tlo, inv_stepf, tr)), m1 = floorf(fmaf(thi, inv_stepf, tr));
-                    const float tend = (m1 - tr + 0.5f) * stepf;
-                    for (float tau = (m0 - tr) * stepf; tau < tend; tau += stepf) {
-                        const float wx = 1.0f - fabsf(fmaf(tau, dfv[0], P[0]));
-                        const float wy = 1.0f - fabsf(fmaf(tau, dfv[1], P[1]));
-                        const float wz = 1.0f - fabsf(fmaf(tau, dfv[2], P[2]));
-                        wsum = fmaf(wx * wy, wz, wsum);
-                    }
-#pragma unroll
-                    for (int u4 = 0; u4 < UP; u4 += 4) {
-                        q[u4 + 0] = fmaf(wsum, yv[u4 / 4].x, q[u4 + 0]);
-                        q[u4 + 1] = fmaf(wsum, yv[u4 / 4].y, q[u4 + 1]);
-                        q[u4 + 2] = fmaf(wsum, yv[u4 / 4].z, q[u4 + 2]);
-                        q[u4 + 3] = fmaf(wsum, yv[u4 / 4].w, q[u4 + 3]);
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < UP; ++u) Qw[lane * (UP + 1) + u] = q[u];
-        __builtin_amdgcn_wave_barrier();
-        if constexpr (BF16) {
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const float *qv = Qw + (nt * 16 + (lane & 15)) * (UP + 1);
-                const int u0 = 4 * (lane >> 4);
-                s4 bv;
-                bv.x = u0 + 0 < UP ? f2bf(qv[min(u0 + 0, UP - 1)]) : (short)0;
-                bv.y = u0 + 1 < UP ? f2bf(qv[min(u0 + 1, UP - 1)]) : (short)0;
-                bv.z = u0 + 2 < UP ? f2bf(qv[min(u0 + 2, UP - 1)]) : (short)0;
-                bv.w = u0 + 3 < UP ? f2bf(qv[min(u0 + 3, UP - 1)]) : (short)0;
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = mfma16x16x16bf16(avb[mt], bv, acc[mt][nt]);
-            }
-        } else {
-#pragma unroll
-            for (int ks = 0; ks < UP / 4; ++ks) {
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt) {
-                    const float bv = qw_at<UP>(Qw, nt, ks, lane);
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = mfma16x16x4(avf[ks][mt], bv, acc[mt][nt]);
-                }
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-    };
-
-    // two buffers: projection s reads one while the copy of projection s + 1
-    // fills the other
-    int cj0, ck0, cnr, cnc;
-    window(0, cj0, ck0, cnr, cnc);
-    stage(0, winA, cj0, ck0, cnr, cnc);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    for (int s = 0; s < S; ++s) {
-        f4 *cur = (s & 1) ? winB : winA;
-        f4 *nxt = (s & 1) ? winA : winB;
-        int nj0 = 0, nk0 = 0, nnr = 0, nnc = 0;
-        if (s + 1 < S) {
-            window(s + 1, nj0, nk0, nnr, nnc);
-            stage(s + 1, nxt, nj0, nk0, nnr, nnc);
-        }
-        body(s, cur, cj0, ck0, cnr, cnc);
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        cj0 = nj0; ck0 = nk0; cnr = nnr; cnc = nnc;
-    }
-
-    // epilogue: lane holds rows (coefficients) 16 mt + 4 (lane/16) + r of voxel column 16 nt + lane % 16
-    double c2 = 0.0;
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-        const int lv = nt * 16 + (lane & 15);
-        const int vy = by * 8 + (lv >> 3), vz = bz * 8 + (lv & 7);
-        if (ix < nx && vy < ny && vz < nz) {
-            const long long base = (((long long)ix * ny + vy) * nz + vz) * C;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int i = mt * 16 + 4 * (lane >> 4) + r;
-                    if (i < C) {
-                        float val = acc[mt][nt][r];
-                        if (c) {
-                            float cv = c[base + i];
-                            val += beta * cv;
-                            c2 += (double)cv * (double)cv;
-                        }
-                        g[base + i] = val;
-                    }
-                }
-            }
-        }
-    }
-    if (partials) {
-        double tot = block_sum(c2, ws);
-        if (tid == 0) partials[bid] = tot;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// backproject, paired by point inversion and with LDS-staged residual windows
-// (trilinear model, centred detector, even nx, eight unique segments).  Block
-// as in k_backproject_inv: waves 0, 1 own two lower-half x-slices, waves 2, 3
-// their inverses; per pair of projections (s0, s0 + 1) the lower group
-// enumerates s0 and the upper group s0 + 1.  Each group stages, for its
-// projection, the residual window of its own 2 x 8 x 8 voxels and the
-// point-reflected window (row nj-1-j, column nk-1-k at the position of
-// (j, k)), so a ray's own and mirrored reads use the same offset in two LDS
-// buffers.  The copies for the next pair are issued before this pair's
-// MFMAs.  Two block barriers per pair: windows staged, Q handed over.
-// ---------------------------------------------------------------------------
-template <int UP, int MT, bool BF16, bool JOS>
-__global__ __launch_bounds__(256) void k_backproject_pw(const float *__restrict__ yf,
-                                                        const ProjFrame *__restrict__ frames,
-                                                        const float *__restrict__ Bu, const s4 *__restrict__ BuT16,
-                                                        int S, int nx, int ny, int nz, int nj, int nk, int C, int Cp,
-                                                        float step, float *__restrict__ g, float beta,
-                                                        const float *__restrict__ c, double *__restrict__ partials,
-                                                        int WR, int WC)
-{
-    constexpr int Q = UP / 4;
-    constexpr int QS = 64 * (UP + 1);
-    extern __shared__ f4 wins[];     // [group][own, reflected][WR][WC][Q]
-    __shared__ float Qs[4][QS];      // each wave's own Q
-    __shared__ float Qx[4][QS];      // Q handed over by the partner wave
-    __shared__ double ws[4];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool upper = wave >= 2;
-    const int grp = upper ? 1 : 0;
-    const int nxh = nx >> 1;
-    const int nbx = (nxh + 1) / 2, nby = (ny + 7) / 8;
-    const int bid = xcd_block(blockIdx.x, gridDim.x);
-    const int bx = bid % nbx, by = (bid / nbx) % nby, bz = bid / (nbx * nby);
-    const int px = bx * 2 + (wave & 1), py = by * 8 + (lane >> 3), pz = bz * 8 + (lane & 7);
-    const bool valid = px < nxh && py < ny && pz < nz;
-    const int ix = upper ? nx - 1 - px : px, iy = upper ? ny - 1 - py : py, iz = upper ? nz - 1 - pz : pz;
-    const double xv[3] = {ix - 0.5 * (nx - 1), iy - 0.5 * (ny - 1), iz - 0.5 * (nz - 1)};
-    const double inv_step = 1.0 / (double)step;
-    const float stepf = step, inv_stepf = (float)inv_step;
-    const int WROW = WC * Q, WSZ = WR * WROW;
-    f4 *win_own = wins + (2 * grp) * WSZ, *win_ref = wins + (2 * grp + 1) * WSZ;
-
-    // window of this group's voxel box for projection s (its L1 reach lj, lk
-    // around the detector positions, one more on each side for rounding)
-    auto window = [&](int s, int &j0, int &k0, int &nr, int &nc) {
-        const ProjFrame &f = frames[s];
-        const double lo0[3] = {bx * 2 - 0.5 * (nx - 1), by * 8 - 0.5 * (ny - 1), bz * 8 - 0.5 * (nz - 1)};
-        const double hi0[3] = {min(nxh, bx * 2 + 2) - 1 - 0.5 * (nx - 1), min(ny, by * 8 + 8) - 1 - 0.5 * (ny - 1),
-                               min(nz, bz * 8 + 8) - 1 - 0.5 * (nz - 1)};
-        double amin = 0.0, amax = 0.0, bmin = 0.0, bmax = 0.0;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            // the upper group's box is the point inverse of the lower group's
-            const double lo = upper ? -hi0[a] : lo0[a], hi = upper ? -lo0[a] : hi0[a];
-            const double ea = f.ej[a], ka = f.ek[a];
-            amin += (ea >= 0.0 ? lo - f.o[a] : hi - f.o[a]) * ea;
-            amax += (ea >= 0.0 ? hi - f.o[a] : lo - f.o[a]) * ea;
-            bmin += (ka >= 0.0 ? lo - f.o[a] : hi - f.o[a]) * ka;
-            bmax += (ka >= 0.0 ? hi - f.o[a] : lo - f.o[a]) * ka;
-        }
-        const double rj = JOS ? (double)f.jos_rj : f.lj, rk = JOS ? (double)f.jos_rk : f.lk;
-        const int ja = max(0, (int)ceil(amin - rj) - 1), jb = min(nj - 1, (int)floor(amax + rj) + 1);
-        const int ka0 = max(0, (int)ceil(bmin - rk) - 1), kb = min(nk - 1, (int)floor(bmax + rk) + 1);
-        j0 = __builtin_amdgcn_readfirstlane(ja);
-        k0 = __builtin_amdgcn_readfirstlane(ka0);
-        nr = __builtin_amdgcn_readfirstlane(max(0, min(WR, jb - ja + 1)));
-        nc = __builtin_amdgcn_readfirstlane(max(0, min(WC, kb - ka0 + 1)));
-    };
-    // asynchronous copies of the window and of its point reflection (rows spread
-    // over the group's two waves)
-    auto stage = [&](int s, int j0, int k0, int nr, int nc) {
-        const f4 *ys = reinterpret_cast<const f4 *>(yf) + (long long)s * nj * nk * Q;
-        const int rowf4 = nc * Q;
-        for (int r = wave & 1; r < nr; r += 2) {
-            for (int l0 = 0; l0 < rowf4; l0 += 64) {
-                const int l = l0 + lane;
-                if (l < rowf4) {
-                    const int cc = l / Q, q = l - cc * Q;
-                    const f4 *so = ys + ((long long)(j0 + r) * nk + k0) * Q + l;
-                    const f4 *sr = ys + ((long long)(nj - 1 - j0 - r) * nk + (nk - 1 - k0 - cc)) * Q + q;
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)so,
-                                                     (__attribute__((address_space(3))) void *)(win_own + r * WROW + l0),
-                                                     16, 0, 0);
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)sr,
-                                                     (__attribute__((address_space(3))) void *)(win_ref + r * WROW + l0),
-                                                     16, 0, 0);
-                }
-            }
-        }
-    };
-
-    f4 acc[MT][4];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = f4{0.f, 0.f, 0.f, 0.f};
-
-    struct BOps {
-        s4 b16[BF16 ? MT : 1];
-        float f[BF16 ? 1 : UP / 4][MT];
-    };
-    auto load_ops = [&](int s, BOps &o) {
-        if constexpr (BF16) {
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                o.b16[mt] = BuT16[((long long)s * Cp + mt * 16 + (lane & 15)) * 4 + (lane >> 4)];
-        } else {
-            const float *Bs = Bu + (long long)s * UP * Cp;
-#pragma unroll
-            for (int ks = 0; ks < UP / 4; ++ks)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) o.f[ks][mt] = Bs[(ks * 4 + (lane >> 4)) * Cp + mt * 16 + (lane & 15)];
-        }
-    };
-    auto contract = [&](const BOps &o, const float *Qt) {
-        if constexpr (BF16) {
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const float *qv = Qt + (nt * 16 + (lane & 15)) * (UP + 1);
-                const int u0 = 4 * (lane >> 4);
-                s4 bv;
-                bv.x = u0 + 0 < UP ? f2bf(qv[min(u0 + 0, UP - 1)]) : (short)0;
-                bv.y = u0 + 1 < UP ? f2bf(qv[min(u0 + 1, UP - 1)]) : (short)0;
-                bv.z = u0 + 2 < UP ? f2bf(qv[min(u0 + 2, UP - 1)]) : (short)0;
-                bv.w = u0 + 3 < UP ? f2bf(qv[min(u0 + 3, UP - 1)]) : (short)0;
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = mfma16x16x16bf16(o.b16[mt], bv, acc[mt][nt]);
-            }
-        } else {
-#pragma unroll
-            for (int ks = 0; ks < UP / 4; ++ks) {
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt) {
-                    const float bv = qw_at<UP>(Qt, nt, ks, lane);
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = mfma16x16x4(o.f[ks][mt], bv, acc[mt][nt]);
-                }
-            }
-        }
-    };
-
-    int wj0 = 0, wk0 = 0, wnr = 0, wnc = 0;  // this group's window of the current pair
-    if (grp < S) {
-        window(grp, wj0, wk0, wnr, wnc);
-        stage(grp, wj0, wk0, wnr, wnc);
-    }
-    for (int s0 = 0; s0 < S; s0 += 2) {
-        const int s_own = s0 + grp, s_oth = s0 + 1 - grp;
-        const bool has_own = s_own < S, has_oth = s_oth < S;
-        BOps ops_own, ops_oth;
-        load_ops(has_own ? s_own : s0, ops_own);
-        load_ops(has_oth ? s_oth : s0, ops_oth);
-        float q[UP], qm[UP];
-#pragma unroll
-        for (int u = 0; u < UP; ++u) q[u] = qm[u] = 0.0f;
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();  // this pair's windows are staged
-        if (has_own && valid) {
-            const ProjFrame &f = frames[s_own];
-            if constexpr (JOS) {
-                // Joseph's method: the rays whose cut with the voxel's layer lies
-                // within one voxel in-plane, weight (1 - |Delta_B|)(1 - |Delta_C|) /
-                // |d_A|.  The inverse voxel's cut of the reflected ray is the negated
-                // cut point, so the same weight serves both voxels of the pair.
-                const double w0 = xv[0] - f.o[0], w1 = xv[1] - f.o[1], w2 = xv[2] - f.o[2];
-                const double a = w0 * f.ej[0] + w1 * f.ej[1] + w2 * f.ej[2];
-                const double bb = w0 * f.ek[0] + w1 * f.ek[1] + w2 * f.ek[2];
                 const double af = floor(a), bf = floor(bb);
                 const int ai = (int)af, bi = (int)bf;
                 const float ar = (float)(a - af), br = (float)(bb - bf);
-                const float gjB = f.jos_gj[0], gjC = f.jos_gj[1], gkB = f.jos_gk[0], gkC = f.jos_gk[1];
-                const int jlo = max(wj0, ai + (int)ceilf(ar - f.jos_rj));
-                const int jhi = min(wj0 + wnr - 1, ai + (int)floorf(ar + f.jos_rj));
-                for (int j = jlo; j <= jhi; ++j) {
-                    const float dj = (float)(j - ai) - ar;
-                    const float eB = dj * gjB, eC = dj * gjC;
-                    // dk range with |dk gk + e| < 1 on both in-plane axes (a flat
-                    // axis gives all dk or none; the other one is never flat)
-                    const float xB1 = (-1.0f - eB) * f.jos_igk[0], xB2 = (1.0f - eB) * f.jos_igk[0];
-                    const float xC1 = (-1.0f - eC) * f.jos_igk[1], xC2 = (1.0f - eC) * f.jos_igk[1];
-                    const float lo = fmaxf(fminf(xB1, xB2), fminf(xC1, xC2));
-                    const float hi = fminf(fmaxf(xB1, xB2), fmaxf(xC1, xC2));
-                    if (!(lo < hi)) continue;
-                    const int klo = max(wk0, bi + (int)ceilf(br + lo - 1e-4f));
-                    const int khi = min(wk0 + wnc - 1, bi + (int)floorf(br + hi + 1e-4f));
-                    const int rowoff = (j - wj0) * WROW - wk0 * Q;
-                    const f4 *wo = win_own + rowoff, *wr = win_ref + rowoff;
-                    for (int k = klo; k <= khi; ++k) {
-                        f4 yv[Q], ym[Q];
+                const float rj = JOS ? f.jos_rj : (float)f.lj;
+                const int jlo = max(j0 - ai, (int)ceilf(ar - rj)), jhi = min(j0 + WR - 1 - ai, (int)floorf(ar + rj));
+                const float kmin = (float)(k0 - bi), kmax = (float)(k0 + WC - 1 - bi);
+                const f4 *row = wins + w * wsz + ((jlo + ai - j0) * WC + (bi - k0)) * RW;
+                const float fjhi = (float)jhi;
+                // a ray's residual (and the mirrored ray's), read before its weight is
+                // worked out, then added with that weight
+                f4 y[RW];
+                auto load_ray = [&](const f4 *p) {
 #pragma unroll
-                        for (int u4 = 0; u4 < Q; ++u4) {
-                            yv[u4] = wo[k * Q + u4];
-                            ym[u4] = wr[k * Q + u4];
-                        }
-                        const float dk = (float)(k - bi) - br;
-                        const float wB = fmaxf(0.0f, 1.0f - fabsf(fmaf(dk, gkB, eB)));
-                        const float wC = fmaxf(0.0f, 1.0f - fabsf(fmaf(dk, gkC, eC)));
-                        const float wt = wB * wC * f.jos_w;
+                    for (int i = 0; i < RW; ++i) y[i] = p[i];
+                };
+                auto add_ray = [&](float wt) {
 #pragma unroll
-                        for (int u4 = 0; u4 < UP; u4 += 4) {
-                            q[u4 + 0] = fmaf(wt, yv[u4 / 4].x, q[u4 + 0]);
-                            q[u4 + 1] = fmaf(wt, yv[u4 / 4].y, q[u4 + 1]);
-                            q[u4 + 2] = fmaf(wt, yv[u4 / 4].z, q[u4 + 2]);
-                            q[u4 + 3] = fmaf(wt, yv[u4 / 4].w, q[u4 + 3]);
-                            qm[u4 + 0] = fmaf(wt, ym[u4 / 4].x, qm[u4 + 0]);
-                            qm[u4 + 1] = fmaf(wt, ym[u4 / 4].y, qm[u4 + 1]);
-                            qm[u4 + 2] = fmaf(wt, ym[u4 / 4].z, qm[u4 + 2]);
-                            qm[u4 + 3] = fmaf(wt, ym[u4 / 4].w, qm[u4 + 3]);
+                    for (int i = 0; i < RW; ++i) {
+                        float *t = i < Q ? q + 4 * i : qm + 4 * (i - Q);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) t[e] = fmaf(wt, y[i][e], t[e]);
+                    }
+                };
+                if constexpr (JOS) {
+                    // Joseph's method: the rays whose cut with the voxel's layer lies
+                    // within one voxel in-plane, weight (1 - |Delta_B|)(1 - |Delta_C|) /
+                    // |d_A|; the inverse voxel's cut of the mirrored ray is the negated
+                    // cut point, so the same weight serves both voxels of a pair
+                    for (float fj = (float)jlo; fj <= fjhi; fj += 1.0f, row += WC * RW) {
+                        const float dj = fj - ar;
+                        const float eB = dj * f.jos_gj[0], eC = dj * f.jos_gj[1];
+                        // dk range with |dk gk + e| < 1 on both in-plane axes (a flat
+                        // axis gives all dk or none; the other one is never flat)
+                        const float xB1 = (-1.0f - eB) * f.jos_igk[0], xB2 = (1.0f - eB) * f.jos_igk[0];
+                        const float xC1 = (-1.0f - eC) * f.jos_igk[1], xC2 = (1.0f - eC) * f.jos_igk[1];
+                        const float lo = fmaxf(fminf(xB1, xB2), fminf(xC1, xC2));
+                        const float hi = fminf(fmaxf(xB1, xB2), fmaxf(xC1, xC2));
+                        if (!(lo < hi)) continue;
+                        const float kf = fmaxf(kmin, ceilf(br + lo - 1e-4f));
+                        const float ke = fminf(kmax, floorf(br + hi + 1e-4f));
+                        const f4 *ray = row + (int)kf * RW;
+                        for (float fk = kf; fk <= ke; fk += 1.0f, ray += RW) {
+                            load_ray(ray);
+                            const float dk = fk - br;
+                            const float wB = tent1(fmaf(dk, f.jos_gk[0], eB));
+                            const float wC = tent1(fmaf(dk, f.jos_gk[1], eC));
+                            add_ray(wB * wC * f.jos_w);
                         }
                     }
-                }
-            } else {
-                const double w0 = xv[0] - f.o[0], w1 = xv[1] - f.o[1], w2 = xv[2] - f.o[2];
-                const double a = w0 * f.ej[0] + w1 * f.ej[1] + w2 * f.ej[2];
-                const double bb = w0 * f.ek[0] + w1 * f.ek[1] + w2 * f.ek[2];
-                const double ts = (w0 * f.d[0] + w1 * f.d[1] + w2 * f.d[2]) * inv_step;
-                const double af = floor(a), bf = floor(bb), tf = floor(ts);
-                const int ai = (int)af, bi = (int)bf;
-                const float ar = (float)(a - af), br = (float)(bb - bf), tr = (float)(ts - tf);
-                const float hinv[3] = {fabsf(f.inv_df[0]), fabsf(f.inv_df[1]), fabsf(f.inv_df[2])};
-                float nhv[3] = {-hinv[0], -hinv[1], -hinv[2]};
-                asm volatile("" : "+v"(nhv[0]), "+v"(nhv[1]), "+v"(nhv[2]));
-                float dfv[3] = {f.df[0], f.df[1], f.df[2]};
-                asm volatile("" : "+v"(dfv[0]), "+v"(dfv[1]), "+v"(dfv[2]));
-                const float ljf = (float)f.lj;
-                const int jlo = max(wj0, ai + (int)ceilf(ar - ljf));
-                const int jhi = min(wj0 + wnr - 1, ai + (int)floorf(ar + ljf));
-                const float cu[3] = {f.hull[1] + (br + 1e-4f), f.hull[3] + (br + 1e-4f), f.hull[5] + (br + 1e-4f)};
-                const float cl[3] = {f.hull[7] + (br - 1e-4f), f.hull[9] + (br - 1e-4f), f.hull[11] + (br - 1e-4f)};
-                for (int j = jlo; j <= jhi; ++j) {
-                    const float dj = (float)(j - ai) - ar;
-                    const float zmax = fminf(fminf(fmaf(f.hull[0], dj, cu[0]), fmaf(f.hull[2], dj, cu[1])),
-                                             fmaf(f.hull[4], dj, cu[2]));
-                    const float zmin = fmaxf(fmaxf(fmaf(f.hull[6], dj, cl[0]), fmaf(f.hull[8], dj, cl[1])),
-                                             fmaf(f.hull[10], dj, cl[2]));
-                    const int klo = max(wk0, bi + (int)ceilf(zmin));
-                    const int khi = min(wk0 + wnc - 1, bi + (int)floorf(zmax));
-                    const float pj0 = dj * f.ejf[0], pj1 = dj * f.ejf[1], pj2 = dj * f.ejf[2];
-                    const int rowoff = (j - wj0) * WROW - wk0 * Q;
-                    const f4 *wo = win_own + rowoff, *wr = win_ref + rowoff;
-                    float dk = (float)(klo - bi) - br;
-                    for (int k = klo; k <= khi; ++k, dk += 1.0f) {
-                        f4 yv[Q], ym[Q];
-#pragma unroll
-                        for (int u4 = 0; u4 < Q; ++u4) {
-                            yv[u4] = wo[k * Q + u4];
-                            ym[u4] = wr[k * Q + u4];
-                        }
-                        const float P[3] = {fmaf(dk, f.ekf[0], pj0), fmaf(dk, f.ekf[1], pj1), fmaf(dk, f.ekf[2], pj2)};
-                        float tlo = fmaf(-P[0], f.inv_df[0], nhv[0]), thi = fmaf(-P[0], f.inv_df[0], hinv[0]);
-#pragma unroll
-                        for (int m = 1; m < 3; ++m) {
-                            tlo = fmaxf(tlo, fmaf(-P[m], f.inv_df[m], nhv[m]));
-                            thi = fminf(thi, fmaf(-P[m], f.inv_df[m], hinv[m]));
-                        }
-                        float wsum = 0.0f;
-                        const float m0 = ceilf(fmaf(tlo, inv_stepf, tr)), m1 = floorf(fmaf(thi, inv_stepf, tr));
-                        const float tend = (m1 - tr + 0.5f) * stepf;
-                        for (float tau = (m0 - tr) * stepf; tau < tend; tau += stepf) {
-                            const float wx = 1.0f - fabsf(fmaf(tau, dfv[0], P[0]));
-                            const float wy = 1.0f - fabsf(fmaf(tau, dfv[1], P[1]));
-                            const float wz = 1.0f - fabsf(fmaf(tau, dfv[2], P[2]));
-                            wsum = fmaf(wx * wy, wz, wsum);
-                        }
-#pragma unroll
-                        for (int u4 = 0; u4 < UP; u4 += 4) {
-                            q[u4 + 0] = fmaf(wsum, yv[u4 / 4].x, q[u4 + 0]);
-                            q[u4 + 1] = fmaf(wsum, yv[u4 / 4].y, q[u4 + 1]);
-                            q[u4 + 2] = fmaf(wsum, yv[u4 / 4].z, q[u4 + 2]);
-                            q[u4 + 3] = fmaf(wsum, yv[u4 / 4].w, q[u4 + 3]);
-                            qm[u4 + 0] = fmaf(wsum, ym[u4 / 4].x, qm[u4 + 0]);
-                            qm[u4 + 1] = fmaf(wsum, ym[u4 / 4].y, qm[u4 + 1]);
-                            qm[u4 + 2] = fmaf(wsum, ym[u4 / 4].z, qm[u4 + 2]);
-                            qm[u4 + 3] = fmaf(wsum, ym[u4 / 4].w, qm[u4 + 3]);
+                } else {
+                    const double ts = (w0 * f.d[0] + w1 * f.d[1] + w2 * f.d[2]) * inv_step;
+                    const TentRay tent = tent_ray(f, (float)(ts - floor(ts)), step, (float)inv_step);
+                    // hull intercepts shifted by this voxel's fraction br and the 1e-4 slack
+                    const float cu[3] = {f.hull[1] + (br + 1e-4f), f.hull[3] + (br + 1e-4f), f.hull[5] + (br + 1e-4f)};
+                    const float cl[3] = {f.hull[7] + (br - 1e-4f), f.hull[9] + (br - 1e-4f), f.hull[11] + (br - 1e-4f)};
+                    for (float fj = (float)jlo; fj <= fjhi; fj += 1.0f, row += WC * RW) {
+                        // rays of this row that can meet the open cube around the voxel
+                        const float dj = fj - ar;
+                        const float zmax = fminf(fminf(fmaf(f.hull[0], dj, cu[0]), fmaf(f.hull[2], dj, cu[1])),
+                                                 fmaf(f.hull[4], dj, cu[2]));
+                        const float zmin = fmaxf(fmaxf(fmaf(f.hull[6], dj, cl[0]), fmaf(f.hull[8], dj, cl[1])),
+                                                 fmaf(f.hull[10], dj, cl[2]));
+                        const float kf = fmaxf(kmin, ceilf(zmin)), ke = fminf(kmax, floorf(zmax));
+                        const float pj0 = dj * f.ejf[0], pj1 = dj * f.ejf[1], pj2 = dj * f.ejf[2];
+                        const f4 *ray = row + (int)kf * RW;
+                        for (float fk = kf; fk <= ke; fk += 1.0f, ray += RW) {
+                            load_ray(ray);
+                            const float dk = fk - br;
+                            const float P[3] = {fmaf(dk, f.ekf[0], pj0), fmaf(dk, f.ekf[1], pj1),
+                                                fmaf(dk, f.ekf[2], pj2)};
+                            add_ray(ray_weight(P, tent));
                         }
                     }
                 }
             }
+            // own Q to this wave's tile, the inverse's to the partner's
+            const int slot = PB == 2 ? (s0 & 2) + w : w;
+            put_q<UP, BF16>(q, &Qt[wave][0][slot][lane], QS);
+            if constexpr (PAIR) put_q<UP, BF16>(qm, &Qt[wave ^ 2][0][slot][lane], QS);
         }
-        float *Qown = Qs[wave];
-        float *Qout = Qx[wave ^ 2];
+        const bool last = s0 + 2 >= s_end, contract = PB == 1 || (s0 & 2) || last;
+        if (PB == 2 && last && !(s0 & 2)) {  // a lone last pair: nothing in the other two slots
 #pragma unroll
-        for (int u = 0; u < UP; ++u) {
-            Qown[lane * (UP + 1) + u] = q[u];
-            Qout[lane * (UP + 1) + u] = qm[u];
+            for (int t = 0; t < QT; ++t) Qt[wave][t][2][lane] = Qt[wave][t][3][lane] = make_uint4(0, 0, 0, 0);
         }
-        __syncthreads();  // the partner's Q is complete; the windows are free
-        // copies for the next pair run during this pair's MFMAs
-        const int s_next = s0 + 2 + grp;
-        if (s_next < S) {
-            window(s_next, wj0, wk0, wnr, wnc);
-            stage(s_next, wj0, wk0, wnr, wnc);
+        // B^T operands (tables in operand order; a projection past the last one has
+        // Q = 0).  Lane group kq serves projection kq / 2 of the pair and product set
+        // kq % 2, or, with two pairs per contraction, projection kq of the four.
+        const int kq = lane >> 4, sel = PB == 2 ? 0 : kq & 1, sl = PB == 2 ? kq : kq >> 1, n = lane & 15;
+        constexpr int NA = BF16 ? 1 : (PB == 2 ? 3 : 2);
+        uint4 A[NA][MT];
+        if (contract) {
+            int set[NA];
+            if constexpr (BF16)
+                set[0] = UP == 8 ? 4 + sel : (sel ? 4 : 3);
+            else if constexpr (PB == 2)
+                set[0] = 0, set[1] = 1, set[2] = 2;
+            else if constexpr (UP == 8)
+                set[0] = sel, set[1] = 2 + sel;
+            else
+                set[0] = sel, set[1] = sel ? 4 : 2;
+            const uint4 *bp = Bop + (long long)min((PB == 2 ? s0 & ~3 : s0) + sl, s_end - 1) * 6 * Cp + n;
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) A[i][mt] = bp[set[i] * Cp + mt * 16];
         }
-        if (has_own) contract(ops_own, Qown);
-        if (has_oth) contract(ops_oth, Qx[wave]);
+        if (((s0 + 2 - s_begin) & 127) == 0) fill_origins(s0 + 2);
+        __syncthreads();  // Q is complete; the windows are free
+        // copies for the next pair run during this pair's MFMAs; the operands are
+        // waited for first, as the copies share their counter
+        __builtin_amdgcn_s_waitcnt(0);
+        if (!last) {
+            take_origins(s0 + 2);
+            if (s0 + 2 + grp < s_end) stage(s0 + 2 + grp);
+        }
+        if (!contract) continue;
+        // g tile += B^T (coefficients x (projection, piece, u)) * Q, the smallest
+        // products first.  The bf16 MFMA cuts off what it shifts out of its
+        // accumulator, always towards zero: with the sum over all projections kept
+        // there, the relative error grew with their number (1.1e-6 at 240, 2.1e-6 at
+        // 300, against 4.7e-7 and 7.2e-7), so a pair's products start from zero and
+        // are added to g with a rounded float32 add.
+        const uint4 *qb = &Qt[wave][0][sl][n];
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+            const s8 b0 = __builtin_bit_cast(s8, qb[nt * 16]);
+            if constexpr (BF16) {
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    acc[mt][nt] = mfma16x16x32bf16(__builtin_bit_cast(s8, A[0][mt]), b0, acc[mt][nt]);
+            } else {
+                // eight: (b0 q2, b2 q0), (b0 q1, b1 q1), (b0 q0, b1 q0); four: (b0 q2 + b2 q0),
+                // then (b0 q0 + b0 q1) and (b1 q0 + b1 q1), together or (two pairs) in turn
+                const s8 b2 = __builtin_bit_cast(s8, qb[(UP == 4 ? QS : sel ? 0 : 2 * QS) + nt * 16]);
+                f4 t[MT];
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    t[mt] = mfma16x16x32bf16(__builtin_bit_cast(s8, A[NA - 1][mt]), b2, f4{0.f, 0.f, 0.f, 0.f});
+                if constexpr (UP == 8 || PB == 2) {
+                    const s8 b1 = UP == 8 ? __builtin_bit_cast(s8, qb[QS + nt * 16]) : b0;
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        t[mt] = mfma16x16x32bf16(__builtin_bit_cast(s8, A[UP == 8 ? 0 : 1][mt]), b1, t[mt]);
+                }
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    t[mt] = mfma16x16x32bf16(__builtin_bit_cast(s8, A[0][mt]), b0, t[mt]);
+                    acc[mt][nt] += t[mt];
+                }
+            }
+        }
     }
 
+    if (split) {
+        g = split + (long long)blockIdx.y * nx * ny * nz * C;
+        c = nullptr;
+        partials = nullptr;
+    }
+    // epilogue: lane holds rows (coefficients) 16 mt + 4 (lane/16) + r of voxel column 16 nt + lane % 16
     double c2 = 0.0;
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) {
-        const int lv = nt * 16 + (lane & 15);
-        const int qy = by * 8 + (lv >> 3), qz = bz * 8 + (lv & 7);
-        if (px < nxh && qy < ny && qz < nz) {
-            const int vx = ix, vy = upper ? ny - 1 - qy : qy, vz = upper ? nz - 1 - qz : qz;
+        const int qx = x0 + nt, qy = y0 + ((lane >> 2) & 3), qz = z0 + (lane & 3);
+        if (qx < nxh && qy < ny && qz < nz) {
+            const int vx = upper ? nx - 1 - qx : qx, vy = upper ? ny - 1 - qy : qy, vz = upper ? nz - 1 - qz : qz;
             const long long base = (((long long)vx * ny + vy) * nz + vz) * C;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
@@ -2327,154 +1895,179 @@ __global__ __launch_bounds__(256) void k_backproject_pw(const float *__restrict_
     }
 }
 
-// Window extent (rows, columns) of a voxel box with centre spans (sx, sy, sz)
-// over the projections: span . |e| + 2 l + 3 (L1 reach on both sides and the
-// rounding margins); 0 if some projection exceeds lim.
-static void window_extent(const std::vector<ProjFrame> &frames, double sx, double sy, double sz, bool jos, int &wr,
-                          int &wc)
+// g = sum over the splits (in order) + beta c, with the float64 partials of sum c^2
+__global__ __launch_bounds__(256) void k_add_splits(const float *__restrict__ split, int ns, long long n,
+                                                    float *__restrict__ g, float beta, const float *__restrict__ c,
+                                                    double *__restrict__ partials)
+{
+    __shared__ double ws[4];
+    double c2 = 0.0;
+    for (long long e = blockIdx.x * 256LL + threadIdx.x; e < n; e += (long long)gridDim.x * 256) {
+        float v = split[e];
+        for (int i = 1; i < ns; ++i) v += split[i * n + e];
+        if (c) {
+            const float cv = c[e];
+            v += beta * cv;
+            c2 += (double)cv * (double)cv;
+        }
+        g[e] = v;
+    }
+    if (partials) {
+        const double tot = block_sum(c2, ws);
+        if (threadIdx.x == 0) partials[blockIdx.x] = tot;
+    }
+}
+
+// Splits of the projections over blocks, so that a small volume fills the chip.  A
+// compute unit works off n = ceil(blocks splits / units) blocks, three at a time; one
+// or two left over run alone, at about half and four fifths of the rate of three
+// (one or two waves per SIMD do not hide the LDS and scalar latencies).  Every split
+// writes and reads a coefficient volume, at about 4 TB/s, against about 1.2 us per
+// block and pair of projections.  Adjoint with its fold, unsplit -> split: 32^3 / 60
+// projections / 15 coefficients (128 blocks, six splits) 81 -> 52 us, 48^3 / 120 / 28
+// (432 blocks, three) 180 -> 172 us.
+static int adjoint_splits(const Dims &d, int blocks, int units)
+{
+    const double vol_us = 4.0 * d.nx * d.ny * d.nz * d.C / 4e6;
+    int best = 1;
+    double best_t = 1e300;
+    for (int ns = 1; ns <= kMaxSplits && (ns == 1 || 8 * ns <= d.S); ++ns) {
+        const int n = (int)(((long long)blocks * ns + units - 1) / units), r = n % 3;
+        const double work = 3 * (n / 3) + (r == 0 ? 0.0 : r == 1 ? 2.0 : 2.5);
+        const double t = 1.2 * 0.5 * d.S / ns * work + (ns > 1 ? 5.0 + (2 * ns + 1) * vol_us : 0.0);
+        if (t < 0.97 * best_t) {
+            best_t = t;
+            best = ns;
+        }
+    }
+    return best;
+}
+
+// Windows of the staged adjoint for a block's voxel box: rows and columns that hold
+// every ray of its voxels in any projection (centre span . |e| + 2 reach + 3 for
+// rounding), at most the detector; returns the dynamic LDS bytes of the two
+// windows, or 0 where they take more copies than the kernel keeps offsets for or
+// leave fewer than three blocks per CU (the general kernel then reads the residual
+// from memory).
+static int window_lds(const std::vector<ProjFrame> &frames, const Dims &d, bool pair, bool jos, int &wr, int &wc)
 {
     wr = wc = 0;
+    const double sx = 3.0, sy = pair ? 3.0 : 7.0, sz = 7.0;
     for (const ProjFrame &f : frames) {
-        // reach of one voxel's rays: the L1 radius of the trilinear support, or
-        // the parallelogram of Joseph cuts within one voxel
         const double rj = jos ? (double)f.jos_rj : f.lj, rk = jos ? (double)f.jos_rk : f.lk;
         const double sj = sx * fabs(f.ej[0]) + sy * fabs(f.ej[1]) + sz * fabs(f.ej[2]) + 2 * rj;
         const double sk = sx * fabs(f.ek[0]) + sy * fabs(f.ek[1]) + sz * fabs(f.ek[2]) + 2 * rk;
         wr = std::max(wr, (int)floor(sj) + 3);
         wc = std::max(wc, (int)floor(sk) + 3);
     }
+    wr = std::min(wr, d.nj);
+    wc = std::min(wc, d.nk);
+    if (d.Up > 8) return 0;
+    const int nel = (wr * wc * (d.Up / 4) * (pair ? 2 : 1) + 127) & ~127;
+    const int fixed = (d.Up == 8 ? 3 : d.Cp >= 48 ? 4 : 2) * 8192 + 2048;
+    return nel <= kWinCopies * 128 && 2 * nel * 16 + fixed <= 53 * 1024 ? 2 * nel * 16 : 0;
 }
 
-// Paired + windowed adjoint: four windows of wr x wc rays x 8 floats beside
-// 18 KiB of Q tiles must leave three blocks per CU (<= 52 KiB per block).
-int backproject_pw_lds(const std::vector<ProjFrame> &frames, int up, bool jos, int &wr, int &wc)
+static int win_blocks(const Dims &d, bool pair)
 {
-    window_extent(frames, 1.0, 7.0, 7.0, jos, wr, wc);
-    const int bytes = 4 * wr * wc * up * 4;
-    return bytes + 2 * 4 * 64 * (up + 1) * 4 <= 52 * 1024 ? bytes : 0;
+    return pair ? ((d.nx / 2 + 3) / 4) * ((d.ny + 3) / 4) * ((d.nz + 7) / 8)
+                : ((d.nx + 3) / 4) * ((d.ny + 7) / 8) * ((d.nz + 7) / 8);
 }
 
-// Largest detector window of a 4 x 8 x 8 brick over the projections: rows
-// <= 3|e_jx| + 7|e_jy| + 7|e_jz| + 2 l_j + 3 (the voxel-centre span, the L1 reach
-// on both sides, and the rounding margins), columns likewise with e_k.
-bool backproject_window_fits(const std::vector<ProjFrame> &frames)
+void plan_adjoint(const std::vector<ProjFrame> &frames, Dims &d)
 {
-    for (const ProjFrame &f : frames) {
-        const double sj = 3 * fabs(f.ej[0]) + 7 * fabs(f.ej[1]) + 7 * fabs(f.ej[2]) + 2 * f.lj;
-        const double sk = 3 * fabs(f.ek[0]) + 7 * fabs(f.ek[1]) + 7 * fabs(f.ek[2]) + 2 * f.lk;
-        if (floor(sj) + 3 > kWinMax || floor(sk) + 3 > kWinMax) return false;
+    int dev = 0, units = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || units < 1)
+        units = 256;
+    for (int jos = 0; jos < 2; ++jos) {
+        AdjointPlan &p = d.adj[jos];
+        p.pair = d.inv_pair;
+        p.lds = window_lds(frames, d, p.pair != 0, jos != 0, p.wr, p.wc);
+        if (p.lds == 0 && p.pair) {  // a paired window is twice as large per ray
+            p.pair = 0;
+            p.lds = window_lds(frames, d, false, jos != 0, p.wr, p.wc);
+        }
+        p.splits = p.lds > 0 ? adjoint_splits(d, win_blocks(d, p.pair != 0), units) : 1;
     }
-    return true;
 }
-
-// Pairing pays with four unique segments (C2-like workloads: the adjoint
-// 4.21 -> 3.21 ms at 100^3 / 240 projections).  With eight, its own and
-// mirrored residual loads and accumulators raise the register count from 78
-// to 102 (three waves per SIMD instead of four) and the kernel, then bound by
-// load latency rather than by VALU issue, measured 10% slower than the
-// unpaired one (5% of it the per-pair barrier), so it is not used there.
-static bool use_inv_pair(const Dims &d) { return d.inv_pair && d.Up == 4; }
-static bool use_window(const Dims &d) { return d.win_ok && !d.joseph && d.Up == 8; }
-static bool use_pw(const Dims &d) { return (d.joseph ? d.pwj_lds : d.pw_lds) > 0 && d.inv_pair && d.Up == 8; }
-static int backproject_inv_blocks(const Dims &d) { return ((d.nx / 2 + 1) / 2) * ((d.ny + 7) / 8) * ((d.nz + 7) / 8); }
 
 int backproject_blocks(const Dims &d)
 {
-    return use_inv_pair(d) || use_pw(d) ? backproject_inv_blocks(d) : ((d.nx + 3) / 4) * ((d.ny + 7) / 8) * ((d.nz + 7) / 8);
+    const AdjointPlan &p = d.adj[d.joseph];
+    return win_blocks(d, p.lds > 0 && p.pair);
 }
-int backproject_blocks_max(const Dims &d) { return ((d.nx + 3) / 4) * ((d.ny + 7) / 8) * ((d.nz + 7) / 8); }
+int backproject_blocks_max(const Dims &d) { return std::max(win_blocks(d, true), win_blocks(d, false)); }
+
+template <int UP, int MT, bool BF16, bool JOS>
+static void bp_launch(const Dims &d, const ProjFrame *frames, const float *yf, const AdjointTables &t, float *split,
+                      float *g, float beta, const float *c, double *partials, hipStream_t st)
+{
+    const AdjointPlan &p = d.adj[JOS];
+    const int nb = backproject_blocks(d);
+    if constexpr (UP <= 8) {
+        if (p.lds > 0) {
+            const uint4 *bop = reinterpret_cast<const uint4 *>(t.Bop);
+            const int ns = split ? p.splits : 1;
+            const int s_per = ns > 1 ? (d.S + 4 * ns - 1) / (4 * ns) * 4 : d.S;  // whole double pairs
+            const dim3 grid(nb, (d.S + s_per - 1) / s_per);
+            float *sp = grid.y > 1 ? split : nullptr;
+            auto launch = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, grid, dim3(256), p.lds, st, yf, frames, bop, d.S, d.nx, d.ny, d.nz, d.nj,
+                                   d.nk, d.C, d.Cp, d.step, g, beta, c, partials, p.wr, p.wc, s_per, sp);
+            };
+            if (p.pair)
+                launch(k_backproject_win<UP, MT, BF16, JOS, true>);
+            else
+                launch(k_backproject_win<UP, MT, BF16, JOS, false>);
+            if (sp)
+                hipLaunchKernelGGL(k_add_splits, dim3(nb), dim3(256), 0, st, sp, (int)grid.y,
+                                   (long long)d.nx * d.ny * d.nz * d.C, g, beta, c, partials);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_backproject<UP, MT, BF16, JOS>), dim3(nb), dim3(256), 0, st, yf, frames, t.Bu,
+                       reinterpret_cast<const s4 *>(t.BuT16), d.S, d.nx, d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step, g,
+                       beta, c, partials);
+}
 
 template <int UP, int MT>
-static hipError_t bp_t(const Dims &d, const ProjFrame *frames, const float *yf, const float *Bu, const uint16_t *BuT16,
-                       int bf16, float *g, float beta, const float *c, double *partials, hipStream_t st)
+static hipError_t bp_t(const Dims &d, const ProjFrame *frames, const float *yf, const AdjointTables &t, float *split, int bf16,
+                       float *g, float beta, const float *c, double *partials, hipStream_t st)
 {
-    const s4 *bt = reinterpret_cast<const s4 *>(BuT16);
-    const dim3 grid(backproject_blocks(d)), block(256);
-    if constexpr (UP == 4) {
-        if (use_inv_pair(d)) {
-            if (bf16 && d.joseph)
-                hipLaunchKernelGGL((k_backproject_inv<UP, MT, true, true>), grid, block, 0, st, yf, frames, Bu, bt,
-                                   d.S, d.nx, d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step, g, beta, c, partials);
-            else if (bf16)
-                hipLaunchKernelGGL((k_backproject_inv<UP, MT, true, false>), grid, block, 0, st, yf, frames, Bu, bt,
-                                   d.S, d.nx, d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step, g, beta, c, partials);
-            else if (d.joseph)
-                hipLaunchKernelGGL((k_backproject_inv<UP, MT, false, true>), grid, block, 0, st, yf, frames, Bu, bt,
-                                   d.S, d.nx, d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step, g, beta, c, partials);
-            else
-                hipLaunchKernelGGL((k_backproject_inv<UP, MT, false, false>), grid, block, 0, st, yf, frames, Bu, bt,
-                                   d.S, d.nx, d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step, g, beta, c, partials);
-            return hipGetLastError();
-        }
-    }
-    if constexpr (UP == 8) {
-        if (use_pw(d)) {
-            // residual windows sized for the model's reach
-            const int lds = d.joseph ? d.pwj_lds : d.pw_lds;
-            const int wr = d.joseph ? d.pwj_wr : d.pw_wr, wc = d.joseph ? d.pwj_wc : d.pw_wc;
-            if (bf16 && d.joseph)
-                hipLaunchKernelGGL((k_backproject_pw<UP, MT, true, true>), grid, block, lds, st, yf, frames, Bu, bt,
-                                   d.S, d.nx, d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step, g, beta, c, partials, wr, wc);
-            else if (bf16)
-                hipLaunchKernelGGL((k_backproject_pw<UP, MT, true, false>), grid, block, lds, st, yf, frames, Bu, bt,
-                                   d.S, d.nx, d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step, g, beta, c, partials, wr, wc);
-            else if (d.joseph)
-                hipLaunchKernelGGL((k_backproject_pw<UP, MT, false, true>), grid, block, lds, st, yf, frames, Bu, bt,
-                                   d.S, d.nx, d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step, g, beta, c, partials, wr, wc);
-            else
-                hipLaunchKernelGGL((k_backproject_pw<UP, MT, false, false>), grid, block, lds, st, yf, frames, Bu, bt,
-                                   d.S, d.nx, d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step, g, beta, c, partials, wr, wc);
-            return hipGetLastError();
-        }
-        if (use_window(d)) {
-            if (bf16)
-                hipLaunchKernelGGL((k_backproject_win<UP, MT, true>), grid, block, 0, st, yf, frames, Bu, bt, d.S,
-                                   d.nx, d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step, g, beta, c, partials);
-            else
-                hipLaunchKernelGGL((k_backproject_win<UP, MT, false>), grid, block, 0, st, yf, frames, Bu, bt, d.S,
-                                   d.nx, d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step, g, beta, c, partials);
-            return hipGetLastError();
-        }
-    }
     if (bf16 && d.joseph)
-        hipLaunchKernelGGL((k_backproject<UP, MT, true, true>), grid, block, 0, st, yf, frames, Bu, bt, d.S, d.nx,
-                           d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step, g, beta, c, partials);
+        bp_launch<UP, MT, true, true>(d, frames, yf, t, split, g, beta, c, partials, st);
     else if (bf16)
-        hipLaunchKernelGGL((k_backproject<UP, MT, true, false>), grid, block, 0, st, yf, frames, Bu, bt, d.S, d.nx,
-                           d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step, g, beta, c, partials);
+        bp_launch<UP, MT, true, false>(d, frames, yf, t, split, g, beta, c, partials, st);
     else if (d.joseph)
-        hipLaunchKernelGGL((k_backproject<UP, MT, false, true>), grid, block, 0, st, yf, frames, Bu, bt, d.S, d.nx,
-                           d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step, g, beta, c, partials);
+        bp_launch<UP, MT, false, true>(d, frames, yf, t, split, g, beta, c, partials, st);
     else
-        hipLaunchKernelGGL((k_backproject<UP, MT, false, false>), grid, block, 0, st, yf, frames, Bu, bt, d.S, d.nx,
-                           d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step, g, beta, c, partials);
+        bp_launch<UP, MT, false, false>(d, frames, yf, t, split, g, beta, c, partials, st);
     return hipGetLastError();
 }
 
 template <int UP>
-static hipError_t bp_mt(const Dims &d, const ProjFrame *frames, const float *yf, const float *Bu,
-                        const uint16_t *BuT16, int bf16, float *g, float beta, const float *c, double *partials,
-                        hipStream_t st)
+static hipError_t bp_mt(const Dims &d, const ProjFrame *frames, const float *yf, const AdjointTables &t, float *split, int bf16,
+                        float *g, float beta, const float *c, double *partials, hipStream_t st)
 {
     switch (d.Cp / 16) {
-    case 1: return bp_t<UP, 1>(d, frames, yf, Bu, BuT16, bf16, g, beta, c, partials, st);
-    case 2: return bp_t<UP, 2>(d, frames, yf, Bu, BuT16, bf16, g, beta, c, partials, st);
-    case 3: return bp_t<UP, 3>(d, frames, yf, Bu, BuT16, bf16, g, beta, c, partials, st);
-    case 4: return bp_t<UP, 4>(d, frames, yf, Bu, BuT16, bf16, g, beta, c, partials, st);
-    case 5: return bp_t<UP, 5>(d, frames, yf, Bu, BuT16, bf16, g, beta, c, partials, st);
-    case 6: return bp_t<UP, 6>(d, frames, yf, Bu, BuT16, bf16, g, beta, c, partials, st);
+    case 1: return bp_t<UP, 1>(d, frames, yf, t, split, bf16, g, beta, c, partials, st);
+    case 2: return bp_t<UP, 2>(d, frames, yf, t, split, bf16, g, beta, c, partials, st);
+    case 3: return bp_t<UP, 3>(d, frames, yf, t, split, bf16, g, beta, c, partials, st);
+    case 4: return bp_t<UP, 4>(d, frames, yf, t, split, bf16, g, beta, c, partials, st);
+    case 5: return bp_t<UP, 5>(d, frames, yf, t, split, bf16, g, beta, c, partials, st);
+    case 6: return bp_t<UP, 6>(d, frames, yf, t, split, bf16, g, beta, c, partials, st);
     default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_backproject(const Dims &d, const ProjFrame *frames, const float *yf, const float *Bu,
-                              const uint16_t *BuT16, int bf16, float *g, float beta, const float *c, double *partials,
-                              hipStream_t st)
+hipError_t launch_backproject(const Dims &d, const ProjFrame *frames, const float *yf, const AdjointTables &t,
+                              float *split, int bf16, float *g, float beta, const float *c, double *partials, hipStream_t st)
 {
     switch (d.Up) {
-    case 4: return bp_mt<4>(d, frames, yf, Bu, BuT16, bf16, g, beta, c, partials, st);
-    case 8: return bp_mt<8>(d, frames, yf, Bu, BuT16, bf16, g, beta, c, partials, st);
-    case 16: return bp_mt<16>(d, frames, yf, Bu, BuT16, bf16, g, beta, c, partials, st);
+    case 4: return bp_mt<4>(d, frames, yf, t, split, bf16, g, beta, c, partials, st);
+    case 8: return bp_mt<8>(d, frames, yf, t, split, bf16, g, beta, c, partials, st);
+    case 16: return bp_mt<16>(d, frames, yf, t, split, bf16, g, beta, c, partials, st);
     default: return hipErrorInvalidValue;
     }
 }
