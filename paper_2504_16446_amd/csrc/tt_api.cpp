@@ -125,7 +125,7 @@ static uint16_t to_bf16(float x)
 struct Tables {
     std::vector<float> bu;         // [bu_rows][Cp]: row s*Up + u, zero padded
     std::vector<float> bsw;        // bu in MFMA lane order: tile rt, k-step ks, lane l
-    std::vector<uint16_t> bsw16;   // bf16 bu in MFMA lane order (16-row tiles, k blocks of 16)
+    std::vector<uint16_t> bsw16;   // bf16 bu in MFMA lane order (16-row tiles, 32-coefficient steps)
     std::vector<uint16_t> but16;   // bf16 [S][Cp][16]: B^T with u padded to 16
     std::vector<uint16_t> bop;     // [S][6][Cp][8]: operands of the staged adjoint
 };
@@ -139,24 +139,20 @@ static void build_tables(const tt_ctx *c, Tables &t)
         for (int u = 0; u < d.U; ++u)
             for (int i = 0; i < d.C; ++i)
                 t.bu[((size_t)s * d.Up + u) * d.Cp + i] = (float)c->B[((size_t)s * d.nseg + u) * d.C + i];
-    // row tile rt (16 Cp values): 32-coefficient steps kp, lane l, eight values
-    // bu[16 rt + l % 16][32 kp + 8 (l / 16) + q]; then, for Cp / 16 odd, the last
-    // 16 coefficients as four values bu[16 rt + l % 16][32 KP + 4 (l / 16) + q]
-    const int KP = d.Cp / 32;
-    t.bsw16.assign(t.bu.size(), 0);
+    // row tile rt, 32-coefficient step kp, lane l: eight values
+    // bu[16 rt + l % 16][32 kp + 8 (l / 16) + q], zero from Cp on
+    const int KP = (d.Cp + 31) / 32;
+    t.bsw16.assign((size_t)bu_rows / 16 * KP * 512, 0);
     t.but16.assign((size_t)S * d.Cp * 16, 0);
-    for (int rt = 0; rt < bu_rows / 16; ++rt) {
-        const size_t base = (size_t)rt * 16 * d.Cp;
+    for (int rt = 0; rt < bu_rows / 16; ++rt)
         for (int l = 0; l < 64; ++l) {
             const float *row = &t.bu[((size_t)rt * 16 + l % 16) * d.Cp];
             for (int kp = 0; kp < KP; ++kp)
-                for (int q = 0; q < 8; ++q)
-                    t.bsw16[base + ((size_t)kp * 64 + l) * 8 + q] = to_bf16(row[32 * kp + 8 * (l / 16) + q]);
-            if (d.Cp & 16)
-                for (int q = 0; q < 4; ++q)
-                    t.bsw16[base + (size_t)KP * 512 + l * 4 + q] = to_bf16(row[32 * KP + 4 * (l / 16) + q]);
+                for (int q = 0; q < 8; ++q) {
+                    const int k = 32 * kp + 8 * (l / 16) + q;
+                    if (k < d.Cp) t.bsw16[(((size_t)rt * KP + kp) * 64 + l) * 8 + q] = to_bf16(row[k]);
+                }
         }
-    }
     for (int s = 0; s < S; ++s)
         for (int i = 0; i < d.Cp; ++i)
             for (int u = 0; u < d.Up; ++u)
@@ -435,7 +431,7 @@ int tt_create(const tt_geometry *geom, tt_ctx **out)
         hipMalloc(&c->d_sp, sp_len * sizeof(int2)) != hipSuccess ||
         hipMalloc(&c->d_gtab, gtab_len * sizeof(int)) != hipSuccess)
         return cleanup(TT_ENOMEM, "device allocation failed");
-    c->table_bytes = sizeof(ProjFrame) * S + bu.size() * 10 + (but16.size() + t.bop.size()) * 2 + sp_len * sizeof(int2) +
+    c->table_bytes = sizeof(ProjFrame) * S + bu.size() * 8 + (bsw16.size() + but16.size() + t.bop.size()) * 2 + sp_len * sizeof(int2) +
                      gtab_len * sizeof(int);
     if (hipMemcpy(c->d_frames, c->frames.data(), sizeof(ProjFrame) * S, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(c->d_Bu, bu.data(), bu.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||

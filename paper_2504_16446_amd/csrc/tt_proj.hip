@@ -300,21 +300,22 @@ hipError_t launch_map_fp32(const Dims &d, const float *c, const float *Bsw, int 
 // ---------------------------------------------------------------------------
 // map, bf16 tier: c is rounded to bf16 while it is staged in LDS, B comes as
 // bf16 in MFMA lane order, products accumulate in fp32.  K = Cp runs in
-// 32-coefficient steps on the 16x16x32 instruction and, when Cp / 16 is odd,
-// a last 16-coefficient step on the 16x16x16 one.  Row tile rt of Bsw16
-// (16 Cp shorts at rt * 16 Cp) holds for step kp < Cp / 32 and lane l the
-// eight values Bu[16 rt + l % 16][32 kp + 8 (l / 16) + q] at (kp * 64 + l) * 8,
-// then for the odd step the four values Bu[16 rt + l % 16][32 (Cp / 32) +
-// 4 (l / 16) + q] at (Cp / 32) * 512 + l * 4.  Same tiling as the fp32 kernel.
+// 32-coefficient steps on the 16x16x32 instruction, the last one filled up with
+// zeros when Cp / 16 is odd.  (It must not end in a 16x16x16 step: that
+// instruction right behind a 16x16x32 one on the same accumulator took the
+// accumulator's first two registers before they were written, in a few tiles of a
+// million, so that repeated forwards differed by 1e-3.)  Row tile rt of Bsw16 holds
+// for step kp and lane l the eight values Bu[16 rt + l % 16][32 kp + 8 (l / 16) + q]
+// at ((rt KP + kp) 64 + l) 8, KP = ceil(Cp / 32).  Same tiling as the fp32 kernel.
 // ---------------------------------------------------------------------------
 template <int UP>
 __global__ __launch_bounds__(256) void k_map_bf16(const float *__restrict__ c, const short *__restrict__ Bsw16,
                                                   int V, int C, int Cp, int ny, int nz, int s0, int np,
                                                   long long vol_pad, float *__restrict__ M)
 {
-    extern __shared__ short cb[];  // [64][Cp + 8] bf16, row = voxel (16-byte rows)
+    extern __shared__ short cb[];  // [64][32 KP + 8] bf16, row = voxel (16-byte rows)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int ld = Cp + 8;
+    const int KP = (Cp + 31) / 32, ld = 32 * KP + 8;
     const int v0 = blockIdx.x * 64;
     const int nv = min(64, V - v0);
     const float *cg = c + (long long)v0 * C;
@@ -328,7 +329,6 @@ __global__ __launch_bounds__(256) void k_map_bf16(const float *__restrict__ c, c
     }
     __syncthreads();
 
-    const int KP = Cp / 32;
     const int rt0 = (s0 * UP) / 16 + blockIdx.y * 16 + wave * 4;
     const int kq = lane >> 4;
     f4 acc[4][4];
@@ -340,24 +340,12 @@ __global__ __launch_bounds__(256) void k_map_bf16(const float *__restrict__ c, c
         s8 a[4];
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt)
-            a[mt] = *reinterpret_cast<const s8 *>(Bsw16 + (long long)(rt0 + mt) * 16 * Cp + (kp * 64 + lane) * 8);
+            a[mt] = *reinterpret_cast<const s8 *>(Bsw16 + ((long long)(rt0 + mt) * KP + kp) * 512 + lane * 8);
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) {
             const s8 b = *reinterpret_cast<const s8 *>(cb + (nt * 16 + (lane & 15)) * ld + kp * 32 + 8 * kq);
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt) acc[nt][mt] = mfma16x16x32bf16(a[mt], b, acc[nt][mt]);
-        }
-    }
-    if (Cp & 16) {
-        s4 a[4];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-            a[mt] = *reinterpret_cast<const s4 *>(Bsw16 + (long long)(rt0 + mt) * 16 * Cp + KP * 512 + lane * 4);
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const s4 b = *reinterpret_cast<const s4 *>(cb + (nt * 16 + (lane & 15)) * ld + KP * 32 + 4 * kq);
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt) acc[nt][mt] = mfma16x16x16bf16(a[mt], b, acc[nt][mt]);
         }
     }
 #pragma unroll
@@ -386,8 +374,8 @@ __global__ __launch_bounds__(64 * NW) void k_map_bf16_rb(const float *__restrict
                                                          int V, int C, int ny, int nz, int s0, int np,
                                                          long long vol_pad, float *__restrict__ M)
 {
-    constexpr int Cp = 16 * CPT, KP = CPT / 2, ODD = CPT & 1;
-    constexpr int ld = Cp + 8;                  // LDS row of one voxel, in shorts (16-byte multiple)
+    constexpr int Cp = 16 * CPT, KP = (CPT + 1) / 2;
+    constexpr int ld = 32 * KP + 8;             // LDS row of one voxel, in shorts (16-byte multiple)
     constexpr int NT = 64 * NW;                 // threads of the block
     constexpr int MW = 16 / NW;                 // row tiles per wave (256 rows per block)
     constexpr int NPF = (16 * Cp + NT - 1) / NT;  // float4 per thread covering a 64 x C tile (C <= Cp)
@@ -395,15 +383,12 @@ __global__ __launch_bounds__(64 * NW) void k_map_bf16_rb(const float *__restrict
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int kq = lane >> 4;
     const int rt0 = (s0 * UP) / 16 + blockIdx.y * 16 + wave * MW;
-    s8 a8[MW][KP > 0 ? KP : 1];
-    s4 a4[MW];
+    s8 a8[MW][KP];
 #pragma unroll
-    for (int mt = 0; mt < MW; ++mt) {
-        const short *rt = Bsw16 + (long long)(rt0 + mt) * 16 * Cp;
+    for (int mt = 0; mt < MW; ++mt)
 #pragma unroll
-        for (int kp = 0; kp < KP; ++kp) a8[mt][kp] = *reinterpret_cast<const s8 *>(rt + (kp * 64 + lane) * 8);
-        if constexpr (ODD) a4[mt] = *reinterpret_cast<const s4 *>(rt + KP * 512 + lane * 4);
-    }
+        for (int kp = 0; kp < KP; ++kp)
+            a8[mt][kp] = *reinterpret_cast<const s8 *>(Bsw16 + ((long long)(rt0 + mt) * KP + kp) * 512 + lane * 8);
     // coefficients C..ld-1 of every voxel row stay zero for every tile
     for (int e = tid; e < 64 * (ld - C); e += NT) cb[(e / (ld - C)) * ld + C + e % (ld - C)] = 0;
     const int ntiles = (V + 63) / 64;
@@ -461,14 +446,6 @@ __global__ __launch_bounds__(64 * NW) void k_map_bf16_rb(const float *__restrict
                 for (int mt = 0; mt < MW; ++mt) acc[nt][mt] = mfma16x16x32bf16(a8[mt][kp], b, acc[nt][mt]);
             }
         }
-        if constexpr (ODD) {
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const s4 b = *reinterpret_cast<const s4 *>(cb + (nt * 16 + (lane & 15)) * ld + KP * 32 + 4 * kq);
-#pragma unroll
-                for (int mt = 0; mt < MW; ++mt) acc[nt][mt] = mfma16x16x16bf16(a4[mt], b, acc[nt][mt]);
-            }
-        }
         const int v0 = tile * 64;
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) {
@@ -522,7 +499,7 @@ static hipError_t map_bf16_t(const Dims &d, const float *c, const uint16_t *Bsw1
     const int V = d.nx * d.ny * d.nz;
     const long long vol_pad = (long long)(d.nx + 2) * (d.ny + 2) * (d.nz + 2);
     dim3 grid((V + 63) / 64, (np * UP + 255) / 256);
-    size_t lds = (size_t)64 * (d.Cp + 8) * sizeof(short);
+    size_t lds = (size_t)64 * ((d.Cp + 31) / 32 * 32 + 8) * sizeof(short);
     hipLaunchKernelGGL(k_map_bf16<UP>, grid, dim3(256), lds, st, c, reinterpret_cast<const short *>(Bsw16), V, d.C,
                        d.Cp, d.ny, d.nz, s0, np, vol_pad, M);
     return hipGetLastError();
