@@ -146,151 +146,205 @@ __global__ __launch_bounds__(256) void k_conv(const u16 *__restrict__ x, const s
 }
 
 // ---------------------------------------------------------------------------
-// Weight gradient, split over K (voxels): block (tap, chunk) accumulates
-// gw[tap] over the voxel tiles t = chunk, chunk + nchunks, ... and writes its
-// CI x CO partial; a second kernel sums the partials in chunk order.
-// Tiles are staged channel-major in LDS so both MFMA operands read 8
-// consecutive voxels of one channel.  Staging item (row, octet): the 8
-// voxels of one z-row of the tile (contiguous in the tile's voxel order) and
-// 8 channels; the thread loads the 8 voxels' 16-byte channel octets,
-// transposes the 8 x 8 block in registers and writes 8 rows of 16 bytes.
-// The next tile's loads are issued before the current tile's MFMAs.
+// Weight gradient gw[d][ci][co] = sum_v x[v + d - 1, ci] gy[v, co] as a GEMM with
+// K = voxels.  Block (dx, chunk) accumulates the nine taps (dx, *, *) over the voxel
+// tiles t = chunk, chunk + nchunks, ... in registers (each wave a quarter of the
+// CI x CO outputs of every tap) and writes its partials; a second kernel sums them
+// in chunk order.
+//
+// The tile (2 x 8 x 8 voxels) of gy and its halo of x (x shifted by dx - 1, one
+// voxel more in y and z) are staged channels-last, as they are in memory.  The
+// operands need eight consecutive voxels of one channel per lane, so they are read
+// with gfx950's transposing LDS loads (a group of 16 lanes reads 4 voxels x 16
+// channels and each lane gets one channel's 4 voxels); a tap is a shifted read.
+// K = 32 takes the z-rows y = j, j + 2, j + 4, j + 6 (lane group kq: y = j + 2 kq), so
+// that the operand of tap dy at j is that of row offset j + dy - 1 in the same lanes:
+// 12 x fragments per x-slice serve 18 (j, tap) products.  The next tile's loads are
+// in flight during the MFMAs.
+//
+// Measured, with gb (batch 8 x 48^3): 64 -> 64 channels 829 -> 214 us (236 -> 913
+// TFLOP/s), 32 -> 64 672 -> 138, 64 -> 32 609 -> 132, 32 -> 32 434 -> 108; batch 1,
+// 64 -> 64 140 -> 53.  The kernel it replaces ran one tap per block: 27 reads of x and
+// gy, and an 8 x 8 register transpose per staged octet.  Now the MFMAs (16 cycles
+// each, two waves per SIMD) and the 110 KiB of partials per chunk and dx (1 KiB per
+// output tile: at batch 1 half of the time) bound it.
+//
+// gb: each tile's gy is summed, as it is staged, by one of its three blocks.
 // ---------------------------------------------------------------------------
-struct Oct8 {
-    uint4 v[8];
-};
+constexpr int WX = 2, WY = 8, WZ = 8, WV = WX * WY * WZ;      // tile
+constexpr int WHY = WY + 2, WHZ = WZ + 2, WHV = WX * WHY * WHZ;  // x halo (x extent WX)
 
-// w[q] = the q-th channel of the 8 voxels in r.v[0..7], as 8 packed bf16
-__device__ __forceinline__ uint4 oct_column(const Oct8 &r, int q)
+typedef short s4 __attribute__((ext_vector_type(4)));
+
+// eight voxels (two groups of four, `step` shorts apart) of one channel per lane
+__device__ __forceinline__ s8 read_tr(const u16 *p, int step)
 {
-    unsigned h[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const unsigned word = (q >> 1) == 0 ? r.v[i].x : (q >> 1) == 1 ? r.v[i].y : (q >> 1) == 2 ? r.v[i].z : r.v[i].w;
-        h[i] = (q & 1) ? (word >> 16) : (word & 0xffffu);
-    }
-    return make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+    typedef __attribute__((address_space(3))) s4 *lp;
+    const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p));
+    const s4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p + step));
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
 template <int CI, int CO>
-__global__ __launch_bounds__(256) void k_wgrad(const u16 *__restrict__ x, const u16 *__restrict__ gy, int N, int X,
-                                               int Y, int Z, int nchunks, float *__restrict__ part)
+__global__ __launch_bounds__(256, 2) void k_wgrad(const u16 *__restrict__ x, const u16 *__restrict__ gy, int N, int X,
+                                                  int Y, int Z, int nchunks, float *__restrict__ part,
+                                                  float *__restrict__ bpart)
 {
-    constexpr int LDV = TV + 8;  // padded voxel stride (bf16; 16-byte rows)
-    __shared__ __attribute__((aligned(16))) u16 xs[CI * LDV];
-    __shared__ __attribute__((aligned(16))) u16 gs[CO * LDV];
+    constexpr int LX = CI + 8, LG = CO + 8;     // padded voxel strides (shorts): spread over the banks
+    constexpr int CX = CI / 8, CG = CO / 8;     // 16-byte octets per voxel
+    constexpr int NX = (WHV * CX + 255) / 256, NG = WV * CG / 256;  // staged octets per thread
+    constexpr int WM = CI == CO ? 2 : (CI < CO ? 1 : 4), WN = 4 / WM;  // waves over ci and co
+    constexpr int MT = CI / 16 / WM, NT = CO / 16 / WN;
+    __shared__ __attribute__((aligned(16))) u16 xs[WHV * LX];
+    __shared__ __attribute__((aligned(16))) u16 gs[WV * LG];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tap = blockIdx.x / nchunks, chunk = blockIdx.x % nchunks;
-    const int dx = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dz = tap % 3 - 1;
-    const int nbz = (Z + TZ - 1) / TZ, nby = (Y + TY - 1) / TY, nbx = (X + TX - 1) / TX;
+    // the three blocks of a chunk run on one XCD (blocks go round the eight XCDs)
+    const int i8 = blockIdx.x >> 3, chunk = (i8 / 3) * 8 + (blockIdx.x & 7), dxi = i8 % 3;
+    if (chunk >= nchunks) return;
+    const int nbz = (Z + WZ - 1) / WZ, nby = (Y + WY - 1) / WY, nbx = (X + WX - 1) / WX;
     const int ntiles = N * nbx * nby * nbz;
     const long long vol = (long long)X * Y * Z;
-    constexpr int MT = CI / 16, NT = CO / 16;
-    constexpr int TPW = MT * NT / 4;  // output tiles per wave
-    constexpr int ROWS = TX * TY;     // z-rows of TZ = 8 voxels per tile
-    constexpr int XI = ROWS * (CI / 8), GI = ROWS * (CO / 8);  // staging items of x and gy
-    static_assert(TZ == 8 && XI + GI <= 256, "one staging item per thread");
-    // this thread's staging item: x rows first, then gy rows
-    const bool is_x = tid < XI, has_item = tid < XI + GI;
-    const int it = is_x ? tid : tid - XI;
-    const int row = it % ROWS, oct = it / ROWS;
-    const int rtx = row / TY, rty = row % TY;
-    const int cstride = is_x ? CI : CO;
-    const u16 *src = is_x ? x : gy;
-    const int sx = is_x ? dx : 0, sy = is_x ? dy : 0, sz = is_x ? dz : 0;
-    u16 *dst = (is_x ? xs : gs) + oct * 8 * LDV + row * TZ;
 
-    auto load = [&](int t, Oct8 &r) {
+    uint4 rx[NX], rg[NG];
+    auto load = [&](int t) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) r.v[i] = make_uint4(0, 0, 0, 0);
-        if (!has_item || t >= ntiles) return;
+        for (int i = 0; i < NX; ++i) rx[i] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < NG; ++i) rg[i] = make_uint4(0, 0, 0, 0);
+        if (t >= ntiles) return;
         int b = t;
-        const int bz = b % nbz;
+        const int z0 = b % nbz * WZ;
         b /= nbz;
-        const int by = b % nby;
+        const int y0 = b % nby * WY;
         b /= nby;
-        const int bx = b % nbx;
-        const int n = b / nbx;
-        const int ox = bx * TX + rtx, oy = by * TY + rty;
-        const int gx = ox + sx, gyy = oy + sy;
-        if (ox >= X || oy >= Y || gx < 0 || gx >= X || gyy < 0 || gyy >= Y) return;
-        const u16 *p = src + ((long long)n * vol + ((long long)gx * Y + gyy) * Z) * cstride + oct * 8;
+        const int x0 = b % nbx * WX, n = b / nbx;
+        const u16 *xn = x + (long long)n * vol * CI, *gn = gy + (long long)n * vol * CO;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int oz = bz * TZ + i, gz = oz + sz;
-            if (oz < Z && gz >= 0 && gz < Z) r.v[i] = *reinterpret_cast<const uint4 *>(p + (long long)gz * cstride);
+        for (int i = 0; i < NX; ++i) {
+            const int e = tid + 256 * i, p = e / CX;
+            const int gx = x0 + p / (WHY * WHZ) + dxi - 1, gyy = y0 + p / WHZ % WHY - 1, gz = z0 + p % WHZ - 1;
+            if (e < WHV * CX && (unsigned)gx < (unsigned)X && (unsigned)gyy < (unsigned)Y && (unsigned)gz < (unsigned)Z)
+                rx[i] = *reinterpret_cast<const uint4 *>(xn + (((long long)gx * Y + gyy) * Z + gz) * CI + e % CX * 8);
+        }
+#pragma unroll
+        for (int i = 0; i < NG; ++i) {
+            const int e = tid + 256 * i, p = e / CG;
+            const int gx = x0 + p / (WY * WZ), gyy = y0 + p / WZ % WY, gz = z0 + p % WZ;
+            if (gx < X && gyy < Y && gz < Z)
+                rg[i] = *reinterpret_cast<const uint4 *>(gn + (((long long)gx * Y + gyy) * Z + gz) * CO + e % CG * 8);
         }
     };
 
-    f4 acc[TPW];
+    f4 acc[9][MT][NT];
 #pragma unroll
-    for (int i = 0; i < TPW; ++i) acc[i] = f4{0.f, 0.f, 0.f, 0.f};
-    const int kq = lane >> 4;
-    Oct8 cur;
-    load(chunk, cur);
-    for (int t = chunk; t < ntiles; t += nchunks) {
-        __syncthreads();  // the previous tile's MFMA reads are done
-        if (has_item) {
+    for (int a = 0; a < 9; ++a)
 #pragma unroll
-            for (int q = 0; q < 8; ++q) *reinterpret_cast<uint4 *>(dst + q * LDV) = oct_column(cur, q);
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[a][mt][nt] = f4{0.f, 0.f, 0.f, 0.f};
+    float bs[8];  // sums of this thread's octet of gy channels
+#pragma unroll
+    for (int q = 0; q < 8; ++q) bs[q] = 0.0f;
+    // this lane's place in a transposing read: voxel row lane % 16 / 4, four channels
+    const int kq = lane >> 4, m = lane & 15;
+    const int wm = wave % WM, wn = wave / WM;
+    const u16 *xa = xs + (2 * kq * WHZ + (m >> 2)) * LX + wm * MT * 16 + (m & 3) * 4;
+    const u16 *ga = gs + (2 * kq * WZ + (m >> 2)) * LG + wn * NT * 16 + (m & 3) * 4;
+
+    load(chunk);
+    for (int t = chunk, it = 0; t < ntiles; t += nchunks, ++it) {
+        __syncthreads();  // the previous tile's reads are done
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            const int e = tid + 256 * i;
+            if (e < WHV * CX) *reinterpret_cast<uint4 *>(xs + e / CX * LX + e % CX * 8) = rx[i];
+        }
+#pragma unroll
+        for (int i = 0; i < NG; ++i) {
+            const int e = tid + 256 * i;
+            *reinterpret_cast<uint4 *>(gs + e / CG * LG + e % CG * 8) = rg[i];
+        }
+        if (bpart && it % 3 == dxi) {
+#pragma unroll
+            for (int i = 0; i < NG; ++i) {
+                const unsigned w[4] = {rg[i].x, rg[i].y, rg[i].z, rg[i].w};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    bs[2 * q] += __uint_as_float(w[q] << 16);
+                    bs[2 * q + 1] += __uint_as_float(w[q] & 0xffff0000u);
+                }
+            }
         }
         __syncthreads();
-        load(t + nchunks, cur);  // next tile in flight during the MFMAs
-        // gw[ci][co] += sum_v xs[ci][v] gs[co][v]: M = CI, N = CO, K = 128 voxels
+        load(t + nchunks);  // next tile in flight during the MFMAs
+#pragma unroll 1
+        for (int xi = 0; xi < WX; ++xi) {
+            s8 bv[2][NT];
 #pragma unroll
-        for (int ks = 0; ks < TV / 32; ++ks) {
+            for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int i = 0; i < TPW; ++i) {
-                const int tile = wave * TPW + i;
-                const int mt = tile / NT, nt = tile % NT;
-                const s8 av = *reinterpret_cast<const s8 *>(xs + (mt * 16 + (lane & 15)) * LDV + ks * 32 + 8 * kq);
-                const s8 bv = *reinterpret_cast<const s8 *>(gs + (nt * 16 + (lane & 15)) * LDV + ks * 32 + 8 * kq);
-                acc[i] = mfma_bf16(av, bv, acc[i]);
+                for (int nt = 0; nt < NT; ++nt)
+                    bv[j][nt] = read_tr(ga + (xi * WY + j) * WZ * LG + nt * 16, 4 * LG);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {  // halo row offset: y = r - 1 + 2 kq
+#pragma unroll
+                for (int dz = 0; dz < 3; ++dz) {
+                    s8 av[MT];
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        av[mt] = read_tr(xa + ((xi * WHY + r) * WHZ + dz) * LX + mt * 16, 4 * LX);
+#pragma unroll
+                    for (int dy = 0; dy < 3; ++dy) {
+                        const int j = r - dy;
+                        if (j < 0 || j > 1) continue;
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                            for (int nt = 0; nt < NT; ++nt)
+                                acc[dy * 3 + dz][mt][nt] = mfma_bf16(av[mt], bv[j][nt], acc[dy * 3 + dz][mt][nt]);
+                    }
+                }
             }
         }
     }
-    // partial[tap][chunk][ci][co]; lane holds rows ci = 16 mt + 4 kq + r, column co = 16 nt + lane % 16
-    float *pp = part + ((long long)tap * nchunks + chunk) * CI * CO;
+    // partial[chunk][tap][ci][co]; lane holds rows ci = 16 mt + 4 kq + r, column co = 16 nt + lane % 16
+    float *pp = part + ((long long)chunk * 27 + dxi * 9) * CI * CO;
 #pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-        const int tile = wave * TPW + i;
-        const int mt = tile / NT, nt = tile % NT;
+    for (int a = 0; a < 9; ++a)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) pp[(mt * 16 + 4 * kq + r) * CO + nt * 16 + (lane & 15)] = acc[i][r];
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    pp[(a * CI + (wm * MT + mt) * 16 + 4 * kq + r) * CO + (wn * NT + nt) * 16 + m] = acc[a][mt][nt][r];
+    if (bpart) {  // thread t holds channels 8 (t % CG) .. + 7
+        float *red = reinterpret_cast<float *>(xs);
+        static_assert(sizeof(xs) >= 256 * 8 * sizeof(float), "room for the sums");
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 8; ++q) red[tid * 8 + q] = bs[q];
+        __syncthreads();
+        if (tid < CO) {
+            float s = 0.0f;
+            for (int i = tid / 8; i < 256; i += CG) s += red[i * 8 + tid % 8];
+            bpart[((long long)chunk * 3 + dxi) * CO + tid] = s;
+        }
     }
 }
 
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float *__restrict__ part, int nchunks, int per_tap,
+__global__ __launch_bounds__(256) void k_wgrad_reduce(const float *__restrict__ part, int nchunks, int n,
                                                       float *__restrict__ gw)
 {
-    const int tap = blockIdx.y;
-    for (int e = blockIdx.x * 256 + threadIdx.x; e < per_tap; e += gridDim.x * 256) {
-        float s = 0.0f;
-        for (int c = 0; c < nchunks; ++c) s += part[((long long)tap * nchunks + c) * per_tap + e];
-        gw[(long long)tap * per_tap + e] = s;
-    }
-}
-
-// bias gradient, stage 1: partial[blk][co] = sum over this block's voxels of gy[v][co]
-__global__ __launch_bounds__(256) void k_bias_partial(const u16 *__restrict__ gy, long long nvox, int CO,
-                                                      float *__restrict__ partial)
-{
-    __shared__ float sh[256];
-    const int per = 256 / CO;  // voxels handled side by side
-    const int c = threadIdx.x % CO, vo = threadIdx.x / CO;
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= n) return;
     float s = 0.0f;
-    for (long long v = (long long)blockIdx.x * per + vo; v < nvox; v += (long long)gridDim.x * per)
-        s += bf2f(gy[v * CO + c]);
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    if (threadIdx.x < CO) {
-        float t = 0.0f;
-        for (int i = 0; i < per; ++i) t += sh[i * CO + threadIdx.x];
-        partial[(long long)blockIdx.x * CO + threadIdx.x] = t;
-    }
+#pragma unroll 8
+    for (int c = 0; c < nchunks; ++c) s += part[(long long)c * n + e];
+    gw[e] = s;
 }
 
-// bias gradient, stage 2: gb[co] = sum over blocks, one block per channel: thread t
+// bias gradient: gb[co] = sum over blocks, one block per channel: thread t
 // adds partials t, t + 256, ... in order, then a fixed-shape tree in LDS
 __global__ __launch_bounds__(256) void k_bias_reduce(const float *__restrict__ partial, int nblk, int CO, float *gb)
 {
@@ -496,11 +550,13 @@ hipError_t conv_dispatch(int ci, int co, const u16 *x, const void *wsw, const fl
 }
 
 template <int CI, int CO>
-hipError_t wgrad_t(const u16 *x, const u16 *gy, int N, int X, int Y, int Z, int nchunks, float *part, float *gw,
-                   hipStream_t st)
+hipError_t wgrad_t(const u16 *x, const u16 *gy, int N, int X, int Y, int Z, int nchunks, float *part, float *bpart,
+                   float *gw, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_wgrad<CI, CO>), dim3(27 * nchunks), dim3(256), 0, st, x, gy, N, X, Y, Z, nchunks, part);
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3((CI * CO + 255) / 256, 27), dim3(256), 0, st, part, nchunks, CI * CO, gw);
+    hipLaunchKernelGGL((k_wgrad<CI, CO>), dim3(3 * 8 * ((nchunks + 7) / 8)), dim3(256), 0, st, x, gy, N, X, Y, Z, nchunks,
+                       part, bpart);
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3((27 * CI * CO + 255) / 256), dim3(256), 0, st, part, nchunks, 27 * CI * CO,
+                       gw);
     return hipGetLastError();
 }
 
@@ -520,33 +576,33 @@ hipError_t net_conv(int epi, int ci, int co, const uint16_t *x, const void *wsw,
     }
 }
 
+// Chunks of voxel tiles: three blocks each, so that 168 chunks are the 504 blocks that
+// fit the chip at once (two per compute unit); at least two tiles per chunk, as each
+// writes 27 CI CO partials.
 int net_wgrad_chunks(int N, int X, int Y, int Z)
 {
-    const long long ntiles = (long long)N * ((X + TX - 1) / TX) * ((Y + TY - 1) / TY) * ((Z + TZ - 1) / TZ);
-    return (int)std::max(1LL, std::min(64LL, ntiles));
+    const long long ntiles = (long long)N * ((X + WX - 1) / WX) * ((Y + WY - 1) / WY) * ((Z + WZ - 1) / WZ);
+    return (int)std::max(1LL, std::min(168LL, (ntiles + 1) / 2));
 }
-
-constexpr int kBiasBlocks = 512;
 
 size_t net_wgrad_work_bytes(int ci, int co, int N, int X, int Y, int Z)
 {
-    return ((size_t)27 * net_wgrad_chunks(N, X, Y, Z) * ci * co + (size_t)kBiasBlocks * co) * sizeof(float);
+    return (size_t)net_wgrad_chunks(N, X, Y, Z) * (27 * ci * co + 3 * co) * sizeof(float);
 }
 
 hipError_t net_wgrad(int ci, int co, const uint16_t *x, const uint16_t *gy, int N, int X, int Y, int Z, float *work,
                      float *gw, float *gb, hipStream_t st)
 {
     const int nch = net_wgrad_chunks(N, X, Y, Z);
+    float *bp = gb ? work + (size_t)27 * nch * ci * co : nullptr;
     hipError_t e;
-    if (ci == 32 && co == 32) e = wgrad_t<32, 32>(x, gy, N, X, Y, Z, nch, work, gw, st);
-    else if (ci == 32 && co == 64) e = wgrad_t<32, 64>(x, gy, N, X, Y, Z, nch, work, gw, st);
-    else if (ci == 64 && co == 32) e = wgrad_t<64, 32>(x, gy, N, X, Y, Z, nch, work, gw, st);
-    else if (ci == 64 && co == 64) e = wgrad_t<64, 64>(x, gy, N, X, Y, Z, nch, work, gw, st);
+    if (ci == 32 && co == 32) e = wgrad_t<32, 32>(x, gy, N, X, Y, Z, nch, work, bp, gw, st);
+    else if (ci == 32 && co == 64) e = wgrad_t<32, 64>(x, gy, N, X, Y, Z, nch, work, bp, gw, st);
+    else if (ci == 64 && co == 32) e = wgrad_t<64, 32>(x, gy, N, X, Y, Z, nch, work, bp, gw, st);
+    else if (ci == 64 && co == 64) e = wgrad_t<64, 64>(x, gy, N, X, Y, Z, nch, work, bp, gw, st);
     else return hipErrorInvalidValue;
     if (e != hipSuccess || !gb) return e;
-    float *bp = work + (size_t)27 * nch * ci * co;
-    hipLaunchKernelGGL(k_bias_partial, dim3(kBiasBlocks), dim3(256), 0, st, gy, (long long)N * X * Y * Z, co, bp);
-    hipLaunchKernelGGL(k_bias_reduce, dim3(co), dim3(256), 0, st, bp, kBiasBlocks, co, gb);
+    hipLaunchKernelGGL(k_bias_reduce, dim3(co), dim3(256), 0, st, bp, 3 * nch, co, gb);
     return hipGetLastError();
 }
 
