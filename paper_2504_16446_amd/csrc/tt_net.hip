@@ -42,25 +42,37 @@ __device__ __forceinline__ u16 f2bf(float x)
 
 __device__ __forceinline__ float bf2f(u16 h) { return __uint_as_float((unsigned)h << 16); }
 
-// Spatial tile of one block: 4 (x) x 4 (y) x 8 (z) = 128 voxels, z fastest.
-constexpr int TX = 4, TY = 4, TZ = 8, TV = TX * TY * TZ;
-constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2, HV = HX * HY * HZ;
-
 enum { EPI_RELU_BF16 = 0, EPI_BIAS_F32 = 1, EPI_MASK_BF16 = 2 };
 
 // ---------------------------------------------------------------------------
-// Convolution as implicit GEMM: rows = the block's 128 voxels, columns = CO,
-// K = 27 taps x CI.  The (tile + 1)-halo of the input is staged in LDS once;
-// each tap reads it at a shifted position.  Wave w owns voxels 32w..32w+31
-// (two 16-row tiles) and all CO/16 column tiles.
+// Convolution as implicit GEMM: rows = CO, columns = the block's voxels, K = 27
+// taps x CI.  Tile: 4 (x) x TY (y) x 8 (z) voxels, wave w owning the x-slice w.  The
+// (tile + 1)-halo of the input is staged in LDS once, as it is in memory; each tap
+// reads it at a shifted position.  The 16-byte octets of a voxel are rotated by the
+// voxel's index (octet ^ (p mod 8 or 4)), which spreads the reads of one octet of
+// 16 voxels over the banks without padding.
+//
+// What bounded the kernel it replaces (batch 8 x 48^3, 64 -> 64: 280 us, MFMAs busy
+// 29%): each wave read a weight fragment right before its use, from L2 (all fragments
+// are 27 CI CO shorts, more than L1 holds), the halo's loads were waited for one by
+// one, and its stores were two bytes a lane.  Now the weights come two steps ahead, a
+// fragment serves VT = TY / 2 column tiles (64 voxels a wave instead of 32), ten halo
+// loads of a thread are in flight together, and a lane stores four channels.  TY = 8
+// where there are blocks enough to fill the chip, TY = 4 for smaller volumes.
+// Forward / input gradient, batch 8 x 48^3, before -> now: 64 -> 64 280 -> 235 / 319 ->
+// 242 us (834 / 808 TFLOP/s; a large bf16 matrix product reaches 1130 here), 32 -> 64
+// 149 -> 116 / 210 -> 144, 64 -> 32 191 -> 141 / 165 -> 138, 32 -> 32 84 -> 63 / 92 -> 73;
+// batch 1, 64 -> 64 48 -> 35 / 55 -> 37.
 // ---------------------------------------------------------------------------
-template <int CI, int CO, int EPI>
-__global__ __launch_bounds__(256) void k_conv(const u16 *__restrict__ x, const s8 *__restrict__ wsw,
+template <int CI, int CO, int EPI, int TY>
+__global__ __launch_bounds__(256, 2) void k_conv(const u16 *__restrict__ x, const s8 *__restrict__ wsw,
                                               const float *__restrict__ bias, const u16 *__restrict__ mask,
                                               void *__restrict__ y, int X, int Y, int Z)
 {
-    constexpr int LD = CI + 8;  // padded channel stride of the halo (bf16)
-    __shared__ u16 halo[HV * LD];
+    constexpr int TX = 4, TZ = 8, HY = TY + 2, HZ = TZ + 2, HV = (TX + 2) * HY * HZ;
+    constexpr int CH = CI / 8;                   // 16-byte octets per voxel
+    constexpr int VT = TY / 2, NT = CO / 16, CB = CI / 32;
+    __shared__ uint4 halo[HV * CH];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nbz = (Z + TZ - 1) / TZ, nby = (Y + TY - 1) / TY, nbx = (X + TX - 1) / TX;
     int b = blockIdx.x;
@@ -73,73 +85,93 @@ __global__ __launch_bounds__(256) void k_conv(const u16 *__restrict__ x, const s
     const int x0 = bx * TX - 1, y0 = by * TY - 1, z0 = bz * TZ - 1;
     const long long vol = (long long)X * Y * Z;
     const u16 *xn = x + (long long)n * vol * CI;
-    // stage the halo: 16-byte chunks of 8 channels
-    constexpr int CH = CI / 8;
-    for (int e = tid; e < HV * CH; e += 256) {
-        const int p = e / CH, ch = e % CH;
-        const int hz = p % HZ, hy = (p / HZ) % HY, hx = p / (HZ * HY);
-        const int gx = x0 + hx, gy = y0 + hy, gz = z0 + hz;
-        uint4 val = make_uint4(0, 0, 0, 0);
-        if (gx >= 0 && gx < X && gy >= 0 && gy < Y && gz >= 0 && gz < Z)
-            val = *reinterpret_cast<const uint4 *>(xn + (((long long)gx * Y + gy) * Z + gz) * CI + ch * 8);
-        *reinterpret_cast<uint4 *>(halo + p * LD + ch * 8) = val;
-    }
-    __syncthreads();
-
-    constexpr int NT = CO / 16, CB = CI / 32;
-    f4 acc[2][NT];
+    // the halo's octets, ten loads of a thread in flight together (outside the volume
+    // they read the image's first voxel and store zero)
+    constexpr int NH = (HV * CH + 255) / 256;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+    for (int i0 = 0; i0 < NH; i0 += 10) {
+        uint4 r[10];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f4{0.f, 0.f, 0.f, 0.f};
-    // the two voxel rows this lane supplies to the A operand
-    int hp[2];
+        for (int i = i0; i < min(i0 + 10, NH); ++i) {
+            const int e = min(tid + 256 * i, HV * CH - 1), p = e / CH;
+            const int hz = p % HZ, hy = (p / HZ) % HY, hx = p / (HZ * HY);
+            const int gx = x0 + hx, gy = y0 + hy, gz = z0 + hz;
+            const bool in = (unsigned)gx < (unsigned)X && (unsigned)gy < (unsigned)Y && (unsigned)gz < (unsigned)Z;
+            const uint4 v = *reinterpret_cast<const uint4 *>(
+                xn + (in ? (((long long)gx * Y + gy) * Z + gz) * CI + e % CH * 8 : 0LL));
+            r[i - i0] = in ? v : make_uint4(0, 0, 0, 0);
+        }
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-        const int vt = wave * 32 + mt * 16 + (lane & 15);
-        const int tz = vt % TZ, ty = (vt / TZ) % TY, tx = vt / (TZ * TY);
-        hp[mt] = (tx * HY + ty) * HZ + tz;
-    }
-    const int kq = lane >> 4;
-    for (int tap = 0; tap < 27; ++tap) {
-        const int dx = tap / 9, dy = (tap / 3) % 3, dz = tap % 3;
-        const int toff = (dx * HY + dy) * HZ + dz;
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-            s8 bv[NT];
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) bv[nt] = wsw[((tap * CB + cb) * NT + nt) * 64 + lane];
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt) {
-                const s8 av = *reinterpret_cast<const s8 *>(halo + (hp[mt] + toff) * LD + cb * 32 + 8 * kq);
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = mfma_bf16(av, bv[nt], acc[mt][nt]);
-            }
+        for (int i = i0; i < min(i0 + 10, NH); ++i) {
+            const int e = tid + 256 * i, p = e / CH;
+            if (e < HV * CH) halo[p * CH + ((e % CH) ^ (p & (CH - 1)))] = r[i - i0];
         }
     }
-    // epilogue: lane holds rows (voxels) 16 mt + 4 kq + r of column (channel) 16 nt + lane % 16
+    // weight fragments of step (tap, cb), two steps ahead of the MFMAs
+    const int kq = lane >> 4, m = lane & 15;
+    const s8 *wp = wsw + lane;
+    s8 wv[3][NT];
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int vt = wave * 32 + mt * 16 + 4 * kq + r;
-            const int tz = vt % TZ, ty = (vt / TZ) % TY, tx = vt / (TZ * TY);
-            const int gx = x0 + 1 + tx, gy = y0 + 1 + ty, gz = z0 + 1 + tz;
-            if (gx >= X || gy >= Y || gz >= Z) continue;
-            const long long vi = (long long)n * vol + ((long long)gx * Y + gy) * Z + gz;
+        for (int nt = 0; nt < NT; ++nt) wv[i][nt] = wp[(i * NT + nt) * 64];
+    __syncthreads();
+
+    f4 acc[VT][NT];
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const int co = nt * 16 + (lane & 15);
-                float v = acc[mt][nt][r];
+    for (int vt = 0; vt < VT; ++vt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[vt][nt] = f4{0.f, 0.f, 0.f, 0.f};
+    // the voxel this lane supplies to column tile vt: y = 2 vt + m / 8, z = m % 8 of slice `wave`
+    int row = (wave * HY + (m >> 3)) * HZ + (m & 7);
+    constexpr int STEPS = 27 * CB;
+    for (int xy = 0; xy < 9; ++xy) {
+#pragma unroll
+        for (int i = 0; i < 3 * CB; ++i) {  // dz, cb
+            const int dz = i / CB, cb = i % CB;
+            const int ahead = min(xy * 3 * CB + i + 2, STEPS - 1);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) wv[(i + 2) % 3][nt] = wp[(ahead * NT + nt) * 64];
+#pragma unroll
+            for (int vt = 0; vt < VT; ++vt) {
+                const int p = row + dz + vt * 2 * HZ;
+                const s8 xv = __builtin_bit_cast(s8, halo[p * CH + ((cb * 4 + kq) ^ (p & (CH - 1)))]);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) acc[vt][nt] = mfma_bf16(wv[i % 3][nt], xv, acc[vt][nt]);
+            }
+        }
+        row += xy % 3 == 2 ? (HY - 2) * HZ : HZ;  // the next (dx, dy)
+    }
+    // epilogue: lane holds channels 16 nt + 4 kq + r of voxel column m: four channels a store
+    const int gx = x0 + 1 + wave, gz = z0 + 1 + (m & 7);
+#pragma unroll
+    for (int vt = 0; vt < VT; ++vt) {
+        const int gy = y0 + 1 + 2 * vt + (m >> 3);
+        if (gx >= X || gy >= Y || gz >= Z) continue;
+        const long long vi = (long long)n * vol + ((long long)gx * Y + gy) * Z + gz;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int co = nt * 16 + 4 * kq;
+            f4 v = acc[vt][nt];
+            if (EPI == EPI_MASK_BF16) {
+                const uint2 k = *reinterpret_cast<const uint2 *>(mask + vi * CO + co);
+                v[0] = __uint_as_float(k.x << 16) > 0.0f ? v[0] : 0.0f;
+                v[1] = __uint_as_float(k.x & 0xffff0000u) > 0.0f ? v[1] : 0.0f;
+                v[2] = __uint_as_float(k.y << 16) > 0.0f ? v[2] : 0.0f;
+                v[3] = __uint_as_float(k.y & 0xffff0000u) > 0.0f ? v[3] : 0.0f;
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] += bias[co + r];
+            }
+            if (EPI == EPI_BIAS_F32) {
+                *reinterpret_cast<f4 *>(reinterpret_cast<float *>(y) + vi * CO + co) = v;
+            } else {
                 if (EPI == EPI_RELU_BF16) {
-                    v = fmaxf(v + bias[co], 0.0f);
-                    reinterpret_cast<u16 *>(y)[vi * CO + co] = f2bf(v);
-                } else if (EPI == EPI_BIAS_F32) {
-                    reinterpret_cast<float *>(y)[vi * CO + co] = v + bias[co];
-                } else {
-                    v = bf2f(mask[vi * CO + co]) > 0.0f ? v : 0.0f;
-                    reinterpret_cast<u16 *>(y)[vi * CO + co] = f2bf(v);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.0f);
                 }
+                const unsigned lo = f2bf(v[0]) | (unsigned)f2bf(v[1]) << 16, hi = f2bf(v[2]) | (unsigned)f2bf(v[3]) << 16;
+                *reinterpret_cast<uint2 *>(reinterpret_cast<u16 *>(y) + vi * CO + co) = make_uint2(lo, hi);
             }
         }
     }
@@ -162,12 +194,9 @@ __global__ __launch_bounds__(256) void k_conv(const u16 *__restrict__ x, const s
 // 12 x fragments per x-slice serve 18 (j, tap) products.  The next tile's loads are
 // in flight during the MFMAs.
 //
-// Measured, with gb (batch 8 x 48^3): 64 -> 64 channels 829 -> 214 us (236 -> 913
-// TFLOP/s), 32 -> 64 672 -> 138, 64 -> 32 609 -> 132, 32 -> 32 434 -> 108; batch 1,
-// 64 -> 64 140 -> 53.  The kernel it replaces ran one tap per block: 27 reads of x and
-// gy, and an 8 x 8 register transpose per staged octet.  Now the MFMAs (16 cycles
-// each, two waves per SIMD) and the 110 KiB of partials per chunk and dx (1 KiB per
-// output tile: at batch 1 half of the time) bound it.
+// What bounded the kernel it replaces (one tap per block): 27 reads of x and gy and
+// an 8 x 8 register transpose per staged octet, MFMAs 4-8% of the time.  Layer
+// 64 -> 64 at batch 8 x 48^3: see net_wgrad.
 //
 // gb: each tile's gy is summed, as it is staged, by one of its three blocks.
 // ---------------------------------------------------------------------------
@@ -528,13 +557,20 @@ __global__ __launch_bounds__(256) void k_tile_blend(const float *__restrict__ y,
 
 int grid_for(long long n) { return (int)min((n + 255) / 256, 8192LL); }
 
+// Blocks of the 4 x 8 x 8-voxel tile below which the 4 x 4 x 8 one is used: one per
+// compute unit.
+constexpr int kConvWideBlocks = 256;
+
 template <int CI, int CO, int EPI>
 hipError_t conv_t(const u16 *x, const void *wsw, const float *bias, const u16 *mask, void *y, int N, int X, int Y, int Z,
                   hipStream_t st)
 {
-    const int nb = N * ((X + TX - 1) / TX) * ((Y + TY - 1) / TY) * ((Z + TZ - 1) / TZ);
-    hipLaunchKernelGGL((k_conv<CI, CO, EPI>), dim3(nb), dim3(256), 0, st, x, reinterpret_cast<const s8 *>(wsw), bias,
-                       mask, y, X, Y, Z);
+    auto blocks = [&](int ty) { return N * ((X + 3) / 4) * ((Y + ty - 1) / ty) * ((Z + 7) / 8); };
+    const s8 *w = reinterpret_cast<const s8 *>(wsw);
+    if (blocks(8) >= kConvWideBlocks)
+        hipLaunchKernelGGL((k_conv<CI, CO, EPI, 8>), dim3(blocks(8)), dim3(256), 0, st, x, w, bias, mask, y, X, Y, Z);
+    else
+        hipLaunchKernelGGL((k_conv<CI, CO, EPI, 4>), dim3(blocks(4)), dim3(256), 0, st, x, w, bias, mask, y, X, Y, Z);
     return hipGetLastError();
 }
 
