@@ -394,6 +394,7 @@ int tt_create(const tt_geometry *geom, tt_ctx **out)
     // blocks per CU), 76 KiB for more (two blocks per CU); measured best of
     // 20-76 KiB on 100^3 x 4 and of 32-76 KiB on 128^3 and 256^3 x 8
     d.march_lds = plan_slabs(c->frames, d.Up, (d.Up == 4 ? 52 : 76) * 1024);
+    plan_rings(c->frames, g, d.Up, d.ring_lds, d.ring_all);
     plan_adjoint(c->frames, d);
 
     if (hipGetDevice(&c->device) != hipSuccess) {

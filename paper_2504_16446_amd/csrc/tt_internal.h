@@ -53,6 +53,13 @@ struct ProjFrame {
     // voxels that contains every corner those samples touch.  slab_w = 0:
     // the projection's rays gather from global memory instead.
     int slab_a, slab_w, slab_eb, slab_ez;
+    // Ring plan of the march over single planes of axis slab_a: ring_r planes are
+    // kept (0: the projection runs on the slab plan), each a box of ring_eb x ring_ez
+    // voxels that contains every corner which the tile's samples within one plane
+    // of it touch.
+    // The projections are launched in classes of LDS size (ring_c), smaller rings
+    // leaving room for more blocks per compute unit.
+    int ring_r, ring_eb, ring_ez, ring_c;
     // Joseph's method: dominant axis A of d (ties within 1e-9 go to the lower
     // axis) and the cut weight 1/|d_A|; for the adjoint, the in-plane offset of
     // a ray's cut from a voxel centre in the voxel's layer is
@@ -70,6 +77,7 @@ struct ProjFrame {
 };
 
 constexpr int kMarchTile = 16;  // rays per tile edge in the forward march
+constexpr int kRingClasses = 2;  // LDS sizes of the ring march
 
 int num_coeffs(int ell_max);
 void sh_eval_one(int ell_max, const double *dir, double *out);
@@ -77,6 +85,9 @@ void build_frames(const Geometry &g, std::vector<ProjFrame> &frames, std::vector
 // Fills the slab plan of every frame for staged voxels of `up` floats within
 // `lds_budget` bytes; returns the largest staging size in bytes (0 if none).
 int plan_slabs(std::vector<ProjFrame> &frames, int up, int lds_budget);
+// Fills the ring plan (after plan_slabs) for up <= 8, the dynamic LDS bytes of each
+// class (0: empty), and in `all` whether every projection has a ring.
+void plan_rings(std::vector<ProjFrame> &frames, const Geometry &g, int up, int *lds, int &all);
 
 // ---------------------------------------------------------------------------
 // Kernel launchers (tt_proj.hip, tt_vec.hip).  All asynchronous on `st`.
@@ -95,7 +106,8 @@ struct Dims {
     int S, nj, nk;      // projections and detector
     int nseg, U, Up;    // segments, unique segments, padded unique segments
     float step;         // sample spacing of the trilinear model (1 for Joseph: no step factor)
-    int march_lds;      // dynamic LDS bytes of the staged march (0: no projection staged)
+    int march_lds;      // dynamic LDS bytes of the slab march (0: no projection staged)
+    int ring_lds[kRingClasses], ring_all;  // dynamic LDS bytes of the ring march's classes (0: empty); 1: it runs every projection
     int joseph;         // 0: unit-step trilinear samples, 1: Joseph's method
     int inv_pair;       // 1: point-inversion-symmetric geometry (no detector offsets, even nx): the
                         //    adjoint (either model) enumerates each voxel pair (v, -v) once

@@ -682,6 +682,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((UP == 4 &&
     const int k = tk * kMarchTile + (threadIdx.x / kMarchTile);
     const bool live = j < nj && k < nk;
     const ProjFrame &f = frames[s];
+    if (!FUSED && f.ring_r > 0) return;  // this projection runs in k_march_ring
     const float *Mp = FUSED ? M : M + (long long)p * vol_pad * UP;
     int2 *tab = reinterpret_cast<int2 *>(lds);
     int *gch = reinterpret_cast<int *>(lds + (UP * kk * 8 + 15) / 16);  // [ng] channels, then [ng][UP] constants
@@ -986,12 +987,266 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((UP == 4 &&
     }
 }
 
+// ---------------------------------------------------------------------------
+// march over a ring of staged planes (four or eight unique segments): one thread
+// per ray, block = 16 x 16 rays of one projection, as k_march, with one plane of the
+// slab axis A staged per step instead of a slab of them.
+//
+// Plane a holds the voxels that the tile's samples with index position in
+// [a - 1, a + 1) along A touch, from its own origin; a sample in [a, a + 1) reads
+// planes a and a + 1.  The ring keeps R planes: while the rays gather from a and
+// a + 1, the copies of a + 2 .. a + R - 1 are in flight, so a step waits only for a copy
+// issued R - 2 steps before.  One barrier per step: it ends the reads of plane a - 1,
+// whose slot then takes plane a + R - 1.
+//
+// What bounded the slab march: every slab waited for its own copies with nothing in
+// flight beside them (32^3, one block per compute unit: 47 of 59 us), and its staging
+// took about as many VALU instructions as the samples.  Here a thread's elements of a
+// plane are the same for all planes, so inside the volume a copy is one add.  March in ms,
+// slabs -> rings: 32^3 x 4 unique segments 0.062 -> 0.043, 100^3 x 4 1.59 -> 1.37,
+// 128^3 x 8 7.71 -> 6.38, 256^3 x 8 73.1 -> 62.1.  What bounds it now is the LDS: eight
+// corner reads of 16 bytes per sample and four segments.
+//
+// A plane's float4 halves (eight segments) lie one after the other, so that neighbouring
+// voxels are 16 bytes apart and a wave's reads spread over all banks (interleaved by
+// voxel: 256^3 63.2, 128^3 6.46 ms).
+//
+// The copies are written in assembly, because the compiler otherwise waits for all of
+// them before any LDS read (it cannot tell the slots apart); they have no register
+// output.  wait_copies is the only wait for them.
+// ---------------------------------------------------------------------------
+constexpr int kRingCopies = 8;  // copies of 64 float4 per wave and plane (at most)
+
+__device__ __forceinline__ void copy_to_lds(const void *base, unsigned off, unsigned lds_byte)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_byte), "v"(off), "s"(base)
+                 : "memory", "m0");
+}
+
+// x in 32.32 fixed point, in scalar registers
+__device__ __forceinline__ long long fixed32(double x)
+{
+    const double hi = floor(x);
+    const int h = __builtin_amdgcn_readfirstlane((int)hi);
+    const unsigned l = __builtin_amdgcn_readfirstlane((unsigned)((x - hi) * 4294967296.0));
+    return (long long)(((unsigned long long)(unsigned)h << 32) | l);
+}
+
+// waits until at most n of this wave's copies are outstanding (n uniform; more than
+// 24 as 24), and for its LDS reads
+__device__ __forceinline__ void wait_copies(int n)
+{
+    switch (n) {
+#define TT_WAIT(k) \
+    case k: asm volatile("s_waitcnt vmcnt(" #k ") lgkmcnt(0)" ::: "memory"); break;
+        TT_WAIT(0) TT_WAIT(1) TT_WAIT(2) TT_WAIT(3) TT_WAIT(4) TT_WAIT(5) TT_WAIT(6) TT_WAIT(7) TT_WAIT(8)
+        TT_WAIT(9) TT_WAIT(10) TT_WAIT(11) TT_WAIT(12) TT_WAIT(13) TT_WAIT(14) TT_WAIT(15) TT_WAIT(16)
+        TT_WAIT(17) TT_WAIT(18) TT_WAIT(19) TT_WAIT(20) TT_WAIT(21) TT_WAIT(22) TT_WAIT(23)
+#undef TT_WAIT
+    default: asm volatile("s_waitcnt vmcnt(24) lgkmcnt(0)" ::: "memory"); break;
+    }
+}
+
+template <int UP>
+__global__ __launch_bounds__(256) void k_march_ring(const float *__restrict__ M, const ProjFrame *__restrict__ frames,
+                                                    int s0, int nx, int ny, int nz, int nj, int nk, int nseg, int U,
+                                                    float step, long long vol_pad, float *__restrict__ I, int jos,
+                                                    int cls)
+{
+    constexpr int Q = UP / 4;
+    extern __shared__ f4 ring[];  // [R][Q][plane voxel]
+    __shared__ int arange[2];
+    const int ntj = (nj + kMarchTile - 1) / kMarchTile, ntk = (nk + kMarchTile - 1) / kMarchTile;
+    const int lb = blockIdx.x;
+    const int p = lb / (ntj * ntk), s = s0 + p;
+    const ProjFrame &f = frames[s];
+    const int R = f.ring_r;
+    if (R == 0 || f.ring_c != cls) return;  // this projection runs in k_march, or in the launch of its class
+    const int tj = (lb / ntk) % ntj, tk = lb % ntk;
+    const int j = tj * kMarchTile + (threadIdx.x % kMarchTile);
+    const int k = tk * kMarchTile + (threadIdx.x / kMarchTile);
+    const bool live = j < nj && k < nk;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    double b[3], ds[3];
+    int n0 = 0, n1 = -1;
+    if (live) ray_setup(f, j, k, nx, ny, nz, step, b, ds, n0, n1, jos != 0);
+    float acc[UP];
+#pragma unroll
+    for (int u = 0; u < UP; ++u) acc[u] = 0.0f;
+
+    const int A = f.slab_a, B = 1 - A, EB = f.ring_eb, EZ = f.ring_ez;
+    const bool fwd = f.d[A] > 0.0;  // samples are visited in increasing index coordinate along A
+    int left = n1 - n0 + 1;         // samples still to visit
+    if (threadIdx.x == 0) {
+        arange[0] = INT_MAX;
+        arange[1] = INT_MIN;
+    }
+    __syncthreads();
+    if (left > 0) {
+        const int nf = fwd ? n0 : n1, nl = fwd ? n1 : n0;
+        atomicMin(&arange[0], (int)floor(fma((double)nf, A ? ds[1] : ds[0], A ? b[1] : b[0])));
+        atomicMax(&arange[1], (int)floor(fma((double)nl, A ? ds[1] : ds[0], A ? b[1] : b[0])));
+    }
+    __syncthreads();
+    const int amin = __builtin_amdgcn_readfirstlane(arange[0]), amax = __builtin_amdgcn_readfirstlane(arange[1]);
+    if (amin <= amax) {
+        // Origin of plane a: the lowest position along B and z of the tile's rays
+        // between planes a - 1 and a + 1, kb + a rB and kz + a rZ (affine in a)
+        const double n3[3] = {(double)nx, (double)ny, (double)nz};
+        double b00[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+            b00[q] = f.o[q] + (tj * kMarchTile) * f.ej[q] + (tk * kMarchTile) * f.ek[q] + 0.5 * (n3[q] + 1.0);
+        const double rB = f.d[B] * f.inv_d[A], rZ = f.d[2] * f.inv_d[A];
+        double kb = 1e300, kz = 1e300;
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            const double J = (v & 1) ? kMarchTile - 1 : 0.0, K = (v & 2) ? kMarchTile - 1 : 0.0, P = (v & 4) ? 1.0 : -1.0;
+            const double t = P - (b00[A] + J * f.ej[A] + K * f.ek[A]);
+            kb = fmin(kb, b00[B] + J * f.ej[B] + K * f.ek[B] + t * rB);
+            kz = fmin(kz, b00[2] + J * f.ej[2] + K * f.ek[2] + t * rZ);
+        }
+        // in fixed point, stepped from plane to plane by scalar adds (off by 2^-32 per
+        // plane at most, within the 1e-6 that the origin is lowered by)
+        const long long rBf = fixed32(rB), rZf = fixed32(rZ);
+        long long gB = fixed32(fma((double)amin, rB, kb - 1e-6)), gZ = fixed32(fma((double)amin, rZ, kz - 1e-6));
+        long long tB = gB, tZ = gZ;  // of the next plane to stage; gB, gZ of the plane gathered from
+        // M strides (in voxels) of the plane's axes; z is contiguous
+        const int sy = nz + 2, sx = (ny + 2) * sy;
+        const int sA = A == 0 ? sx : sy, sB = A == 0 ? sy : sx;
+        const int nAp = (A == 0 ? nx : ny) + 1, nBp = (A == 0 ? ny : nx) + 1, nZp = nz + 1;
+        // this lane's elements of a plane: wave w copies elements 256 i + 64 w + lane;
+        // byte offset from the plane's origin, and (row, z) for planes that leave the volume
+        const int nel = EB * EZ * Q, nch = (nel + 63) >> 6, slot_bytes = nch * 1024;
+        const int ncp = (nch - wave + 3) >> 2;  // copies of this wave per plane
+        unsigned off[kRingCopies], rz[kRingCopies];
+#pragma unroll
+        for (int i = 0; i < kRingCopies; ++i) {
+            const int e = min(256 * i + 64 * wave + lane, nel - 1);
+            const int qe = Q == 2 && e >= EB * EZ ? 1 : 0, vox = e - qe * EB * EZ;
+            const int ib = vox / EZ, iz = vox - ib * EZ;
+            off[i] = (unsigned)((ib * sB + iz) * Q + qe) * 16u;
+            rz[i] = (unsigned)(ib << 16 | iz << 4 | qe);
+        }
+        const char *Mp = reinterpret_cast<const char *>(M) + (long long)p * vol_pad * UP * 4;
+        const unsigned ring0 = __builtin_amdgcn_readfirstlane(
+            (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)ring + wave * 1024);
+        auto stage = [&](int a, int slot) {
+            const int B0 = (int)(tB >> 32), Z0 = (int)(tZ >> 32);
+            tB += rBf;
+            tZ += rZf;
+            const unsigned dst = ring0 + slot * slot_bytes;
+            if (a >= 0 && a <= nAp && B0 >= 0 && B0 + EB - 1 <= nBp && Z0 >= 0 && Z0 + EZ - 1 <= nZp) {
+                const char *src = Mp + ((long long)a * sA + (long long)B0 * sB + Z0) * (Q * 16);
+#pragma unroll
+                for (int i = 0; i < kRingCopies; ++i)
+                    if (i < ncp) copy_to_lds(src, off[i], dst + i * 4096);
+            } else {  // voxels outside the padded volume copy one of its border, which is zero
+                const char *src = Mp + (long long)min(max(a, 0), nAp) * sA * (Q * 16);
+#pragma unroll
+                for (int i = 0; i < kRingCopies; ++i)
+                    if (i < ncp) {
+                        const int vb = min(max(B0 + (int)(rz[i] >> 16), 0), nBp);
+                        const int vz = min(max(Z0 + (int)(rz[i] >> 4 & 0xfff), 0), nZp);
+                        copy_to_lds(src, (unsigned)((vb * sB + vz) * Q + (int)(rz[i] & 15)) * 16u, dst + i * 4096);
+                    }
+            }
+        };
+        // current sample's index position (float64: sums of up to the ray's length)
+        double pA, pB, pZ;
+        const double dA = fwd ? (A ? ds[1] : ds[0]) : -(A ? ds[1] : ds[0]);
+        const double dB = fwd ? (A ? ds[0] : ds[1]) : -(A ? ds[0] : ds[1]), dZ = fwd ? ds[2] : -ds[2];
+        {
+            const double m0 = (double)(fwd ? n0 : n1);
+            pA = fma(m0, A ? ds[1] : ds[0], A ? b[1] : b[0]);
+            pB = fma(m0, A ? ds[0] : ds[1], A ? b[0] : b[1]);
+            pZ = fma(m0, ds[2], b[2]);
+        }
+        const float bmax = (float)(EB - 2), zmax = (float)(EZ - 2);
+        const int row_bytes = EZ * 16, q_f4 = EB * EZ;
+
+        const int last = amax + 1;  // last plane needed
+        int issued = amin - 1;      // last plane whose copies are issued
+        for (int i = 0; i < R - 1 && issued < last; ++i) {
+            ++issued;
+            stage(issued, i);
+        }
+        int slot = 0;
+        for (int a = amin; a <= amax; ++a) {
+            wait_copies(max(0, issued - (a + 1)) * ncp);
+            __builtin_amdgcn_s_barrier();  // planes a, a + 1 are staged; plane a - 1 is read
+            asm volatile("" ::: "memory");
+            const int nslot = slot + 1 == R ? 0 : slot + 1;
+            if (issued < last) {
+                ++issued;
+                stage(issued, slot == 0 ? R - 1 : slot - 1);
+            }
+            const int B0 = (int)(gB >> 32), Z0 = (int)(gZ >> 32);
+            gB += rBf;
+            gZ += rZf;
+            const int B1 = (int)(gB >> 32), Z1 = (int)(gZ >> 32);
+            // bytes from a voxel of plane a to the same (B, z) in plane a + 1
+            const int up = (nslot - slot) * slot_bytes + ((B0 - B1) * EZ + Z0 - Z1) * 16;
+            const char *pl = reinterpret_cast<const char *>(ring) + slot * slot_bytes;
+            // (the last step takes what is left, also where the summed position of a
+            // last sample is rounded to the far side of its plane)
+            const double aend = a == amax ? 1e300 : (double)(a + 1);
+            while (left > 0 && pA < aend) {
+                // the cell is clamped into the plane's box and the fractions are taken
+                // against the clamped cell (float32 may round a position up to a face)
+                const float fa = (float)(pA - (double)a), pb = (float)(pB - (double)B0), pz = (float)(pZ - (double)Z0);
+                const float lbb = fminf(fmaxf(floorf(pb), 0.0f), bmax), lz = fminf(fmaxf(floorf(pz), 0.0f), zmax);
+                const float fb = pb - lbb, fz = pz - lz;
+                const float ga_ = 1.0f - fa, gb_ = 1.0f - fb, gz_ = 1.0f - fz;
+                const float w00 = ga_ * gb_, w01 = ga_ * fb, w10 = fa * gb_, w11 = fa * fb;
+                const float w[8] = {w00 * gz_, w00 * fz, w01 * gz_, w01 * fz, w10 * gz_, w10 * fz, w11 * gz_, w11 * fz};
+                const char *c0 = pl + (__umul24((int)lbb, EZ) + (int)lz) * 16;
+                const f4 *cell[4] = {reinterpret_cast<const f4 *>(c0), reinterpret_cast<const f4 *>(c0 + row_bytes),
+                                     reinterpret_cast<const f4 *>(c0 + up),
+                                     reinterpret_cast<const f4 *>(c0 + up + row_bytes)};
+#pragma unroll
+                for (int cc = 0; cc < 8; ++cc) {
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) {
+                        const f4 mv = cell[cc >> 1][(cc & 1) + q * q_f4];
+                        acc[4 * q + 0] = fmaf(w[cc], mv.x, acc[4 * q + 0]);
+                        acc[4 * q + 1] = fmaf(w[cc], mv.y, acc[4 * q + 1]);
+                        acc[4 * q + 2] = fmaf(w[cc], mv.z, acc[4 * q + 2]);
+                        acc[4 * q + 3] = fmaf(w[cc], mv.w, acc[4 * q + 3]);
+                    }
+                }
+                pA += dA;
+                pB += dB;
+                pZ += dZ;
+                --left;
+            }
+            slot = nslot;
+        }
+    }
+    if (!live) return;
+    const float wgt = jos ? f.jos_w : step;  // Joseph: each cut weighs 1 / |d_A|
+    float *out = I + (((long long)s * nj + j) * nk + k) * nseg;
+#pragma unroll
+    for (int u = 0; u < UP; ++u) {
+        if (u < U) {
+            for (int cseg = u; cseg < nseg; cseg += U) out[cseg] = wgt * acc[u];
+        }
+    }
+}
+
 template <int UP>
 static hipError_t march_t(const Dims &d, const ProjFrame *frames, const float *M, int s0, int np, float *I,
                           hipStream_t st)
 {
     const long long vol_pad = (long long)(d.nx + 2) * (d.ny + 2) * (d.nz + 2);
     dim3 grid(((d.nk + kMarchTile - 1) / kMarchTile) * ((d.nj + kMarchTile - 1) / kMarchTile) * np);
+    if constexpr (UP <= 8) {
+        for (int c = 0; c < kRingClasses; ++c)
+            if (d.ring_lds[c] > 0)
+                hipLaunchKernelGGL((k_march_ring<UP>), grid, dim3(kMarchTile * kMarchTile), d.ring_lds[c], st, M, frames, s0,
+                                   d.nx, d.ny, d.nz, d.nj, d.nk, d.nseg, d.U, d.step, vol_pad, I, d.joseph, c);
+        if (d.ring_all) return hipGetLastError();
+    }
     hipLaunchKernelGGL((k_march<UP, false>), grid, dim3(kMarchTile * kMarchTile), d.march_lds, st, M, frames, s0,
                        d.nx, d.ny, d.nz, d.nj, d.nk, d.nseg, d.U, d.step, vol_pad, I, nullptr, 0, 0, nullptr, nullptr, 0,
                        d.joseph);
