@@ -51,18 +51,18 @@ def test_adjoint_matches_the_oracle(name, offsets, n_seg, model):
 @pytest.mark.parametrize("n_seg", [8, 16])
 def test_a_workspace_without_room_for_splits_still_works(n_seg):
     # 129 projections of a small volume are split over blocks, each with a coefficient
-    # volume of scratch at the end of the workspace; one volume less, and the adjoint
-    # runs unsplit: the same sum in another order
+    # volume of scratch at the end of the workspace; one volume less beside the smallest
+    # forward batch, and the adjoint runs unsplit: the same sum in another order
     import ctypes as C
 
     from paper_2504_16446_amd._lib import call
     inner, outer = tilted_angles(43, (0.0, 27.0, 45.0), span_deg=360.0)
     og = oracle.Geometry((8, 9, 10), 4, inner, outer, 11, 12, n_seg, synth.lab_frame())
-    P = gpu_projector(og, device="cuda:0", forward_batch=16)
+    P = gpu_projector(og, device="cuda:0", forward_batch=1)
     y = torch.from_numpy(np.random.default_rng(5).standard_normal(og.data_shape).astype(np.float32)).cuda()
     split = P.adjoint(y)
     volume = split.numel() * 4
-    assert call("tt_workspace_bytes", P._h, 16) == P.work_bytes
+    assert call("tt_workspace_bytes", P._h, 1) == P.work_bytes
     call("tt_set_workspace", P._h, C.c_void_p(P._ws.data_ptr()), P.work_bytes - volume)
     whole = P.adjoint(y)
     assert rel_l2(whole.cpu().numpy(), split.cpu().numpy()) <= TOL
