@@ -186,7 +186,9 @@ int tt_sizes(const tt_ctx *ctx, int64_t *out8);
  * forward_batch <= 0 gives the workspace without mapped volumes, which serves
  * only the fused forward of tt_set_sparse_map; with a sparse map of at most 32
  * kept basis functions per projection the workspace also holds a
- * channel-major copy of c, nx ny nz C floats).
+ * channel-major copy of c, nx ny nz C floats; where the adjoint of a small
+ * volume is split over the projections, also the splits' sums, up to eight
+ * times nx ny nz C floats, without which it runs unsplit).
  * tt_set_workspace attaches caller memory (device, 256-byte aligned) and
  * picks the largest batch that fits; TT_EINVAL below the smallest size (with
  * a sparse map set, below the size without mapped volumes).  The
