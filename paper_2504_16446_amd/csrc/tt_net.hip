@@ -591,6 +591,7 @@ hipError_t wgrad_t(const u16 *x, const u16 *gy, int N, int X, int Y, int Z, int 
 {
     hipLaunchKernelGGL((k_wgrad<CI, CO>), dim3(3 * 8 * ((nchunks + 7) / 8)), dim3(256), 0, st, x, gy, N, X, Y, Z, nchunks,
                        part, bpart);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     hipLaunchKernelGGL(k_wgrad_reduce, dim3((27 * CI * CO + 255) / 256), dim3(256), 0, st, part, nchunks, 27 * CI * CO,
                        gw);
     return hipGetLastError();

@@ -1242,10 +1242,12 @@ static hipError_t march_t(const Dims &d, const ProjFrame *frames, const float *M
     dim3 grid(((d.nk + kMarchTile - 1) / kMarchTile) * ((d.nj + kMarchTile - 1) / kMarchTile) * np);
     if constexpr (UP <= 8) {
         for (int c = 0; c < kRingClasses; ++c)
-            if (d.ring_lds[c] > 0)
+            if (d.ring_lds[c] > 0) {
                 hipLaunchKernelGGL((k_march_ring<UP>), grid, dim3(kMarchTile * kMarchTile), d.ring_lds[c], st, M, frames, s0,
                                    d.nx, d.ny, d.nz, d.nj, d.nk, d.nseg, d.U, d.step, vol_pad, I, d.joseph, c);
-        if (d.ring_all) return hipGetLastError();
+                if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+            }
+        if (d.ring_all) return hipSuccess;
     }
     hipLaunchKernelGGL((k_march<UP, false>), grid, dim3(kMarchTile * kMarchTile), d.march_lds, st, M, frames, s0,
                        d.nx, d.ny, d.nz, d.nj, d.nk, d.nseg, d.U, d.step, vol_pad, I, nullptr, 0, 0, nullptr, nullptr, 0,
@@ -1304,11 +1306,13 @@ hipError_t launch_march_fused(const Dims &d, const ProjFrame *frames, const floa
 {
     if (d.sparse_k < 1) return hipErrorInvalidValue;
     const long long V = (long long)d.nx * d.ny * d.nz;
-    if (d.sparse_cm)
+    if (d.sparse_cm) {
         hipLaunchKernelGGL(k_channel_major, dim3((unsigned)std::min<long long>((V + 63) / 64, 4096)), dim3(256),
                            64 * (d.C + 1) * sizeof(float), st, c, V, d.C, cT);
-    else
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    } else {
         cT = nullptr;  // stage from the coefficient records
+    }
     switch (d.Up) {
     case 4: return march_fused_t<4>(d, frames, c, sp, cT, gtab, I, st);
     case 8: return march_fused_t<8>(d, frames, c, sp, cT, gtab, I, st);
@@ -2232,8 +2236,8 @@ int backproject_blocks(const Dims &d)
 int backproject_blocks_max(const Dims &d) { return std::max(win_blocks(d, true), win_blocks(d, false)); }
 
 template <int UP, int MT, bool BF16, bool JOS>
-static void bp_launch(const Dims &d, const ProjFrame *frames, const float *yf, const AdjointTables &t, float *split,
-                      float *g, float beta, const float *c, double *partials, hipStream_t st)
+static hipError_t bp_launch(const Dims &d, const ProjFrame *frames, const float *yf, const AdjointTables &t,
+                            float *split, float *g, float beta, const float *c, double *partials, hipStream_t st)
 {
     const AdjointPlan &p = d.adj[JOS];
     const int nb = backproject_blocks(d);
@@ -2252,30 +2256,27 @@ static void bp_launch(const Dims &d, const ProjFrame *frames, const float *yf, c
                 launch(k_backproject_win<UP, MT, BF16, JOS, true>);
             else
                 launch(k_backproject_win<UP, MT, BF16, JOS, false>);
-            if (sp)
-                hipLaunchKernelGGL(k_add_splits, dim3(nb), dim3(256), 0, st, sp, (int)grid.y,
-                                   (long long)d.nx * d.ny * d.nz * d.C, g, beta, c, partials);
-            return;
+            // (the sum must not run over scratch that was not written)
+            if (hipError_t e = hipGetLastError(); e != hipSuccess || !sp) return e;
+            hipLaunchKernelGGL(k_add_splits, dim3(nb), dim3(256), 0, st, sp, (int)grid.y,
+                               (long long)d.nx * d.ny * d.nz * d.C, g, beta, c, partials);
+            return hipGetLastError();
         }
     }
     hipLaunchKernelGGL((k_backproject<UP, MT, BF16, JOS>), dim3(nb), dim3(256), 0, st, yf, frames, t.Bu,
                        reinterpret_cast<const s4 *>(t.BuT16), d.S, d.nx, d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step, g,
                        beta, c, partials);
+    return hipGetLastError();
 }
 
 template <int UP, int MT>
 static hipError_t bp_t(const Dims &d, const ProjFrame *frames, const float *yf, const AdjointTables &t, float *split, int bf16,
                        float *g, float beta, const float *c, double *partials, hipStream_t st)
 {
-    if (bf16 && d.joseph)
-        bp_launch<UP, MT, true, true>(d, frames, yf, t, split, g, beta, c, partials, st);
-    else if (bf16)
-        bp_launch<UP, MT, true, false>(d, frames, yf, t, split, g, beta, c, partials, st);
-    else if (d.joseph)
-        bp_launch<UP, MT, false, true>(d, frames, yf, t, split, g, beta, c, partials, st);
-    else
-        bp_launch<UP, MT, false, false>(d, frames, yf, t, split, g, beta, c, partials, st);
-    return hipGetLastError();
+    if (bf16 && d.joseph) return bp_launch<UP, MT, true, true>(d, frames, yf, t, split, g, beta, c, partials, st);
+    if (bf16) return bp_launch<UP, MT, true, false>(d, frames, yf, t, split, g, beta, c, partials, st);
+    if (d.joseph) return bp_launch<UP, MT, false, true>(d, frames, yf, t, split, g, beta, c, partials, st);
+    return bp_launch<UP, MT, false, false>(d, frames, yf, t, split, g, beta, c, partials, st);
 }
 
 template <int UP>
