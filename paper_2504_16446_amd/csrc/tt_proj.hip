@@ -1814,10 +1814,26 @@ __device__ __forceinline__ void put_q(const float *q, uint4 *t, int stride)
     }
 }
 
+// Waves per SIMD that the registers have to leave room for.
+//  - Two from 64 padded coefficients on: left alone, the kernels of four segments take 272
+//    to 312 registers (accumulators in accumulation registers and moves between), which is
+//    one wave per SIMD.  72^3 / 120 projections / 4 unique segments / 91 coefficients, one
+//    wave -> two: 1161 -> 642 us, unpaired 1916 -> 1172, Joseph 929 -> 522 and 1511 -> 879;
+//    bf16 tier, 66 coefficients: 1013 -> 498.  (Unpaired trilinear float32 with 66 stays
+//    below 256 by itself, and is 4% faster so.)
+//  - Five or six (unpaired: smaller windows) for Joseph's method with up to 16
+//    coefficients, the least arithmetic per barrier: 101 x 100 x 100 / 240 projections
+//    unpaired 1787 -> 1559 us (gathering from memory, without barriers: 1592); paired
+//    100^3 / 240 1204 -> 1090, 128 x 127 x 127 / 300 2757 -> 2546 (72^3 / 160, whose last
+//    blocks then run alone, 331 -> 345).
+template <int UP, int MT, bool BF16, bool JOS, bool PAIR>
+constexpr int kAdjointWaves = MT >= 4 ? (UP == 4 && MT == 5 && !BF16 && !JOS && !PAIR ? 1 : 2)
+                                      : UP == 4 && MT == 1 && JOS ? (PAIR ? 5 : 6) : 3;
+
 constexpr int kWinCopies = 6;  // copies of 128 float4 per window and pair (at most)
 
 template <int UP, int MT, bool BF16, bool JOS, bool PAIR>
-__global__ __launch_bounds__(256, MT <= 3 ? 3 : 1) void k_backproject_win(const float *__restrict__ yf,
+__global__ __launch_bounds__(256, (kAdjointWaves<UP, MT, BF16, JOS, PAIR>)) void k_backproject_win(const float *__restrict__ yf,
                                                          const ProjFrame *__restrict__ frames,
                                                          const uint4 *__restrict__ Bop, int S, int nx, int ny, int nz,
                                                          int nj, int nk, int C, int Cp, float step,
