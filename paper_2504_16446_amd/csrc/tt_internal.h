@@ -93,10 +93,11 @@ void plan_rings(std::vector<ProjFrame> &frames, const Geometry &g, int up, int *
 // Kernel launchers (tt_proj.hip, tt_vec.hip).  All asynchronous on `st`.
 // ---------------------------------------------------------------------------
 // Staged adjoint of one projector model: point-inversion pairing, dynamic LDS
-// bytes (0: not used), window rows / columns, and splits of the projections over
-// blocks (each needs a coefficient volume of scratch; 1: none).
+// bytes (0: not used), window rows / columns, splits of the projections over blocks
+// (each needs a coefficient volume of scratch; 1: none), and whether the grid is more
+// than three blocks per compute unit.
 struct AdjointPlan {
-    int pair, lds, wr, wc, splits;
+    int pair, lds, wr, wc, splits, deep;
 };
 constexpr int kMaxSplits = 8;
 

@@ -1789,6 +1789,11 @@ __device__ __forceinline__ void split_bf16(float a, float b, unsigned &h, unsign
 // one product of four projections, so two pairs share a contraction.
 // It pays from 48 padded coefficients on (fewer MFMAs and adds); below, the smaller
 // tiles leave room for more blocks.
+// It also takes registers (168, three waves per SIMD, with 48), so that unpaired adjoints
+// of 48 coefficients use it only where a grid has no fourth block per compute unit to
+// run: one pair per contraction with four waves, 64^3 / 120 projections with detector
+// offsets (four blocks per unit) 533 -> 407 us, 100^3 / 240 3260 -> 3002 us (Joseph
+// 2232 -> 2020), but 48^3 / 120 (two blocks per unit) 274 -> 286.
 template <int UP, int MT>
 constexpr int kPairs = UP == 4 && MT >= 3 ? 2 : 1;
 template <int UP, bool BF16>
@@ -1826,14 +1831,14 @@ __device__ __forceinline__ void put_q(const float *q, uint4 *t, int stride)
 //    unpaired 1787 -> 1559 us (gathering from memory, without barriers: 1592); paired
 //    100^3 / 240 1204 -> 1090, 128 x 127 x 127 / 300 2757 -> 2546 (72^3 / 160, whose last
 //    blocks then run alone, 331 -> 345).
-template <int UP, int MT, bool BF16, bool JOS, bool PAIR>
+template <int UP, int MT, bool BF16, bool JOS, bool PAIR, int PB>
 constexpr int kAdjointWaves = MT >= 4 ? (UP == 4 && MT == 5 && !BF16 && !JOS && !PAIR ? 1 : 2)
-                                      : UP == 4 && MT == 1 && JOS ? (PAIR ? 5 : 6) : 3;
+                                      : UP == 4 && MT == 1 && JOS ? (PAIR ? 5 : 6) : PB < kPairs<UP, MT> ? 4 : 3;
 
 constexpr int kWinCopies = 6;  // copies of 128 float4 per window and pair (at most)
 
-template <int UP, int MT, bool BF16, bool JOS, bool PAIR>
-__global__ __launch_bounds__(256, (kAdjointWaves<UP, MT, BF16, JOS, PAIR>)) void k_backproject_win(const float *__restrict__ yf,
+template <int UP, int MT, bool BF16, bool JOS, bool PAIR, int PB = kPairs<UP, MT>>
+__global__ __launch_bounds__(256, (kAdjointWaves<UP, MT, BF16, JOS, PAIR, PB>)) void k_backproject_win(const float *__restrict__ yf,
                                                          const ProjFrame *__restrict__ frames,
                                                          const uint4 *__restrict__ Bop, int S, int nx, int ny, int nz,
                                                          int nj, int nk, int C, int Cp, float step,
@@ -1848,8 +1853,7 @@ __global__ __launch_bounds__(256, (kAdjointWaves<UP, MT, BF16, JOS, PAIR>)) void
     constexpr int RW = PAIR ? 2 * Q : Q;    // float4 per staged ray: own, then reflected
     constexpr int QT = kQTiles<UP, BF16>;
     extern __shared__ f4 wins[];            // [2][WR * WC * RW rounded up to 128]
-    constexpr int PB = kPairs<UP, MT>;      // pairs per contraction
-    constexpr int QS = 2 * PB * 64;         // stride of the operand tiles
+    constexpr int QS = 2 * PB * 64;         // stride of the operand tiles (PB: pairs per contraction)
     __shared__ uint4 Qt[4][QT][2 * PB][64];  // [wave][tile][projection][voxel]
     __shared__ int2 wtab[2][64];            // window origins of the next 64 pairs
     __shared__ double ws[4];
@@ -2241,6 +2245,7 @@ void plan_adjoint(const std::vector<ProjFrame> &frames, Dims &d)
             p.lds = window_lds(frames, d, false, jos != 0, p.wr, p.wc);
         }
         p.splits = p.lds > 0 ? adjoint_splits(d, win_blocks(d, p.pair != 0), units) : 1;
+        p.deep = (long long)win_blocks(d, p.pair != 0) * p.splits > 3LL * units;
     }
 }
 
@@ -2268,8 +2273,12 @@ static hipError_t bp_launch(const Dims &d, const ProjFrame *frames, const float 
                 hipLaunchKernelGGL(kernel, grid, dim3(256), p.lds, st, yf, frames, bop, d.S, d.nx, d.ny, d.nz, d.nj,
                                    d.nk, d.C, d.Cp, d.step, g, beta, c, partials, p.wr, p.wc, s_per, sp);
             };
+            // (the bf16 Joseph kernel runs four waves with two pairs as well)
+            constexpr int unpaired_pb = UP == 4 && MT == 3 && !(BF16 && JOS) ? 1 : kPairs<UP, MT>;
             if (p.pair)
                 launch(k_backproject_win<UP, MT, BF16, JOS, true>);
+            else if (p.deep)
+                launch(k_backproject_win<UP, MT, BF16, JOS, false, unpaired_pb>);
             else
                 launch(k_backproject_win<UP, MT, BF16, JOS, false>);
             // (the sum must not run over scratch that was not written)

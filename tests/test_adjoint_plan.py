@@ -1,0 +1,39 @@
+"""Which adjoint kernel a geometry runs, from its launches on a stand-in runtime
+(template arguments: unique segments, 16-coefficient tiles, bf16 tier, Joseph, paired,
+projection pairs per contraction)."""
+import pytest
+
+import oracle
+import tt_inputs as synth
+from fake_hip import scenario
+from geoms import tilted_angles
+
+
+def adjoint_launches(F, n, ell, n_rot, n_seg, model, offsets, step):
+    inner, outer = tilted_angles(n_rot, (0.0, 15.0, 30.0, 45.0), span_deg=360.0)
+    kw = dict(joff=[0.5] * len(inner), koff=[0.25] * len(inner)) if offsets else {}
+    og = oracle.Geometry((n, n, n), ell, inner, outer, n, n, n_seg, synth.lab_frame(), model=model, step=step, **kw)
+    h = F.create(og, model)
+    F.workspace(h, 1)
+    s = F.sizes(h)
+    rc, seen = F.launches("tt_adjoint", h, F.buffer(4 * s[1]), F.buffer(4 * s[0]), 0.0, None)
+    assert rc == 0
+    return [name for name, *_ in seen]
+
+
+def _kernel(names, up, mt, *flags):
+    name = f"k_backproject_winILi{up}ELi{mt}E" + "".join(f"Lb{int(f)}E" if isinstance(f, bool) else f"Li{f}E" for f in flags)
+    assert any(name in k for k in names), (name, names)
+
+
+@pytest.mark.parametrize("model", ["trilinear", "joseph"])
+@pytest.mark.parametrize("n, pairs", [(48, 2), (56, 2), (64, 1), (72, 1)])
+def test_unpaired_adjoints_of_four_segments_and_48_coefficients(n, pairs, model):
+    # more than three blocks of 4 x 8 x 8 voxels per compute unit (256): one pair per contraction
+    names = scenario("test_adjoint_plan", "adjoint_launches", n, 8, 30, 8, model, True, 1.0)
+    _kernel(names, 4, 3, False, model == "joseph", False, pairs)
+
+
+def test_paired_adjoints_keep_two_pairs():
+    names = scenario("test_adjoint_plan", "adjoint_launches", 64, 8, 30, 8, "trilinear", False, 1.0)
+    _kernel(names, 4, 3, False, False, True, 2)

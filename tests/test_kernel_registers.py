@@ -27,5 +27,6 @@ def test_adjoint_kernels_leave_room_for_two_waves():
     ks = {n: k for n, k in _kernels().items() if "k_backproject" in n}
     assert len(ks) >= 96, len(ks)
     assert {n: k[".vgpr_count"] for n, k in ks.items() if k[".vgpr_count"] > 256} == {}
-    # without spilling for it (a few set-up values at most)
-    assert {n: k[".private_segment_fixed_size"] for n, k in ks.items() if k[".private_segment_fixed_size"] > 16} == {}
+    # without spilling for it, from 64 coefficients on (a few set-up values at most)
+    wide = {n: k[".private_segment_fixed_size"] for n, k in ks.items() if re.search("ILi[0-9]+ELi[456]E", n)}
+    assert len(wide) >= 48 and {n: b for n, b in wide.items() if b > 16} == {}
