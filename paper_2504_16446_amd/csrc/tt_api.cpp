@@ -47,7 +47,7 @@ struct tt_ctx {
     float *d_Bu = nullptr;      // [bu_rows][Cp]: row s*Up + u, zero padded
     float *d_Bsw = nullptr;     // Bu in MFMA lane order (16-row tiles), for the forward map
     uint16_t *d_Bsw16 = nullptr; // bf16 Bu in MFMA lane order (16-row tiles, 32-coefficient steps), forward
-    uint16_t *d_BuT16 = nullptr; // bf16 [S][Cp][16]: B^T with u padded to 16, adjoint
+    uint16_t *d_BuT16 = nullptr; // bf16 [S][Cp][16]: B^T, adjoint of 16 unique segments
     uint16_t *d_Bop = nullptr;  // [S][6][Cp][8] bf16 operands of the staged adjoint (up to 8 unique segments)
     int pb = 0;                 // projections per forward batch (0: no workspace attached)
     long long vol_pad = 0;
@@ -126,7 +126,7 @@ struct Tables {
     std::vector<float> bu;         // [bu_rows][Cp]: row s*Up + u, zero padded
     std::vector<float> bsw;        // bu in MFMA lane order: tile rt, k-step ks, lane l
     std::vector<uint16_t> bsw16;   // bf16 bu in MFMA lane order (16-row tiles, 32-coefficient steps)
-    std::vector<uint16_t> but16;   // bf16 [S][Cp][16]: B^T with u padded to 16
+    std::vector<uint16_t> but16;   // bf16 [S][Cp][16]: B^T (16 unique segments)
     std::vector<uint16_t> bop;     // [S][6][Cp][8]: operands of the staged adjoint
 };
 static void build_tables(const tt_ctx *c, Tables &t)
@@ -143,7 +143,6 @@ static void build_tables(const tt_ctx *c, Tables &t)
     // bu[16 rt + l % 16][32 kp + 8 (l / 16) + q], zero from Cp on
     const int KP = (d.Cp + 31) / 32;
     t.bsw16.assign((size_t)bu_rows / 16 * KP * 512, 0);
-    t.but16.assign((size_t)S * d.Cp * 16, 0);
     for (int rt = 0; rt < bu_rows / 16; ++rt)
         for (int l = 0; l < 64; ++l) {
             const float *row = &t.bu[((size_t)rt * 16 + l % 16) * d.Cp];
@@ -153,7 +152,8 @@ static void build_tables(const tt_ctx *c, Tables &t)
                     if (k < d.Cp) t.bsw16[(((size_t)rt * KP + kp) * 64 + l) * 8 + q] = to_bf16(row[k]);
                 }
         }
-    for (int s = 0; s < S; ++s)
+    t.but16.assign(d.Up > 8 ? (size_t)S * d.Cp * 16 : 0, 0);
+    for (int s = 0; s < S && d.Up > 8; ++s)
         for (int i = 0; i < d.Cp; ++i)
             for (int u = 0; u < d.Up; ++u)
                 t.but16[((size_t)s * d.Cp + i) * 16 + u] = to_bf16(t.bu[((size_t)s * d.Up + u) * d.Cp + i]);
@@ -427,7 +427,7 @@ int tt_create(const tt_geometry *geom, tt_ctx **out)
         hipMalloc(&c->d_Bu, bu.size() * sizeof(float)) != hipSuccess ||
         hipMalloc(&c->d_Bsw, bsw.size() * sizeof(float)) != hipSuccess ||
         hipMalloc(&c->d_Bsw16, bsw16.size() * sizeof(uint16_t)) != hipSuccess ||
-        hipMalloc(&c->d_BuT16, but16.size() * sizeof(uint16_t)) != hipSuccess ||
+        (!but16.empty() && hipMalloc(&c->d_BuT16, but16.size() * sizeof(uint16_t)) != hipSuccess) ||
         (!t.bop.empty() && hipMalloc(&c->d_Bop, t.bop.size() * sizeof(uint16_t)) != hipSuccess) ||
         hipMalloc(&c->d_sp, sp_len * sizeof(int2)) != hipSuccess ||
         hipMalloc(&c->d_gtab, gtab_len * sizeof(int)) != hipSuccess)
@@ -438,7 +438,8 @@ int tt_create(const tt_geometry *geom, tt_ctx **out)
         hipMemcpy(c->d_Bu, bu.data(), bu.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(c->d_Bsw, bsw.data(), bsw.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(c->d_Bsw16, bsw16.data(), bsw16.size() * sizeof(uint16_t), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(c->d_BuT16, but16.data(), but16.size() * sizeof(uint16_t), hipMemcpyHostToDevice) != hipSuccess ||
+        (!but16.empty() &&
+         hipMemcpy(c->d_BuT16, but16.data(), but16.size() * sizeof(uint16_t), hipMemcpyHostToDevice) != hipSuccess) ||
         (!t.bop.empty() &&
          hipMemcpy(c->d_Bop, t.bop.data(), t.bop.size() * sizeof(uint16_t), hipMemcpyHostToDevice) != hipSuccess) ||
         hipDeviceSynchronize() != hipSuccess)
@@ -554,7 +555,8 @@ int tt_set_sparse_map(tt_ctx *c, int k)
     TT_HIP(hipMemcpy(c->d_Bu, t.bu.data(), t.bu.size() * sizeof(float), hipMemcpyHostToDevice));
     TT_HIP(hipMemcpy(c->d_Bsw, t.bsw.data(), t.bsw.size() * sizeof(float), hipMemcpyHostToDevice));
     TT_HIP(hipMemcpy(c->d_Bsw16, t.bsw16.data(), t.bsw16.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
-    TT_HIP(hipMemcpy(c->d_BuT16, t.but16.data(), t.but16.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
+    if (!t.but16.empty())
+        TT_HIP(hipMemcpy(c->d_BuT16, t.but16.data(), t.but16.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
     if (!t.bop.empty()) TT_HIP(hipMemcpy(c->d_Bop, t.bop.data(), t.bop.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
     if (!sp.empty()) TT_HIP(hipMemcpy(c->d_sp, sp.data(), sp.size() * sizeof(int2), hipMemcpyHostToDevice));
     if (!gtab.empty()) TT_HIP(hipMemcpy(c->d_gtab, gtab.data(), gtab.size() * sizeof(int), hipMemcpyHostToDevice));

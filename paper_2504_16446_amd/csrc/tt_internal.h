@@ -93,7 +93,7 @@ void plan_rings(std::vector<ProjFrame> &frames, const Geometry &g, int up, int *
 // Kernel launchers (tt_proj.hip, tt_vec.hip).  All asynchronous on `st`.
 // ---------------------------------------------------------------------------
 // Staged adjoint of one projector model: point-inversion pairing, dynamic LDS
-// bytes (0: not used), window rows / columns, splits of the projections over blocks
+// bytes (0 with sixteen unique segments: not used), window rows / columns, splits of the projections over blocks
 // (each needs a coefficient volume of scratch; 1: none), and whether the grid is more
 // than three blocks per compute unit.
 struct AdjointPlan {
@@ -154,7 +154,7 @@ hipError_t launch_residual_fold(const Dims &d, const float *Ip, const float *dat
 // bf16 != 0: the transpose map rounds Q and B to bf16.
 struct AdjointTables {
     const float *Bu;        // [S Up][Cp]
-    const uint16_t *BuT16;  // [S][Cp][16]: bf16 B^T, u padded with zeros
+    const uint16_t *BuT16;  // [S][Cp][16]: bf16 B^T (sixteen unique segments; else null)
     const uint16_t *Bop;    // [S][6][Cp][8]: operands of the staged adjoint (see build_tables)
 };
 // split: scratch of d.adj[d.joseph].splits coefficient volumes, or null (no splits).

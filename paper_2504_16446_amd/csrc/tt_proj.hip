@@ -1428,7 +1428,7 @@ hipError_t launch_residual_fold(const Dims &d, const float *Ip, const float *dat
 }
 
 // ---------------------------------------------------------------------------
-// backproject: block = brick of 4 (x) x 8 (y) x 8 (z) voxels; wave w owns the
+// backproject (sixteen unique segments): block = brick of 4 (x) x 8 (y) x 8 (z) voxels; wave w owns the
 // x-slice w (64 voxels = 4 column tiles of 16).  Loops over all projections.
 // ---------------------------------------------------------------------------
 // Q tile entry (u = 4 ks + lane / 16) of voxel column 16 nt + lane % 16 (row stride UP + 1)
@@ -2203,8 +2203,9 @@ static int adjoint_splits(const Dims &d, int blocks, int units)
 // every ray of its voxels in any projection (centre span . |e| + 2 reach + 3 for
 // rounding), at most the detector; returns the dynamic LDS bytes of the two
 // windows, or 0 where they take more copies than the kernel keeps offsets for or
-// leave fewer than three blocks per CU (the general kernel then reads the residual
-// from memory).
+// leave fewer than three blocks per CU.  Without pairs they always fit: e_j and e_k are
+// unit vectors and 2 reach <= 2 |e|_1, so 5 |e_x| + 9 |e_y| + 9 |e_z| + 3 <= 16.7, that is
+// 16 x 16 rays, four of six copies and 42 KiB at most.
 static int window_lds(const std::vector<ProjFrame> &frames, const Dims &d, bool pair, bool jos, int &wr, int &wc)
 {
     wr = wc = 0;
@@ -2262,36 +2263,36 @@ static hipError_t bp_launch(const Dims &d, const ProjFrame *frames, const float 
 {
     const AdjointPlan &p = d.adj[JOS];
     const int nb = backproject_blocks(d);
-    if constexpr (UP <= 8) {
-        if (p.lds > 0) {
-            const uint4 *bop = reinterpret_cast<const uint4 *>(t.Bop);
-            const int ns = split ? p.splits : 1;
-            const int s_per = ns > 1 ? (d.S + 4 * ns - 1) / (4 * ns) * 4 : d.S;  // whole double pairs
-            const dim3 grid(nb, (d.S + s_per - 1) / s_per);
-            float *sp = grid.y > 1 ? split : nullptr;
-            auto launch = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, grid, dim3(256), p.lds, st, yf, frames, bop, d.S, d.nx, d.ny, d.nz, d.nj,
-                                   d.nk, d.C, d.Cp, d.step, g, beta, c, partials, p.wr, p.wc, s_per, sp);
-            };
-            // (the bf16 Joseph kernel runs four waves with two pairs as well)
-            constexpr int unpaired_pb = UP == 4 && MT == 3 && !(BF16 && JOS) ? 1 : kPairs<UP, MT>;
-            if (p.pair)
-                launch(k_backproject_win<UP, MT, BF16, JOS, true>);
-            else if (p.deep)
-                launch(k_backproject_win<UP, MT, BF16, JOS, false, unpaired_pb>);
-            else
-                launch(k_backproject_win<UP, MT, BF16, JOS, false>);
-            // (the sum must not run over scratch that was not written)
-            if (hipError_t e = hipGetLastError(); e != hipSuccess || !sp) return e;
-            hipLaunchKernelGGL(k_add_splits, dim3(nb), dim3(256), 0, st, sp, (int)grid.y,
-                               (long long)d.nx * d.ny * d.nz * d.C, g, beta, c, partials);
-            return hipGetLastError();
-        }
+    if constexpr (UP > 8) {
+        hipLaunchKernelGGL((k_backproject<UP, MT, BF16, JOS>), dim3(nb), dim3(256), 0, st, yf, frames, t.Bu,
+                           reinterpret_cast<const s4 *>(t.BuT16), d.S, d.nx, d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step,
+                           g, beta, c, partials);
+        return hipGetLastError();
+    } else {
+        if (p.lds == 0) return hipErrorInvalidValue;  // (cannot be: see window_lds)
+        const uint4 *bop = reinterpret_cast<const uint4 *>(t.Bop);
+        const int ns = split ? p.splits : 1;
+        const int s_per = ns > 1 ? (d.S + 4 * ns - 1) / (4 * ns) * 4 : d.S;  // whole double pairs
+        const dim3 grid(nb, (d.S + s_per - 1) / s_per);
+        float *sp = grid.y > 1 ? split : nullptr;
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, dim3(256), p.lds, st, yf, frames, bop, d.S, d.nx, d.ny, d.nz, d.nj, d.nk,
+                               d.C, d.Cp, d.step, g, beta, c, partials, p.wr, p.wc, s_per, sp);
+        };
+        // (the bf16 Joseph kernel runs four waves with two pairs as well)
+        constexpr int unpaired_pb = UP == 4 && MT == 3 && !(BF16 && JOS) ? 1 : kPairs<UP, MT>;
+        if (p.pair)
+            launch(k_backproject_win<UP, MT, BF16, JOS, true>);
+        else if (p.deep)
+            launch(k_backproject_win<UP, MT, BF16, JOS, false, unpaired_pb>);
+        else
+            launch(k_backproject_win<UP, MT, BF16, JOS, false>);
+        // (the sum must not run over scratch that was not written)
+        if (hipError_t e = hipGetLastError(); e != hipSuccess || !sp) return e;
+        hipLaunchKernelGGL(k_add_splits, dim3(nb), dim3(256), 0, st, sp, (int)grid.y,
+                           (long long)d.nx * d.ny * d.nz * d.C, g, beta, c, partials);
+        return hipGetLastError();
     }
-    hipLaunchKernelGGL((k_backproject<UP, MT, BF16, JOS>), dim3(nb), dim3(256), 0, st, yf, frames, t.Bu,
-                       reinterpret_cast<const s4 *>(t.BuT16), d.S, d.nx, d.ny, d.nz, d.nj, d.nk, d.C, d.Cp, d.step, g,
-                       beta, c, partials);
-    return hipGetLastError();
 }
 
 template <int UP, int MT>

@@ -37,3 +37,24 @@ def test_unpaired_adjoints_of_four_segments_and_48_coefficients(n, pairs, model)
 def test_paired_adjoints_keep_two_pairs():
     names = scenario("test_adjoint_plan", "adjoint_launches", 64, 8, 30, 8, "trilinear", False, 1.0)
     _kernel(names, 4, 3, False, False, True, 2)
+
+
+def random_frames(F, n_seg, nx, model):
+    import numpy as np
+    r = np.random.default_rng(n_seg + nx)
+    og = oracle.Geometry((nx, 40, 40), 8, r.uniform(0, 2 * np.pi, 400), r.uniform(0, np.pi, 400), 60, 60, n_seg,
+                         synth.lab_frame(), model=model)
+    h = F.create(og, model)
+    F.workspace(h, 1)
+    s = F.sizes(h)
+    rc, seen = F.launches("tt_adjoint", h, F.buffer(4 * s[1]), F.buffer(4 * s[0]), 0.0, None)
+    return rc, [name for name, *_ in seen]
+
+
+@pytest.mark.parametrize("model", ["trilinear", "joseph"])
+@pytest.mark.parametrize("nx", [40, 41])
+@pytest.mark.parametrize("n_seg", [8, 16])
+def test_windows_of_any_orientation_fit(n_seg, nx, model):
+    # up to eight unique segments have no other kernel
+    rc, names = scenario("test_adjoint_plan", "random_frames", n_seg, nx, model)
+    assert rc == 0 and any("k_backproject_win" in k for k in names)
