@@ -1445,7 +1445,9 @@ __device__ __forceinline__ float qw_at(const float *Qw, int nt, int ks, int lane
 // So every ray evaluates the same n_tau samples (three, or four for steep
 // diagonals, at step 1) without a branch; kept as a range per ray over all
 // three axes, a loop and its exec masks, the adjoint's lanes waited for the
-// ray with the most samples at every step.
+// ray with the most samples at every step.  (Also at small steps, where the range is
+// shorter: 64^3 / 120 projections / 4 unique segments at step 0.1 1136 us with a
+// range, 1068 with the fixed number, 870 with its loop unrolled by four.)
 struct TentRay {
     float d[3], sd[3];  // ray direction, and the sample spacing along each axis
     float ca, cb;       // first sample: n = ceil(ca P_0 + cb)
@@ -1472,6 +1474,7 @@ __device__ __forceinline__ TentRay tent_ray(const ProjFrame &f, float tr, float 
 // max(0, 1 - |x|), one instruction (clamp modifier)
 __device__ __forceinline__ float tent1(float x) { return __builtin_amdgcn_fmed3f(1.0f - fabsf(x), 0.0f, 1.0f); }
 
+template <bool MANY>
 __device__ __forceinline__ float ray_weight(const float P[3], const TentRay &t)
 {
     const float tau = fmaf(ceilf(fmaf(t.ca, P[0], t.cb)), t.step, t.off);
@@ -1484,7 +1487,17 @@ __device__ __forceinline__ float ray_weight(const float P[3], const TentRay &t)
         z += t.sd[2];
         w = fmaf(tent1(x) * tent1(y), tent1(z), w);
     }
-    for (int i = 0; i < t.more; ++i) {
+    const int fours = MANY ? t.more & ~3 : 0;
+    for (int n = 0; n < fours; n += 4) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            x += t.sd[0];
+            y += t.sd[1];
+            z += t.sd[2];
+            w = fmaf(tent1(x) * tent1(y), tent1(z), w);
+        }
+    }
+    for (int i = fours; i < t.more; ++i) {
         x += t.sd[0];
         y += t.sd[1];
         z += t.sd[2];
@@ -1642,7 +1655,7 @@ __global__ __launch_bounds__(256) void k_backproject(const float *__restrict__ y
 #pragma unroll
                     for (int u4 = 0; u4 < UP / 4; ++u4) yv[u4] = yrow[k * (UP / 4) + u4];  // in flight meanwhile
                     const float P[3] = {fmaf(dk, f.ekf[0], pj0), fmaf(dk, f.ekf[1], pj1), fmaf(dk, f.ekf[2], pj2)};
-                    const float wsum = ray_weight(P, tent);
+                    const float wsum = ray_weight<false>(P, tent);
 #pragma unroll
                     for (int u4 = 0; u4 < UP; u4 += 4) {
                         q[u4 + 0] = fmaf(wsum, yv[u4 / 4].x, q[u4 + 0]);
@@ -1837,7 +1850,7 @@ constexpr int kAdjointWaves = MT >= 4 ? (UP == 4 && MT == 5 && !BF16 && !JOS && 
 
 constexpr int kWinCopies = 6;  // copies of 128 float4 per window and pair (at most)
 
-template <int UP, int MT, bool BF16, bool JOS, bool PAIR, int PB = kPairs<UP, MT>>
+template <int UP, int MT, bool BF16, bool JOS, bool PAIR, int PB = kPairs<UP, MT>, bool MANY = false>
 __global__ __launch_bounds__(256, (kAdjointWaves<UP, MT, BF16, JOS, PAIR, PB>)) void k_backproject_win(const float *__restrict__ yf,
                                                          const ProjFrame *__restrict__ frames,
                                                          const uint4 *__restrict__ Bop, int S, int nx, int ny, int nz,
@@ -2030,7 +2043,7 @@ __global__ __launch_bounds__(256, (kAdjointWaves<UP, MT, BF16, JOS, PAIR, PB>)) 
                             const float dk = fk - br;
                             const float P[3] = {fmaf(dk, f.ekf[0], pj0), fmaf(dk, f.ekf[1], pj1),
                                                 fmaf(dk, f.ekf[2], pj2)};
-                            add_ray(ray_weight(P, tent));
+                            add_ray(ray_weight<MANY>(P, tent));
                         }
                     }
                 }
@@ -2231,6 +2244,18 @@ static int win_blocks(const Dims &d, bool pair)
                 : ((d.nx + 3) / 4) * ((d.ny + 7) / 8) * ((d.nz + 7) / 8);
 }
 
+// Samples of a ray above which the loop over those beyond the first three is unrolled by
+// four (steps below about 0.45).  With four unique segments and 48 coefficients these
+// kernels also run four waves with one pair per contraction: the branches of that loop
+// then have other waves beside them.  One sample at a time -> by fours, 64^3 / 120
+// projections / 45 coefficients, at steps 0.5, 0.4, 0.25, 0.1 (in brackets the kernels
+// before the staged one, with a range per ray):
+//   4 segments  443 -> 369  485 -> 384  599 -> 455  1067 ->  735 us  (461 470 509  760)
+//   8 segments  538 -> 542  583 -> 551  709 -> 622  1229 ->  932     (800 838 953 1433)
+//   unpaired    718 -> 738  792 -> 755  994 -> 879  1810 -> 1421     (786 830 961 1493)
+// and 100^3 / 240, 4 segments  2683 -> 2774  2932 -> 2898  3616 -> 3403  6400 -> 5412.
+constexpr int kFewSamples = 7;
+
 void plan_adjoint(const std::vector<ProjFrame> &frames, Dims &d)
 {
     int dev = 0, units = 0;
@@ -2246,6 +2271,9 @@ void plan_adjoint(const std::vector<ProjFrame> &frames, Dims &d)
             p.lds = window_lds(frames, d, false, jos != 0, p.wr, p.wc);
         }
         p.splits = p.lds > 0 ? adjoint_splits(d, win_blocks(d, p.pair != 0), units) : 1;
+        p.many = 0;
+        for (const ProjFrame &f : frames)
+            if (f.n_tau > kFewSamples) p.many = 1;
         p.deep = (long long)win_blocks(d, p.pair != 0) * p.splits > 3LL * units;
     }
 }
@@ -2281,7 +2309,11 @@ static hipError_t bp_launch(const Dims &d, const ProjFrame *frames, const float 
         };
         // (the bf16 Joseph kernel runs four waves with two pairs as well)
         constexpr int unpaired_pb = UP == 4 && MT == 3 && !(BF16 && JOS) ? 1 : kPairs<UP, MT>;
-        if (p.pair)
+        constexpr int many_pb = UP == 4 && MT == 3 ? 1 : kPairs<UP, MT>;
+        if (!JOS && p.many)
+            p.pair ? launch(k_backproject_win<UP, MT, BF16, false, true, many_pb, true>)
+                   : launch(k_backproject_win<UP, MT, BF16, false, false, many_pb, true>);
+        else if (p.pair)
             launch(k_backproject_win<UP, MT, BF16, JOS, true>);
         else if (p.deep)
             launch(k_backproject_win<UP, MT, BF16, JOS, false, unpaired_pb>);

@@ -58,3 +58,12 @@ def test_windows_of_any_orientation_fit(n_seg, nx, model):
     # up to eight unique segments have no other kernel
     rc, names = scenario("test_adjoint_plan", "random_frames", n_seg, nx, model)
     assert rc == 0 and any("k_backproject_win" in k for k in names)
+
+
+@pytest.mark.parametrize("n_seg, up, pairs", [(8, 4, 1), (16, 8, 1)])
+@pytest.mark.parametrize("offsets", [False, True])
+def test_small_steps_unroll_the_samples_of_a_ray(offsets, n_seg, up, pairs):
+    names = scenario("test_adjoint_plan", "adjoint_launches", 64, 8, 30, n_seg, "trilinear", offsets, 0.25)
+    _kernel(names, up, 3, False, False, not offsets, pairs, True)
+    names = scenario("test_adjoint_plan", "adjoint_launches", 64, 8, 30, n_seg, "trilinear", offsets, 0.8)
+    assert not any("Li1ELb1EEEv" in k or "Li2ELb1EEEv" in k for k in names), names
