@@ -58,6 +58,8 @@ __device__ __forceinline__ short f2bf(float x)
     return (short)(u >> 16);
 }
 
+__device__ __forceinline__ float bf16_value(float x) { return __uint_as_float((unsigned)(unsigned short)f2bf(x) << 16); }
+
 __device__ __forceinline__ long long pad_index(int v, int ny, int nz)
 {
     int iz = v % nz;
@@ -1848,12 +1850,72 @@ template <int UP, int MT, bool BF16, bool JOS, bool PAIR, int PB>
 constexpr int kAdjointWaves = MT >= 4 ? (UP == 4 && MT == 5 && !BF16 && !JOS && !PAIR ? 1 : 2)
                                       : UP == 4 && MT == 1 && JOS ? (PAIR ? 5 : 6) : PB < kPairs<UP, MT> ? 4 : 3;
 
-constexpr int kWinCopies = 6;  // copies of 128 float4 per window and pair (at most)
+// sum over projections s0 .. s1 - 1 of B^T Q at one voxel (centred position x, y, z) in
+// float32, four coefficients per 16 of them (Bu: from the first).  For the few sums that
+// k_backproject_win cannot take: all rays in reach of the voxel, from memory.
+template <int UP, int MT, bool BF16, bool JOS>
+__device__ __forceinline__ void sum_in_f32(const float *yf, const ProjFrame *frames, const float *Bu, int s0, int s1,
+                                           int nj, int nk, int Cp, float step, double x, double y, double z, f4 *sum)
+{
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) sum[mt] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int s = s0; s < s1; ++s) {
+        const ProjFrame &f = frames[s];
+        const double w0 = x - f.o[0], w1 = y - f.o[1], w2 = z - f.o[2];
+        const double a = w0 * f.ej[0] + w1 * f.ej[1] + w2 * f.ej[2];
+        const double b = w0 * f.ek[0] + w1 * f.ek[1] + w2 * f.ek[2];
+        const double ts = (w0 * f.d[0] + w1 * f.d[1] + w2 * f.d[2]) / (double)step;
+        const int ai = (int)floor(a), bi = (int)floor(b);
+        const float ar = (float)(a - floor(a)), br = (float)(b - floor(b));
+        const float rj = JOS ? f.jos_rj : (float)f.lj, rk = JOS ? f.jos_rk : (float)f.lk;
+        const int j1 = min(nj - 1, ai + (int)floorf(ar + rj)), k0 = max(0, bi + (int)ceilf(br - rk));
+        const int k1 = min(nk - 1, bi + (int)floorf(br + rk));
+        const TentRay tent = tent_ray(f, (float)(ts - floor(ts)), step, 1.0f / step);
+        float q[UP];
+#pragma unroll
+        for (int u = 0; u < UP; ++u) q[u] = 0.0f;
+#pragma unroll 1
+        for (int j = max(0, ai + (int)ceilf(ar - rj)); j <= j1; ++j)
+#pragma unroll 1
+            for (int k = k0; k <= k1; ++k) {
+                const float dj = (float)(j - ai) - ar, dk = (float)(k - bi) - br;
+                float wt;
+                if constexpr (JOS) {
+                    wt = tent1(fmaf(dk, f.jos_gk[0], dj * f.jos_gj[0])) *
+                         tent1(fmaf(dk, f.jos_gk[1], dj * f.jos_gj[1])) * f.jos_w;
+                } else {
+                    const float P[3] = {fmaf(dk, f.ekf[0], dj * f.ejf[0]), fmaf(dk, f.ekf[1], dj * f.ejf[1]),
+                                        fmaf(dk, f.ekf[2], dj * f.ejf[2])};
+                    wt = ray_weight<false>(P, tent);
+                }
+                if (!(wt > 0.0f)) continue;
+                const float *ray = yf + (((long long)s * nj + j) * nk + k) * UP;
+#pragma unroll
+                for (int u = 0; u < UP; ++u) q[u] = fmaf(wt, ray[u], q[u]);
+            }
+#pragma unroll
+        for (int u = 0; u < UP; ++u)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                const float *row = Bu + ((long long)s * UP + u) * Cp + mt * 16;
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    sum[mt][r] = BF16 ? fmaf(bf16_value(row[r]), bf16_value(q[u]), sum[mt][r])
+                                      : fmaf(row[r], q[u], sum[mt][r]);
+            }
+    }
+}
+
+// Copies of 128 float4 per window and pair (at most; window_lds has the sizes)
+template <int UP, bool PAIR>
+constexpr int kWinCopies = UP == 4 ? (PAIR ? 4 : 2) : (PAIR ? 6 : 4);
 
 template <int UP, int MT, bool BF16, bool JOS, bool PAIR, int PB = kPairs<UP, MT>, bool MANY = false>
 __global__ __launch_bounds__(256, (kAdjointWaves<UP, MT, BF16, JOS, PAIR, PB>)) void k_backproject_win(const float *__restrict__ yf,
                                                          const ProjFrame *__restrict__ frames,
-                                                         const uint4 *__restrict__ Bop, int S, int nx, int ny, int nz,
+                                                         const uint4 *__restrict__ Bop, const float *__restrict__ Bu,
+                                                         int S, int nx, int ny, int nz,
                                                          int nj, int nk, int C, int Cp, float step,
                                                          float *__restrict__ g, float beta, const float *__restrict__ c,
                                                          double *__restrict__ partials, int WR, int WC, int s_per,
@@ -1927,9 +1989,9 @@ __global__ __launch_bounds__(256, (kAdjointWaves<UP, MT, BF16, JOS, PAIR, PB>)) 
     // of the window origin.  Elements past the window repeat its last ray.
     const int nel = WR * WC * RW, wsz = (nel + 127) & ~127;
     const bool refl = PAIR && (lane & (RW - 1)) >= Q;
-    unsigned soff[kWinCopies];
+    unsigned soff[kWinCopies<UP, PAIR>];
 #pragma unroll
-    for (int i = 0; i < kWinCopies; ++i) {
+    for (int i = 0; i < kWinCopies<UP, PAIR>; ++i) {
         const int e = (2 * i + (wave & 1)) * 64 + lane;
         const int ray = min(e / RW, WR * WC - 1), part = lane & (RW - 1);
         const int r = ray / WC, rel = r * nk + (ray - r * WC);
@@ -1941,7 +2003,7 @@ __global__ __launch_bounds__(256, (kAdjointWaves<UP, MT, BF16, JOS, PAIR, PB>)) 
         const unsigned d = refl ? -(unsigned)o : (unsigned)o;
         f4 *dst = wins + grp * wsz + (wave & 1) * 64;
 #pragma unroll
-        for (int i = 0; i < kWinCopies; ++i)
+        for (int i = 0; i < kWinCopies<UP, PAIR>; ++i)
             if (i * 128 < nel)
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + (soff[i] + d)),
                                                  (__attribute__((address_space(3))) void *)(dst + i * 128), 16, 0, 0);
@@ -2127,6 +2189,50 @@ __global__ __launch_bounds__(256, (kAdjointWaves<UP, MT, BF16, JOS, PAIR, PB>)) 
         }
     }
 
+    // What the pieces cannot hold: from the largest bf16 on the first one is infinite and
+    // the next NaN (in the bf16 tier, an infinite Q times the operands' padding), and below
+    // 2^-110 the third one loses bits (relative error at residuals around 2^-116 2e-6,
+    // around 2^-124 5e-4).  Sums that are NaN, or so small that each of their up to 2^12 terms
+    // may be, are taken again in float32: an infinite residual gives an infinite gradient,
+    // and no sum is less exact than in float32.
+    // (By voxel, as a NaN is in all its coefficients; but with 48 of them and four segments
+    // the maximum costs the trilinear kernel a spill, 2.22 -> 2.35 ms at 100^3 / 240.)
+    constexpr bool by_element = MT >= 3 && !JOS;
+    unsigned again = 0;
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+        float most = 0.0f;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float v = acc[mt][nt][r];
+                if constexpr (by_element) {
+                    if (v != v || (!BF16 && v != 0.0f && fabsf(v) < 0x1p-98f)) again |= 1u << nt;
+                } else {
+                    most = fmaxf(most, fabsf(v));
+                }
+            }
+        const float first = acc[0][nt][0];
+        if (!by_element && (first != first || (!BF16 && most > 0.0f && most < 0x1p-98f))) again |= 1u << nt;
+    }
+    if (__builtin_expect(__any(again != 0), 0)) {
+#pragma unroll 1
+        for (int nt = 0; nt < 4; ++nt) {
+            if (!(again >> nt & 1)) continue;
+            const int qx = x0 + nt, qy = y0 + ((lane >> 2) & 3), qz = z0 + (lane & 3);
+            f4 sum[MT];
+            sum_in_f32<UP, MT, BF16, JOS>(yf, frames, Bu + 4 * (lane >> 4), s_begin, s_end, nj, nk, Cp, step,
+                                          (upper ? nx - 1 - qx : qx) - 0.5 * (nx - 1),
+                                          (upper ? ny - 1 - qy : qy) - 0.5 * (ny - 1),
+                                          (upper ? nz - 1 - qz : qz) - 0.5 * (nz - 1), sum);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) acc[mt][t] = t == nt ? sum[mt] : acc[mt][t];
+        }
+    }
+
     if (split) {
         g = split + (long long)blockIdx.y * nx * ny * nz * C;
         c = nullptr;
@@ -2235,7 +2341,9 @@ static int window_lds(const std::vector<ProjFrame> &frames, const Dims &d, bool 
     if (d.Up > 8) return 0;
     const int nel = (wr * wc * (d.Up / 4) * (pair ? 2 : 1) + 127) & ~127;
     const int fixed = (d.Up == 8 ? 3 : d.Cp >= 48 ? 4 : 2) * 8192 + 2048;
-    return nel <= kWinCopies * 128 && 2 * nel * 16 + fixed <= 53 * 1024 ? 2 * nel * 16 : 0;
+    const int copies = d.Up == 4 ? (pair ? kWinCopies<4, true> : kWinCopies<4, false>)
+                                 : (pair ? kWinCopies<8, true> : kWinCopies<8, false>);
+    return nel <= copies * 128 && 2 * nel * 16 + fixed <= 53 * 1024 ? 2 * nel * 16 : 0;
 }
 
 static int win_blocks(const Dims &d, bool pair)
@@ -2304,8 +2412,8 @@ static hipError_t bp_launch(const Dims &d, const ProjFrame *frames, const float 
         const dim3 grid(nb, (d.S + s_per - 1) / s_per);
         float *sp = grid.y > 1 ? split : nullptr;
         auto launch = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, grid, dim3(256), p.lds, st, yf, frames, bop, d.S, d.nx, d.ny, d.nz, d.nj, d.nk,
-                               d.C, d.Cp, d.step, g, beta, c, partials, p.wr, p.wc, s_per, sp);
+            hipLaunchKernelGGL(kernel, grid, dim3(256), p.lds, st, yf, frames, bop, t.Bu, d.S, d.nx, d.ny, d.nz, d.nj,
+                               d.nk, d.C, d.Cp, d.step, g, beta, c, partials, p.wr, p.wc, s_per, sp);
         };
         // (the bf16 Joseph kernel runs four waves with two pairs as well)
         constexpr int unpaired_pb = UP == 4 && MT == 3 && !(BF16 && JOS) ? 1 : kPairs<UP, MT>;
