@@ -63,6 +63,7 @@ struct tt_ctx {
     float *d_M = nullptr;       // [pb][vol_pad][Up], zero border
     float *d_cT = nullptr;      // [C][V] channel-major copy of c (fused sparse forward only)
     float *d_split = nullptr;   // coefficient volumes of the adjoint's splits (null: none)
+    bool exact = true;          // the constants and tables are those of the exact map
     size_t table_bytes = 0;
     bool timing = false;
     struct Mark {
@@ -497,12 +498,13 @@ int tt_set_sparse_map(tt_ctx *c, int k)
     if (!c) return fail(TT_EINVAL, "ctx is null");
     if (k < 0) return fail(TT_EINVAL, "k must be >= 0");
     const Dims &d = c->d;
-    if (k == 0 && d.sparse_k == 0) return TT_OK;  // the tables hold the exact constants
+    if (k == 0 && d.sparse_k == 0 && c->exact) return TT_OK;
     if (k > 0 && c->precision == TT_MAP_BF16) return fail(TT_EUNSUPPORTED, "the sparse fused map runs in float32 only");
     const int kk = std::min(k, d.C);
     std::vector<int2> sp;
     std::vector<int> gtab;
     int ng = 0;
+    c->exact = false;  // until all tables are uploaded
     if (k == 0) {
         c->B = c->B_exact;
     } else {
@@ -560,6 +562,7 @@ int tt_set_sparse_map(tt_ctx *c, int k)
     if (!t.bop.empty()) TT_HIP(hipMemcpy(c->d_Bop, t.bop.data(), t.bop.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
     if (!sp.empty()) TT_HIP(hipMemcpy(c->d_sp, sp.data(), sp.size() * sizeof(int2), hipMemcpyHostToDevice));
     if (!gtab.empty()) TT_HIP(hipMemcpy(c->d_gtab, gtab.data(), gtab.size() * sizeof(int), hipMemcpyHostToDevice));
+    c->exact = k == 0;
     const bool was_fused = c->d.sparse_k > 0;
     c->d.sparse_k = k == 0 ? 0 : kk;
     c->d.sparse_ng = ng;
