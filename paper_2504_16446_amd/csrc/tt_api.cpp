@@ -63,6 +63,7 @@ struct tt_ctx {
     float *d_M = nullptr;       // [pb][vol_pad][Up], zero border
     float *d_cT = nullptr;      // [C][V] channel-major copy of c (fused sparse forward only)
     float *d_split = nullptr;   // coefficient volumes of the adjoint's splits (null: none)
+    std::vector<int> ring_sums; // of d
     bool exact = true;          // the constants and tables are those of the exact map
     size_t table_bytes = 0;
     bool timing = false;
@@ -395,7 +396,8 @@ int tt_create(const tt_geometry *geom, tt_ctx **out)
     // blocks per CU), 76 KiB for more (two blocks per CU); measured best of
     // 20-76 KiB on 100^3 x 4 and of 32-76 KiB on 128^3 and 256^3 x 8
     d.march_lds = plan_slabs(c->frames, d.Up, (d.Up == 4 ? 52 : 76) * 1024);
-    plan_rings(c->frames, g, d.Up, d.ring_lds, d.ring_all);
+    plan_rings(c->frames, g, d.Up, d.ring_lds, c->ring_sums);
+    d.ring_sums = c->ring_sums.data();
     plan_adjoint(c->frames, d);
 
     if (hipGetDevice(&c->device) != hipSuccess) {

@@ -295,41 +295,29 @@ int plan_slabs(std::vector<ProjFrame> &frames, int up, int lds_budget)
 //
 // A ring is 3 planes or more (a step then waits for a copy issued one step before) in
 // 79 KiB or less, two blocks per compute unit: larger ones, with one block, are slower
-// than slabs (256^3 x 8 unique segments: march 115 ms against 73).  Grids of at most one
-// block per compute unit take its whole LDS.  Steep projections, whose planes are larger,
-// stay on slabs.
+// than slabs (256^3 x 8 unique segments: march 115 ms against 73), except in grids of at
+// most one block per compute unit, which take its whole LDS.  Steep projections, whose
+// planes are larger, stay on slabs.
 //
 // What bounds the march of a full chip is the number of blocks that hide each other's
-// waits, so rings go into two launches by LDS size where both fill the chip several
-// times.  March in ms with rings of
+// waits, so there rings go into two launches by LDS size.  March in ms with rings of
 //             39 + 53    53    53 + 79   39 KiB   slabs only
-//   100^3 x 4   1.37    1.48     1.48     1.45     1.59   (8820 blocks)
-//   128^3 x 8   6.81    6.97     6.38     7.43     7.71   (14400)
-//   256^3 x 8   67.4    67.1     62.1     70.7     73.1   (76800)
-// and with few blocks a second launch, of rings or slabs, only adds its own length:
-//                            one launch   two    slabs only
-//   32^3 x 4   (180 blocks)     0.043    0.081     0.062
-//   48^3 x 4   (1440)           0.182    0.206     0.200
-//   80^3 x 4   (5000)           -        0.836     0.760  (steep ones on slabs)
-//   32^3 x 8   (240)            -        0.141     0.090  (steep ones on slabs)
-//   64^3 x 8   (1920)           -        0.614     0.561  (steep ones on slabs)
-//   90^3 x 4   (8640)           -        1.03      1.18   (39 + 53 + slabs)
-// hence below kTwoLaunches one launch of rings, or of slabs where a projection needs them.
-void plan_rings(std::vector<ProjFrame> &frames, const Geometry &g, int up, int *lds, int &all)
+//   100^3 x 4   1.37    1.48     1.48     1.45     1.59   (240 projections, 11760 blocks)
+//   128^3 x 8   6.81    6.97     6.38     7.43     7.71   (300 projections, 19200)
+//   256^3 x 8   67.4    67.1     62.1     70.7     73.1   (400 projections, 102400)
+// march_t chooses the launches by the blocks of one forward batch.
+void plan_rings(std::vector<ProjFrame> &frames, const Geometry &g, int up, int *lds, std::vector<int> &sums)
 {
     constexpr int kMaxRing = 8, kMinRing = 3, kMaxElems = 8 * 256;  // elements: the kernel's copies per plane
-    constexpr long long kTwoLaunches = 8192, kCUs = 256;  // blocks
-    const long long tiles = (long long)((g.nj + kMarchTile - 1) / kMarchTile) * ((g.nk + kMarchTile - 1) / kMarchTile);
-    const long long blocks = tiles * (long long)frames.size();
-    const bool two = blocks >= kTwoLaunches;
-    const int most = (blocks <= kCUs ? 159 : up == 4 ? 53 : 79) * 1024;
-    const int budget[kRingClasses] = {two ? (up == 4 ? 39 : 53) * 1024 : most, most};
-    for (int c = 0; c < kRingClasses; ++c) lds[c] = 0;
+    const int S = (int)frames.size(), large = (up == 4 ? 53 : 79) * 1024, small = (up == 4 ? 39 : 53) * 1024;
+    for (int k = 0; k < kRingLaunches; ++k) lds[k] = 0;
+    sums.assign((size_t)kRingLaunches * (S + 1), 0);
     const double T = kMarchTile - 1;
-    all = 1;
-    for (ProjFrame &f : frames) {
+    for (int s = 0; s < S; ++s) {
+        ProjFrame &f = frames[s];
         const int A = f.slab_a, B = 1 - A;
-        f.ring_r = f.ring_eb = f.ring_ez = f.ring_c = 0;
+        f.ring_eb = f.ring_ez = 0;
+        for (int k = 0; k < kRingLaunches; ++k) f.ring_r[k] = 0;
         if (up <= 8 && std::fabs(f.d[A]) >= 0.25) {
             double lo[2] = {1e300, 1e300}, hi[2] = {-1e300, -1e300};
             for (int v = 0; v < 8; ++v) {
@@ -345,21 +333,24 @@ void plan_rings(std::vector<ProjFrame> &frames, const Geometry &g, int up, int *
             const int elems = (eb * ez * (up / 4) + 63) / 64 * 64;
             // 32-bit byte offsets inside a plane of either axis
             const bool near = (long long)(std::max(g.nx, g.ny) + 2) * (g.ny + 2) * (g.nz + 2) * up * 4 < 1LL << 31;
-            for (int c = 0; c < kRingClasses && near && elems <= kMaxElems && f.ring_r == 0; ++c) {
-                const int r = std::min(kMaxRing, budget[c] / (elems * 16));
-                if (r < kMinRing) continue;
-                f.ring_r = r;
-                f.ring_c = c;
+            if (near && elems <= kMaxElems) {
+                auto planes = [&](int budget) {
+                    const int r = std::min(kMaxRing, budget / (elems * 16));
+                    return r < kMinRing ? 0 : r;
+                };
                 f.ring_eb = eb;
                 f.ring_ez = ez;
-                lds[c] = std::max(lds[c], r * elems * 16);
+                f.ring_r[kRingWhole] = planes(159 * 1024);
+                f.ring_r[kRingOne] = planes(large);
+                f.ring_r[kRingSmall] = planes(small);
+                f.ring_r[kRingLarge] = f.ring_r[kRingSmall] ? 0 : f.ring_r[kRingOne];
+                for (int k = 0; k < kRingLaunches; ++k) lds[k] = std::max(lds[k], f.ring_r[k] * elems * 16);
             }
         }
-        if (f.ring_r == 0) all = 0;
-    }
-    if (!all && !two) {
-        for (ProjFrame &f : frames) f.ring_r = 0;
-        for (int c = 0; c < kRingClasses; ++c) lds[c] = 0;
+        for (int k = 0; k < kRingLaunches; ++k) {
+            int *sum = &sums[(size_t)k * (S + 1)];
+            sum[s + 1] = sum[s] + (f.ring_r[k] > 0);
+        }
     }
 }
 

@@ -28,6 +28,10 @@ int basis_count(const Geometry &g);
 // Stand-in for 1 / 0 in branch-free parameter ranges (see ProjFrame::jos_igk).
 constexpr float kFlatInv = 1.0e30f;
 
+// Launches of the ring march: alone with a compute unit's whole LDS, alone with the
+// larger of two budgets, and the two classes of projections by LDS size.
+enum { kRingWhole, kRingOne, kRingSmall, kRingLarge, kRingLaunches };
+
 // Ray frame of one projection, float64, in centred sample coordinates.
 // The ray through pixel (j, k) is o + j e_j + k e_k + t d.
 struct ProjFrame {
@@ -53,13 +57,11 @@ struct ProjFrame {
     // voxels that contains every corner those samples touch.  slab_w = 0:
     // the projection's rays gather from global memory instead.
     int slab_a, slab_w, slab_eb, slab_ez;
-    // Ring plan of the march over single planes of axis slab_a: ring_r planes are
-    // kept (0: the projection runs on the slab plan), each a box of ring_eb x ring_ez
+    // Ring plan of the march over single planes of axis slab_a: in a launch of the kinds
+    // above ring_r planes are kept (0: not in it), each a box of ring_eb x ring_ez
     // voxels that contains every corner which the tile's samples within one plane
     // of it touch.
-    // The projections are launched in classes of LDS size (ring_c), smaller rings
-    // leaving room for more blocks per compute unit.
-    int ring_r, ring_eb, ring_ez, ring_c;
+    int ring_r[kRingLaunches], ring_eb, ring_ez;
     // Joseph's method: dominant axis A of d (ties within 1e-9 go to the lower
     // axis) and the cut weight 1/|d_A|; for the adjoint, the in-plane offset of
     // a ray's cut from a voxel centre in the voxel's layer is
@@ -77,7 +79,6 @@ struct ProjFrame {
 };
 
 constexpr int kMarchTile = 16;  // rays per tile edge in the forward march
-constexpr int kRingClasses = 2;  // LDS sizes of the ring march
 
 int num_coeffs(int ell_max);
 void sh_eval_one(int ell_max, const double *dir, double *out);
@@ -85,9 +86,10 @@ void build_frames(const Geometry &g, std::vector<ProjFrame> &frames, std::vector
 // Fills the slab plan of every frame for staged voxels of `up` floats within
 // `lds_budget` bytes; returns the largest staging size in bytes (0 if none).
 int plan_slabs(std::vector<ProjFrame> &frames, int up, int lds_budget);
-// Fills the ring plan (after plan_slabs) for up <= 8, the dynamic LDS bytes of each
-// class (0: empty), and in `all` whether every projection has a ring.
-void plan_rings(std::vector<ProjFrame> &frames, const Geometry &g, int up, int *lds, int &all);
+// Fills the ring plan (after plan_slabs) for up <= 8, the dynamic LDS bytes of each kind
+// of launch, and for each kind the number of projections in it before projection s
+// (sums, [kRingLaunches][S + 1]).
+void plan_rings(std::vector<ProjFrame> &frames, const Geometry &g, int up, int *lds, std::vector<int> &sums);
 
 // ---------------------------------------------------------------------------
 // Kernel launchers (tt_proj.hip, tt_vec.hip).  All asynchronous on `st`.
@@ -109,7 +111,8 @@ struct Dims {
     int nseg, U, Up;    // segments, unique segments, padded unique segments
     float step;         // sample spacing of the trilinear model (1 for Joseph: no step factor)
     int march_lds;      // dynamic LDS bytes of the slab march (0: no projection staged)
-    int ring_lds[kRingClasses], ring_all;  // dynamic LDS bytes of the ring march's classes (0: empty); 1: it runs every projection
+    int ring_lds[kRingLaunches];  // dynamic LDS bytes of the ring march's launches
+    const int *ring_sums;         // projections in each kind of launch before projection s: [kRingLaunches][S + 1]
     int joseph;         // 0: unit-step trilinear samples, 1: Joseph's method
     int inv_pair;       // 1: point-inversion-symmetric geometry (no detector offsets, even nx): the
                         //    adjoint (either model) enumerates each voxel pair (v, -v) once

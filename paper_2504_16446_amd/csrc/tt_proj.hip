@@ -667,7 +667,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((UP == 4 &&
                                                float step, long long vol_pad, float *__restrict__ I,
                                                const int2 *__restrict__ sp, int kk, int C,
                                                const float *__restrict__ cT, const int *__restrict__ gtab, int ng,
-                                               int jos)
+                                               int jos, int rings)
 {
     constexpr int Q = UP / 4;      // float4 per staged voxel
     // FUSED: the map table int2[UP][kk] (global-memory gathers), the channel
@@ -684,7 +684,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((UP == 4 &&
     const int k = tk * kMarchTile + (threadIdx.x / kMarchTile);
     const bool live = j < nj && k < nk;
     const ProjFrame &f = frames[s];
-    if (!FUSED && f.ring_r > 0) return;  // this projection runs in k_march_ring
+    if (!FUSED && rings && f.ring_r[kRingOne] > 0) return;  // this projection runs in k_march_ring
     const float *Mp = FUSED ? M : M + (long long)p * vol_pad * UP;
     int2 *tab = reinterpret_cast<int2 *>(lds);
     int *gch = reinterpret_cast<int *>(lds + (UP * kk * 8 + 15) / 16);  // [ng] channels, then [ng][UP] constants
@@ -1053,7 +1053,7 @@ template <int UP>
 __global__ __launch_bounds__(256) void k_march_ring(const float *__restrict__ M, const ProjFrame *__restrict__ frames,
                                                     int s0, int nx, int ny, int nz, int nj, int nk, int nseg, int U,
                                                     float step, long long vol_pad, float *__restrict__ I, int jos,
-                                                    int cls)
+                                                    int kind)
 {
     constexpr int Q = UP / 4;
     extern __shared__ f4 ring[];  // [R][Q][plane voxel]
@@ -1062,8 +1062,8 @@ __global__ __launch_bounds__(256) void k_march_ring(const float *__restrict__ M,
     const int lb = blockIdx.x;
     const int p = lb / (ntj * ntk), s = s0 + p;
     const ProjFrame &f = frames[s];
-    const int R = f.ring_r;
-    if (R == 0 || f.ring_c != cls) return;  // this projection runs in k_march, or in the launch of its class
+    const int R = f.ring_r[kind];
+    if (R == 0) return;  // this projection runs in another launch
     const int tj = (lb / ntk) % ntj, tk = lb % ntk;
     const int j = tj * kMarchTile + (threadIdx.x % kMarchTile);
     const int k = tk * kMarchTile + (threadIdx.x / kMarchTile);
@@ -1236,24 +1236,62 @@ __global__ __launch_bounds__(256) void k_march_ring(const float *__restrict__ M,
     }
 }
 
+// Launches of one forward batch.  A second one, of rings or slabs, runs after the first
+// and adds its own length, so it needs blocks enough that this is less than what smaller
+// rings gain; below, one launch of rings, or of slabs where a projection has no ring.
+// March of all batches in ms (in brackets, projections in random order, so that every
+// batch has all kinds):
+//                                      one launch        two           slabs only
+//   128^3 x 8  300 projections, 512 blocks     8.50 (10.7)  12.1 (19.3)  10.4 (12.3)
+//                                    2048      8.08 (8.80)  8.67 (10.3)  8.73 (9.09)
+//                                    4096      7.70 (8.34)  7.44 (8.28)  8.13 (8.35)
+//                                    6144      7.59 (8.12)  7.13 (7.74)  8.01 (8.15)
+//   200^3 x 8  120,                  2704      11.2 (11.3)  11.1 (12.1)  11.7 (11.7)
+//                                    5408      10.8 (10.7)  9.73 (10.1)  11.0 (11.0)
+//   64^3 x 8   240,                  3840                   0.96 (1.01)  0.97 (1.03)
+//   100^3 x 4  240,                   784      2.13 (2.25)  2.45 (3.12)  2.50 (2.66)
+//                                    3136      1.72 (1.73)  1.77 (1.96)  1.92 (1.93)
+//                                   11760      1.48 (1.49)  1.36 (1.38)  1.61 (1.63)
+//   200^3 x 4  120,                  5408      5.11 (5.08)  4.84 (4.91)  5.59 (5.54)
+//   80^3 x 4   200,                  5000                   0.84 (0.83)  0.76 (0.77)
+//   90^3 x 4   240,                  8640      1.08 (1.09)  1.01 (1.03)  1.18 (1.21)
+// (one launch: slabs in those batches that have a projection without a ring).  Up to one
+// block per compute unit rings take the whole LDS: 64^3 x 8 / 120, 256 blocks 0.96 (0.98)
+// against 0.98 (1.13) on slabs, which its steep projections needed otherwise.
+constexpr unsigned kTwoLaunches = 8192, kUnits = 256;  // blocks
+
 template <int UP>
 static hipError_t march_t(const Dims &d, const ProjFrame *frames, const float *M, int s0, int np, float *I,
                           hipStream_t st)
 {
     const long long vol_pad = (long long)(d.nx + 2) * (d.ny + 2) * (d.nz + 2);
     dim3 grid(((d.nk + kMarchTile - 1) / kMarchTile) * ((d.nj + kMarchTile - 1) / kMarchTile) * np);
+    bool rings = false;  // projections that have a ring run on it
     if constexpr (UP <= 8) {
-        for (int c = 0; c < kRingClasses; ++c)
-            if (d.ring_lds[c] > 0) {
-                hipLaunchKernelGGL((k_march_ring<UP>), grid, dim3(kMarchTile * kMarchTile), d.ring_lds[c], st, M, frames, s0,
-                                   d.nx, d.ny, d.nz, d.nj, d.nk, d.nseg, d.U, d.step, vol_pad, I, d.joseph, c);
-                if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-            }
-        if (d.ring_all) return hipSuccess;
+        auto in = [&](int kind) {  // projections of this batch in a launch
+            const int *sum = d.ring_sums + (size_t)kind * (d.S + 1);
+            return sum[s0 + np] - sum[s0];
+        };
+        auto launch = [&](int kind) {
+            hipLaunchKernelGGL((k_march_ring<UP>), grid, dim3(kMarchTile * kMarchTile), d.ring_lds[kind], st, M, frames, s0,
+                               d.nx, d.ny, d.nz, d.nj, d.nk, d.nseg, d.U, d.step, vol_pad, I, d.joseph, kind);
+            return hipGetLastError();
+        };
+        const int all = in(kRingOne), kinds = (in(kRingSmall) > 0) + (in(kRingLarge) > 0) + (all < np);
+        if (grid.x <= kUnits && in(kRingWhole) == np) return launch(kRingWhole);
+        const bool two = grid.x >= (UP == 8 || kinds == 1 ? kTwoLaunches / 2 : kTwoLaunches);
+        if (!two && all == np) return launch(kRingOne);
+        rings = two && all > 0;
+        if (rings) {
+            for (const int kind : {kRingSmall, kRingLarge})
+                if (in(kind) > 0)
+                    if (hipError_t e = launch(kind); e != hipSuccess) return e;
+            if (all == np) return hipSuccess;
+        }
     }
     hipLaunchKernelGGL((k_march<UP, false>), grid, dim3(kMarchTile * kMarchTile), d.march_lds, st, M, frames, s0,
                        d.nx, d.ny, d.nz, d.nj, d.nk, d.nseg, d.U, d.step, vol_pad, I, nullptr, 0, 0, nullptr, nullptr, 0,
-                       d.joseph);
+                       d.joseph, (int)rings);
     return hipGetLastError();
 }
 
@@ -1270,15 +1308,15 @@ static hipError_t march_fused_t(const Dims &d, const ProjFrame *frames, const fl
     if (cT && d.sparse_ng > 16)
         hipLaunchKernelGGL((k_march<UP, true, 32>), grid, dim3(kMarchTile * kMarchTile), lds, st, c, frames, 0, d.nx,
                            d.ny, d.nz, d.nj, d.nk, d.nseg, d.U, d.step, 0LL, I, sp, d.sparse_k, d.C, cT, gtab,
-                           d.sparse_ng, d.joseph);
+                           d.sparse_ng, d.joseph, 0);
     else if (cT && d.sparse_ng > 8)
         hipLaunchKernelGGL((k_march<UP, true, 16>), grid, dim3(kMarchTile * kMarchTile), lds, st, c, frames, 0, d.nx,
                            d.ny, d.nz, d.nj, d.nk, d.nseg, d.U, d.step, 0LL, I, sp, d.sparse_k, d.C, cT, gtab,
-                           d.sparse_ng, d.joseph);
+                           d.sparse_ng, d.joseph, 0);
     else
         hipLaunchKernelGGL((k_march<UP, true, 8>), grid, dim3(kMarchTile * kMarchTile), lds, st, c, frames, 0, d.nx,
                            d.ny, d.nz, d.nj, d.nk, d.nseg, d.U, d.step, 0LL, I, sp, d.sparse_k, d.C, cT, gtab,
-                           d.sparse_ng, d.joseph);
+                           d.sparse_ng, d.joseph, 0);
     return hipGetLastError();
 }
 
