@@ -305,10 +305,18 @@ int plan_slabs(std::vector<ProjFrame> &frames, int up, int lds_budget)
 //   100^3 x 4   1.37    1.48     1.48     1.45     1.59   (240 projections, 11760 blocks)
 //   128^3 x 8   6.81    6.97     6.38     7.43     7.71   (300 projections, 19200)
 //   256^3 x 8   67.4    67.1     62.1     70.7     73.1   (400 projections, 102400)
-// march_t chooses the launches by the blocks of one forward batch.
+// (march_t chooses one launch or two by the blocks of a forward batch).  In a small grid a
+// launch of slabs beside the rings only adds its own length, so there all projections stay
+// on slabs if one has to (ms, one launch and rings beside slabs):
+//   80^3 x 4   200 projections, 5000 blocks  0.76  0.84
+//   64^3 x 8   120,             1920         0.56  0.61
+//   32^3 x 8    60,              240         0.090 0.141
+//   90^3 x 4   240,             8640         1.18  1.03
 void plan_rings(std::vector<ProjFrame> &frames, const Geometry &g, int up, int *lds, std::vector<int> &sums)
 {
     constexpr int kMaxRing = 8, kMinRing = 3, kMaxElems = 8 * 256;  // elements: the kernel's copies per plane
+    constexpr long long kUnits = 256, kMixed = 8192;  // blocks
+    const long long tiles = (long long)((g.nj + kMarchTile - 1) / kMarchTile) * ((g.nk + kMarchTile - 1) / kMarchTile);
     const int S = (int)frames.size(), large = (up == 4 ? 53 : 79) * 1024, small = (up == 4 ? 39 : 53) * 1024;
     for (int k = 0; k < kRingLaunches; ++k) lds[k] = 0;
     sums.assign((size_t)kRingLaunches * (S + 1), 0);
@@ -344,14 +352,21 @@ void plan_rings(std::vector<ProjFrame> &frames, const Geometry &g, int up, int *
                 f.ring_r[kRingOne] = planes(large);
                 f.ring_r[kRingSmall] = planes(small);
                 f.ring_r[kRingLarge] = f.ring_r[kRingSmall] ? 0 : f.ring_r[kRingOne];
-                for (int k = 0; k < kRingLaunches; ++k) lds[k] = std::max(lds[k], f.ring_r[k] * elems * 16);
             }
         }
+    }
+    auto all = [&](int kind) {
+        return std::all_of(frames.begin(), frames.end(), [&](const ProjFrame &f) { return f.ring_r[kind] > 0; });
+    };
+    const bool whole = tiles * S <= kUnits && all(kRingWhole), rings = !whole && (tiles * S >= kMixed || all(kRingOne));
+    for (int s = 0; s < S; ++s)
         for (int k = 0; k < kRingLaunches; ++k) {
+            ProjFrame &f = frames[s];
+            if (k == kRingWhole ? !whole : !rings) f.ring_r[k] = 0;
+            lds[k] = std::max(lds[k], f.ring_r[k] * ((f.ring_eb * f.ring_ez * (up / 4) + 63) / 64 * 64) * 16);
             int *sum = &sums[(size_t)k * (S + 1)];
             sum[s + 1] = sum[s] + (f.ring_r[k] > 0);
         }
-    }
 }
 
 }  // namespace tt

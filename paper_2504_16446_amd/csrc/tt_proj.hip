@@ -1236,30 +1236,26 @@ __global__ __launch_bounds__(256) void k_march_ring(const float *__restrict__ M,
     }
 }
 
-// Launches of one forward batch.  A second one, of rings or slabs, runs after the first
-// and adds its own length, so it needs blocks enough that this is less than what smaller
-// rings gain; below, one launch of rings, or of slabs where a projection has no ring.
-// March of all batches in ms (in brackets, projections in random order, so that every
-// batch has all kinds):
-//                                      one launch        two           slabs only
-//   128^3 x 8  300 projections, 512 blocks     8.50 (10.7)  12.1 (19.3)  10.4 (12.3)
-//                                    2048      8.08 (8.80)  8.67 (10.3)  8.73 (9.09)
-//                                    4096      7.70 (8.34)  7.44 (8.28)  8.13 (8.35)
-//                                    6144      7.59 (8.12)  7.13 (7.74)  8.01 (8.15)
-//   200^3 x 8  120,                  2704      11.2 (11.3)  11.1 (12.1)  11.7 (11.7)
-//                                    5408      10.8 (10.7)  9.73 (10.1)  11.0 (11.0)
-//   64^3 x 8   240,                  3840                   0.96 (1.01)  0.97 (1.03)
-//   100^3 x 4  240,                   784      2.13 (2.25)  2.45 (3.12)  2.50 (2.66)
-//                                    3136      1.72 (1.73)  1.77 (1.96)  1.92 (1.93)
-//                                   11760      1.48 (1.49)  1.36 (1.38)  1.61 (1.63)
-//   200^3 x 4  120,                  5408      5.11 (5.08)  4.84 (4.91)  5.59 (5.54)
-//   80^3 x 4   200,                  5000                   0.84 (0.83)  0.76 (0.77)
-//   90^3 x 4   240,                  8640      1.08 (1.09)  1.01 (1.03)  1.18 (1.21)
-// (one launch: slabs in those batches that have a projection without a ring).  Up to one
-// block per compute unit rings take the whole LDS: 64^3 x 8 / 120, 256 blocks 0.96 (0.98)
-// against 0.98 (1.13) on slabs, which its steep projections needed otherwise.
-constexpr unsigned kTwoLaunches = 8192, kUnits = 256;  // blocks
-
+// Which projections run on rings is the geometry's (plan_rings), so that the forward batch
+// changes no result; in how many launches they do is the batch's.  Two, by LDS size, need
+// blocks enough that the second one's length is less than what the smaller rings gain.
+// March of all batches in ms, rings in one launch and in two, beside a launch of slabs in
+// batches that have a projection without a ring (in brackets, projections in random order,
+// so that every batch has all kinds):
+//                            blocks    one          two          slabs only
+//   128^3 x 8 / 300 projections 512    9.28 (13.4)  12.1 (19.3)  10.5 (12.3)
+//                              2048    8.18 (9.73)  8.69 (10.4)  8.79 (9.06)
+//                              4096    7.58 (8.39)  7.41 (8.26)  8.14 (8.35)
+//                              6144    7.32 (8.04)  7.17 (7.74)  8.02 (8.14)
+//   200^3 x 8 / 120            2704    11.0 (11.9)  11.1 (12.1)  11.7 (11.7)
+//                              5408    10.2 (10.4)  9.72 (10.0)  11.0 (11.0)
+//   100^3 x 4 / 240             784    2.12 (2.25)  2.45 (3.12)  2.49 (2.65)
+//                              3136    1.73 (1.72)  1.76 (1.96)  1.92 (1.91)
+//                             11760    1.46 (1.49)  1.37 (1.37)  1.60 (1.63)
+//   200^3 x 4 / 120            5408    5.08 (5.09)  4.81 (4.91)  5.58 (5.54)
+//   90^3 x 4 / 240             8640    1.08 (1.09)  1.02 (1.03)  1.18 (1.21)
+// (With four segments from 4096 blocks on only where a batch has one kind of projection,
+// which then is one launch.)
 template <int UP>
 static hipError_t march_t(const Dims &d, const ProjFrame *frames, const float *M, int s0, int np, float *I,
                           hipStream_t st)
@@ -1278,16 +1274,13 @@ static hipError_t march_t(const Dims &d, const ProjFrame *frames, const float *M
             return hipGetLastError();
         };
         const int all = in(kRingOne), kinds = (in(kRingSmall) > 0) + (in(kRingLarge) > 0) + (all < np);
-        if (grid.x <= kUnits && in(kRingWhole) == np) return launch(kRingWhole);
-        const bool two = grid.x >= (UP == 8 || kinds == 1 ? kTwoLaunches / 2 : kTwoLaunches);
-        if (!two && all == np) return launch(kRingOne);
-        rings = two && all > 0;
-        if (rings) {
-            for (const int kind : {kRingSmall, kRingLarge})
-                if (in(kind) > 0)
-                    if (hipError_t e = launch(kind); e != hipSuccess) return e;
-            if (all == np) return hipSuccess;
-        }
+        if (in(kRingWhole) == np) return launch(kRingWhole);
+        const bool two = grid.x >= (UP == 8 || kinds == 1 ? 4096 : 8192);
+        rings = all > 0;
+        for (const int kind : {kRingOne, kRingSmall, kRingLarge})
+            if (two == (kind != kRingOne) && in(kind) > 0)
+                if (hipError_t e = launch(kind); e != hipSuccess) return e;
+        if (all == np) return hipSuccess;
     }
     hipLaunchKernelGGL((k_march<UP, false>), grid, dim3(kMarchTile * kMarchTile), d.march_lds, st, M, frames, s0,
                        d.nx, d.ny, d.nz, d.nj, d.nk, d.nseg, d.U, d.step, vol_pad, I, nullptr, 0, 0, nullptr, nullptr, 0,

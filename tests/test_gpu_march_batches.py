@@ -50,3 +50,16 @@ def test_forward(name, model):
     got = P.forward(torch.from_numpy(c).cuda(), out=out).cpu().numpy()
     assert not np.isnan(got).any()
     assert rel_l2(got, oracle.project(og, c.astype(np.float64))) <= TOL
+
+
+@pytest.mark.parametrize("n_seg", [8, 16])
+@pytest.mark.parametrize("tilts, det", [((0.0, 15.0, 45.0), 112), ((0.0, 15.0, 45.0), 40), ((0.0, 20.0, 30.0), 16)])
+def test_the_forward_batch_changes_no_result(tilts, det, n_seg):
+    inner, outer = tilted_angles(30, tilts, span_deg=360.0)
+    og = oracle.Geometry((24, 22, 20), 4, inner, outer, det, det, n_seg, synth.lab_frame())
+    c = torch.from_numpy(np.random.default_rng(9).standard_normal(og.vol_shape).astype(np.float32)).cuda()
+    want = gpu_projector(og, device="cuda:0").forward(c)
+    for batch in (4, 16, 32):
+        P = gpu_projector(og, device="cuda:0", forward_batch=batch)
+        assert P.batch == batch
+        assert torch.equal(P.forward(c), want), batch

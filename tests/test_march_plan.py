@@ -33,15 +33,27 @@ FLAT, STEEP, GATHERED = (0.0, 15.0), (0.0, 15.0, 45.0), (0.0, 15.0, 80.0)
 
 
 @pytest.mark.parametrize("n_seg", [8, 16])
-def test_a_small_batch_runs_one_launch(n_seg):
+def test_a_small_batch_runs_its_rings_in_one_launch(n_seg):
     # 49 blocks per projection; the batches of 16 hold 784 blocks, all of them 17640
     batch, seen = _run(24, 112, STEEP, 120, n_seg, 16)
     assert batch == 16 and len(seen) == 23
-    assert all(len(launches) == 1 for launches in seen)
-    kinds = {launches[0][0] for launches in seen}
-    assert "ring" in kinds and (n_seg == 8 or "slab" in kinds)
+    kinds = [[kind for kind, *_ in launches] for launches in seen]
+    assert all(k in (["ring"], ["slab"], ["ring", "slab"]) for k in kinds)
+    assert kinds.count(["ring"]) >= 15 and (n_seg == 8 or ["slab"] in kinds or ["ring", "slab"] in kinds)
     batch, seen = _run(24, 112, STEEP, 120, n_seg, 360)
     assert batch == 360 and len(seen) == 1 and 2 <= len(seen[0]) <= 3
+
+
+@pytest.mark.parametrize("n_seg", [8, 16])
+def test_which_projections_run_on_rings_does_not_depend_on_the_batch(n_seg):
+    # a projection on a ring or on slabs is rounded differently: 360 x 16 blocks, too few for both
+    for batch in (8, 360):
+        _, seen = _run(20, 60, STEEP, 120, 16, batch)
+        assert {kind for launches in seen for kind, *_ in launches} == {"slab"}
+    # and enough
+    for batch in (8, 360):
+        _, seen = _run(24, 112, STEEP, 120, 16, batch)
+        assert {kind for launches in seen for kind, *_ in launches} == {"ring", "slab"}
 
 
 @pytest.mark.parametrize("n_seg, n_rot, launches", [(16, 40, 1), (16, 60, 2), (8, 60, 1), (8, 120, 2)])
