@@ -189,9 +189,14 @@ int tt_sizes(const tt_ctx *ctx, int64_t *out8);
  * channel-major copy of c, nx ny nz C floats; where the adjoint of a small
  * volume is split over the projections, also the splits' sums, up to eight
  * times nx ny nz C floats, without which it runs unsplit).
- * tt_set_workspace attaches caller memory (device, 256-byte aligned) and
- * picks the largest batch that fits; TT_EINVAL below the smallest size (with
- * a sparse map set, below the size without mapped volumes).  The
+ * tt_set_workspace attaches caller memory (device, 256-byte aligned).  A size
+ * that tt_workspace_bytes gave is used as it was asked for, that batch with
+ * the splits' sums; in any other size it picks the largest batch that fits,
+ * and room for the splits' sums only where the adjoint gains more by them
+ * than the forward loses by further batches.  TT_EINVAL below the smallest
+ * size (with a sparse map set, below the size without mapped volumes).  The
+ * batch changes no result; with and without splits the adjoint sums in
+ * another order, and its results differ in rounding.  The
  * memory must stay allocated and untouched by the caller while attached; the
  * zero border is written once, on the context's stream.  Calls that compute
  * (tt_project, tt_adjoint, tt_loss_grad, the solver, tt_kappa,

@@ -693,23 +693,44 @@ int64_t tt_workspace_bytes(const tt_ctx *c, int forward_batch)
     return (int64_t)ws_layout(c, pb).total;
 }
 
+// Forward batch, and whether the adjoint has its splits, in `bytes` of scratch of which
+// `base` are fixed.  A size as tt_workspace_bytes gives it is used as it was asked for: that
+// batch, with splits.  In any other the largest batch comes first, and room for the splits
+// is taken from it only where they save more than the forward's further batches cost:
+// each about 40 us (8 to 57: 32^3 / 60 projections / 4 unique segments forward in 1 and 3
+// batches 53 and 149 us, 48^3 / 120 166 and 260, 32^3 / 240 116 and 219 in 1 and 4),
+// against a saving of 30, 11 and 185 us.
+struct Batch {
+    int pb;
+    bool split;
+};
+static Batch choose_batch(const tt_ctx *c, size_t base, size_t bytes, bool fused)
+{
+    const size_t sb = split_bytes(c);
+    auto total = [&](int pb) { return base + align256(c->per_proj * (size_t)pb); };
+    auto fitting = [&](size_t room) {
+        int pb = batch_round_down(c, room > base ? (long long)((room - base) / c->per_proj) : 0);
+        while (pb > 0 && total(pb) > room) pb = batch_round_down(c, pb - 1);  // the alignment gap
+        return pb;
+    };
+    const int whole = fitting(bytes);
+    if (sb == 0 || bytes < base + sb) return {whole, false};
+    const int pb = fitting(bytes - sb);
+    if (fused) return {pb, true};  // it needs no batch
+    if (pb < batch_min(c)) return {whole, false};
+    if (total(pb) + sb == bytes) return {pb, true};
+    const int S = c->d.S, more = (S + pb - 1) / pb - (S + whole - 1) / whole;
+    const double gain = c->d.adj[c->d.joseph].split_gain;
+    return gain >= 40.0 * more ? Batch{pb, true} : Batch{whole, false};
+}
+
 int tt_set_workspace(tt_ctx *c, void *work, size_t bytes)
 {
     if (!c) return fail(TT_EINVAL, "ctx is null");
     if (!work) return fail(TT_EINVAL, "workspace is null");
     if (reinterpret_cast<uintptr_t>(work) % 256) return fail(TT_EINVAL, "workspace must be 256-byte aligned");
-    // with the scratch of the adjoint's splits where that leaves a valid workspace
     const size_t base = ws_layout(c, 0, false).total;
-    auto fitting = [&](size_t fixed) {
-        return batch_round_down(c, bytes > fixed ? (long long)((bytes - fixed) / c->per_proj) : 0);
-    };
-    bool split = split_bytes(c) > 0 && bytes >= base + split_bytes(c);
-    int pb = fitting(split ? base + split_bytes(c) : base);
-    if (split && ws_layout(c, pb, true).total > bytes) pb = batch_round_down(c, pb - 1);  // the alignment gap
-    if (split && pb < batch_min(c) && c->d.sparse_k == 0) {
-        split = false;
-        pb = fitting(base);
-    }
+    auto [pb, split] = choose_batch(c, base, bytes, c->d.sparse_k > 0);
     if (pb < batch_min(c)) {
         if (c->d.sparse_k == 0 || bytes < base)
             return fail(TT_EINVAL, "workspace of " + std::to_string(bytes) + " bytes is below the minimum of " +
@@ -913,12 +934,8 @@ int tt_loss_grad_noalloc(tt_ctx *c, const float *cin, const float *data, const f
     }
     const size_t cap = kStaticScratchBytes;
     const bool fused = c->d.sparse_k > 0;  // the fused forward maps nothing
-    auto fitting = [&](size_t fixed) {
-        return fused ? 0 : batch_round_down(c, cap > fixed ? (long long)((cap - fixed) / c->per_proj) : 0);
-    };
-    int pb = fitting(L.total + split_bytes(c) + 256);  // (with the alignment gap)
-    const bool split = split_bytes(c) > 0 && L.total + split_bytes(c) <= cap && (fused || pb >= batch_min(c));
-    if (!split) pb = fitting(L.total);
+    auto [pb, split] = choose_batch(c, L.total, cap, fused);
+    if (fused) pb = 0;
     if (fused ? L.total > cap : pb < batch_min(c))
         return fail(TT_ENOMEM, "problem needs " +
                                    std::to_string(L.total + (fused ? 0 : c->per_proj * (size_t)batch_min(c))) +

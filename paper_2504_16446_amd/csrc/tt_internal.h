@@ -101,6 +101,7 @@ void plan_rings(std::vector<ProjFrame> &frames, const Geometry &g, int up, int *
 // cube (small steps of the trilinear model).
 struct AdjointPlan {
     int pair, lds, wr, wc, splits, deep, many;
+    double split_gain;  // estimated time that the splits save, us
 };
 constexpr int kMaxSplits = 8;
 

@@ -2332,20 +2332,22 @@ __global__ __launch_bounds__(256) void k_add_splits(const float *__restrict__ sp
 // block and pair of projections.  Adjoint with its fold, unsplit -> split: 32^3 / 60
 // projections / 15 coefficients (128 blocks, six splits) 81 -> 52 us, 48^3 / 120 / 28
 // (432 blocks, three) 180 -> 172 us.
-static int adjoint_splits(const Dims &d, int blocks, int units)
+static int adjoint_splits(const Dims &d, int blocks, int units, double &gain)
 {
     const double vol_us = 4.0 * d.nx * d.ny * d.nz * d.C / 4e6;
     int best = 1;
-    double best_t = 1e300;
+    double best_t = 1e300, whole_t = 0.0;
     for (int ns = 1; ns <= kMaxSplits && (ns == 1 || 8 * ns <= d.S); ++ns) {
         const int n = (int)(((long long)blocks * ns + units - 1) / units), r = n % 3;
         const double work = 3 * (n / 3) + (r == 0 ? 0.0 : r == 1 ? 2.0 : 2.5);
         const double t = 1.2 * 0.5 * d.S / ns * work + (ns > 1 ? 5.0 + (2 * ns + 1) * vol_us : 0.0);
+        if (ns == 1) whole_t = t;
         if (t < 0.97 * best_t) {
             best_t = t;
             best = ns;
         }
     }
+    gain = whole_t - best_t;
     return best;
 }
 
@@ -2409,7 +2411,8 @@ void plan_adjoint(const std::vector<ProjFrame> &frames, Dims &d)
             p.pair = 0;
             p.lds = window_lds(frames, d, false, jos != 0, p.wr, p.wc);
         }
-        p.splits = p.lds > 0 ? adjoint_splits(d, win_blocks(d, p.pair != 0), units) : 1;
+        p.split_gain = 0.0;
+        p.splits = p.lds > 0 ? adjoint_splits(d, win_blocks(d, p.pair != 0), units, p.split_gain) : 1;
         p.many = 0;
         for (const ProjFrame &f : frames)
             if (f.n_tau > kFewSamples) p.many = 1;
