@@ -67,3 +67,24 @@ def test_small_steps_unroll_the_samples_of_a_ray(offsets, n_seg, up, pairs):
     _kernel(names, up, 3, False, False, not offsets, pairs, True)
     names = scenario("test_adjoint_plan", "adjoint_launches", 64, 8, 30, n_seg, "trilinear", offsets, 0.8)
     assert not any("Li1ELb1EEEv" in k or "Li2ELb1EEEv" in k for k in names), names
+
+
+def edge_shape(F, name, ell, n_seg, model):
+    from adjoint_shapes import geometry
+    og = geometry(name, ell, n_seg, model)
+    h = F.create(og, model)
+    F.workspace(h, 1)
+    s = F.sizes(h)
+    rc, seen = F.launches("tt_adjoint", h, F.buffer(4 * s[1]), F.buffer(4 * s[0]), 0.0, None)
+    assert rc == 0
+    return [name for name, *_ in seen]
+
+
+@pytest.mark.parametrize("model", ["trilinear", "joseph"])
+@pytest.mark.parametrize("ell, n_seg, up, mt, pairs", [(4, 8, 4, 1, 1), (8, 8, 4, 3, 2), (8, 16, 8, 3, 1)])
+@pytest.mark.parametrize("name, paired, split", [("paired_129", True, True), ("unpaired_129", False, True),
+                                                 ("offsets_131", False, True), ("one_projection", True, False)])
+def test_edge_shapes_run_what_they_are_for(name, paired, split, ell, n_seg, up, mt, pairs, model):
+    names = scenario("test_adjoint_plan", "edge_shape", name, ell, n_seg, model)
+    _kernel(names, up, mt, False, model == "joseph", paired, pairs)
+    assert any("k_add_splits" in k for k in names) == split
