@@ -557,9 +557,13 @@ __global__ __launch_bounds__(256) void k_tile_blend(const float *__restrict__ y,
 
 int grid_for(long long n) { return (int)min((n + 255) / 256, 8192LL); }
 
-// Blocks of the 4 x 8 x 8-voxel tile below which the 4 x 4 x 8 one is used: one per
-// compute unit.
-constexpr int kConvWideBlocks = 256;
+// Blocks of the 4 x 8 x 8-voxel tile below which the 4 x 4 x 8 one is used: it has about
+// twice as many, of which three fit a compute unit at once (768), and saves nothing once
+// they need a second round.  Narrow against wide tile, forward 64 -> 64: 54 blocks 12.0 and
+// 18.6 us, 128 12.6 and 19.0, 225 19.3 and 19.3, 396 27.3 and 28.2, 432 36.4 and 32.0, 500
+// 40.0 and 33.1, 1728 121 and 112; 64 -> 32: 225 11.2 and 13.0, 396 16.2 and 17.0, 432 23.1
+// and 18.5; 32 -> 32: 336 9.2 and 10.1, 450 11.6 and 10.5.
+constexpr int kConvWideBlocks = 400;
 
 template <int CI, int CO, int EPI>
 hipError_t conv_t(const u16 *x, const void *wsw, const float *bias, const u16 *mask, void *y, int N, int X, int Y, int Z,
