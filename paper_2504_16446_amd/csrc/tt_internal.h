@@ -96,9 +96,9 @@ void plan_rings(std::vector<ProjFrame> &frames, const Geometry &g, int up, int *
 // ---------------------------------------------------------------------------
 // Staged adjoint of one projector model: point-inversion pairing, dynamic LDS
 // bytes (0 with sixteen unique segments: not used), window rows / columns, splits of the projections over blocks
-// (each needs a coefficient volume of scratch; 1: none), whether the grid is more than
-// three blocks per compute unit, and whether a ray can have many samples in a voxel's
-// cube (small steps of the trilinear model).
+// (each needs a coefficient volume of scratch; 1: none), whether four blocks per compute
+// unit at a time save a round over three (1) or there are many rounds (2), and whether a
+// ray can have many samples in a voxel's cube (small steps of the trilinear model).
 struct AdjointPlan {
     int pair, lds, wr, wc, splits, deep, many;
     double split_gain;  // estimated time that the splits save, us

@@ -1835,11 +1835,6 @@ __device__ __forceinline__ void split_bf16(float a, float b, unsigned &h, unsign
 // one product of four projections, so two pairs share a contraction.
 // It pays from 48 padded coefficients on (fewer MFMAs and adds); below, the smaller
 // tiles leave room for more blocks.
-// It also takes registers (168, three waves per SIMD, with 48), so that unpaired adjoints
-// of 48 coefficients use it only where a grid has no fourth block per compute unit to
-// run: one pair per contraction with four waves, 64^3 / 120 projections with detector
-// offsets (four blocks per unit) 533 -> 407 us, 100^3 / 240 3260 -> 3002 us (Joseph
-// 2232 -> 2020), but 48^3 / 120 (two blocks per unit) 274 -> 286.
 template <int UP, int MT>
 constexpr int kPairs = UP == 4 && MT >= 3 ? 2 : 1;
 template <int UP, bool BF16>
@@ -1877,9 +1872,26 @@ __device__ __forceinline__ void put_q(const float *q, uint4 *t, int stride)
 //    unpaired 1787 -> 1559 us (gathering from memory, without barriers: 1592); paired
 //    100^3 / 240 1204 -> 1090, 128 x 127 x 127 / 300 2757 -> 2546 (72^3 / 160, whose last
 //    blocks then run alone, 331 -> 345).
-template <int UP, int MT, bool BF16, bool JOS, bool PAIR, int PB>
+//  - Three otherwise; four (DEEP) with four segments and 48 coefficients, unpaired, where
+//    four blocks per compute unit at a time save a round, or in many rounds: three waves
+//    -> four, 120 projections with detector offsets, by blocks per unit: 64^3 (4) 534 -> 415
+//    us, Joseph 387 -> 277; 80^3 (8) 821 -> 809, 585 -> 538; 128^3 / 300 (32) 7720 -> 7470,
+//    5375 -> 4927; but 48^3 (2) 274 -> 303, 72^3 (6) 621 -> 675.  The third piece of Q then
+//    has a tile of half the size, as four blocks have 40 KiB of LDS each.  Paired kernels
+//    spill more there and take it only with many samples per ray and a round to save.
+template <int UP, int MT, bool BF16, bool JOS, bool PAIR, bool DEEP>
 constexpr int kAdjointWaves = MT >= 4 ? (UP == 4 && MT == 5 && !BF16 && !JOS && !PAIR ? 1 : 2)
-                                      : UP == 4 && MT == 1 && JOS ? (PAIR ? 5 : 6) : PB < kPairs<UP, MT> ? 4 : 3;
+                                      : UP == 4 && MT == 1 && JOS ? (PAIR ? 5 : 6) : DEEP ? 4 : 3;
+
+// Q for a packed contraction (DEEP): [q0 | q1] and q2
+__device__ __forceinline__ void put_q_packed(const float *q, uint4 *t, uint2 *t2)
+{
+    unsigned h[2], m[2], l[2];
+    split_bf16(q[0], q[1], h[0], m[0], l[0]);
+    split_bf16(q[2], q[3], h[1], m[1], l[1]);
+    *t = make_uint4(h[0], h[1], m[0], m[1]);
+    *t2 = make_uint2(l[0], l[1]);
+}
 
 // sum over projections s0 .. s1 - 1 of B^T Q at one voxel (centred position x, y, z) in
 // float32, four coefficients per 16 of them (Bu: from the first).  For the few sums that
@@ -1942,8 +1954,8 @@ __device__ __forceinline__ void sum_in_f32(const float *yf, const ProjFrame *fra
 template <int UP, bool PAIR>
 constexpr int kWinCopies = UP == 4 ? (PAIR ? 4 : 2) : (PAIR ? 6 : 4);
 
-template <int UP, int MT, bool BF16, bool JOS, bool PAIR, int PB = kPairs<UP, MT>, bool MANY = false>
-__global__ __launch_bounds__(256, (kAdjointWaves<UP, MT, BF16, JOS, PAIR, PB>)) void k_backproject_win(const float *__restrict__ yf,
+template <int UP, int MT, bool BF16, bool JOS, bool PAIR, bool DEEP = false, bool MANY = false>
+__global__ __launch_bounds__(256, (kAdjointWaves<UP, MT, BF16, JOS, PAIR, DEEP>)) void k_backproject_win(const float *__restrict__ yf,
                                                          const ProjFrame *__restrict__ frames,
                                                          const uint4 *__restrict__ Bop, const float *__restrict__ Bu,
                                                          int S, int nx, int ny, int nz,
@@ -1959,8 +1971,12 @@ __global__ __launch_bounds__(256, (kAdjointWaves<UP, MT, BF16, JOS, PAIR, PB>)) 
     constexpr int RW = PAIR ? 2 * Q : Q;    // float4 per staged ray: own, then reflected
     constexpr int QT = kQTiles<UP, BF16>;
     extern __shared__ f4 wins[];            // [2][WR * WC * RW rounded up to 128]
-    constexpr int QS = 2 * PB * 64;         // stride of the operand tiles (PB: pairs per contraction)
-    __shared__ uint4 Qt[4][QT][2 * PB][64];  // [wave][tile][projection][voxel]
+    constexpr int PB = kPairs<UP, MT>;      // pairs per contraction
+    constexpr int QS = 2 * PB * 64;         // stride of the operand tiles
+    constexpr bool PACK = DEEP && !BF16;
+    static_assert(!DEEP || (UP == 4 && MT == 3), "");
+    __shared__ uint4 Qt[4][PACK ? 1 : QT][2 * PB][64];  // [wave][tile][projection][voxel]
+    __shared__ uint2 Q2[PACK ? 4 : 1][PACK ? 2 * PB : 1][64];
     __shared__ int2 wtab[2][64];            // window origins of the next 64 pairs
     __shared__ double ws[4];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -2143,13 +2159,19 @@ __global__ __launch_bounds__(256, (kAdjointWaves<UP, MT, BF16, JOS, PAIR, PB>)) 
             }
             // own Q to this wave's tile, the inverse's to the partner's
             const int slot = PB == 2 ? (s0 & 2) + w : w;
-            put_q<UP, BF16>(q, &Qt[wave][0][slot][lane], QS);
-            if constexpr (PAIR) put_q<UP, BF16>(qm, &Qt[wave ^ 2][0][slot][lane], QS);
+            if constexpr (PACK) {
+                put_q_packed(q, &Qt[wave][0][slot][lane], &Q2[wave][slot][lane]);
+                if constexpr (PAIR) put_q_packed(qm, &Qt[wave ^ 2][0][slot][lane], &Q2[wave ^ 2][slot][lane]);
+            } else {
+                put_q<UP, BF16>(q, &Qt[wave][0][slot][lane], QS);
+                if constexpr (PAIR) put_q<UP, BF16>(qm, &Qt[wave ^ 2][0][slot][lane], QS);
+            }
         }
         const bool last = s0 + 2 >= s_end, contract = PB == 1 || (s0 & 2) || last;
         if (PB == 2 && last && !(s0 & 2)) {  // a lone last pair: nothing in the other two slots
 #pragma unroll
-            for (int t = 0; t < QT; ++t) Qt[wave][t][2][lane] = Qt[wave][t][3][lane] = make_uint4(0, 0, 0, 0);
+            for (int t = 0; t < (PACK ? 1 : QT); ++t) Qt[wave][t][2][lane] = Qt[wave][t][3][lane] = make_uint4(0, 0, 0, 0);
+            if constexpr (PACK) Q2[wave][2][lane] = Q2[wave][3][lane] = make_uint2(0, 0);
         }
         // B^T operands (tables in operand order; a projection past the last one has
         // Q = 0).  Lane group kq serves projection kq / 2 of the pair and product set
@@ -2200,7 +2222,14 @@ __global__ __launch_bounds__(256, (kAdjointWaves<UP, MT, BF16, JOS, PAIR, PB>)) 
             } else {
                 // eight: (b0 q2, b2 q0), (b0 q1, b1 q1), (b0 q0, b1 q0); four: (b0 q2 + b2 q0),
                 // then (b0 q0 + b0 q1) and (b1 q0 + b1 q1), together or (two pairs) in turn
-                const s8 b2 = __builtin_bit_cast(s8, qb[(UP == 4 ? QS : sel ? 0 : 2 * QS) + nt * 16]);
+                s8 b2;
+                if constexpr (PACK) {
+                    const uint2 l = Q2[wave][sl][nt * 16 + n];
+                    const uint4 h = __builtin_bit_cast(uint4, b0);
+                    b2 = __builtin_bit_cast(s8, make_uint4(l.x, l.y, h.x, h.y));
+                } else {
+                    b2 = __builtin_bit_cast(s8, qb[(UP == 4 ? QS : sel ? 0 : 2 * QS) + nt * 16]);
+                }
                 f4 t[MT];
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
@@ -2386,15 +2415,14 @@ static int win_blocks(const Dims &d, bool pair)
 }
 
 // Samples of a ray above which the loop over those beyond the first three is unrolled by
-// four (steps below about 0.45).  With four unique segments and 48 coefficients these
-// kernels also run four waves with one pair per contraction: the branches of that loop
-// then have other waves beside them.  One sample at a time -> by fours, 64^3 / 120
-// projections / 45 coefficients, at steps 0.5, 0.4, 0.25, 0.1 (in brackets the kernels
-// before the staged one, with a range per ray):
-//   4 segments  443 -> 369  485 -> 384  599 -> 455  1067 ->  735 us  (461 470 509  760)
-//   8 segments  538 -> 542  583 -> 551  709 -> 622  1229 ->  932     (800 838 953 1433)
-//   unpaired    718 -> 738  792 -> 755  994 -> 879  1810 -> 1421     (786 830 961 1493)
-// and 100^3 / 240, 4 segments  2683 -> 2774  2932 -> 2898  3616 -> 3403  6400 -> 5412.
+// four (steps below about 0.45).  One sample at a time -> by fours, 64^3 / 120 projections /
+// 45 coefficients, at steps 0.5, 0.4, 0.25, 0.1 (in brackets the kernels before the staged
+// one, with a range per ray):
+//   4 segments  445 -> 471  486 -> 426  602 -> 487  1072 ->  763 us  (464 474 512  766)
+//   unpaired    664 -> 513  731 -> 546  921 -> 669  1698 -> 1171     (595 641 781 1340)
+//   8 segments  542 -> 542  585 -> 565  713 -> 639  1236 ->  938     (803 842 957 1434)
+//   unpaired    722 -> 738  792 -> 760  995 -> 886  1822 -> 1438     (790 833 966 1501)
+// (4 segments from 0.4 on with four waves per SIMD).
 constexpr int kFewSamples = 7;
 
 void plan_adjoint(const std::vector<ProjFrame> &frames, Dims &d)
@@ -2416,7 +2444,9 @@ void plan_adjoint(const std::vector<ProjFrame> &frames, Dims &d)
         p.many = 0;
         for (const ProjFrame &f : frames)
             if (f.n_tau > kFewSamples) p.many = 1;
-        p.deep = (long long)win_blocks(d, p.pair != 0) * p.splits > 3LL * units;
+        // blocks per unit: four at a time where that saves a round, or in many rounds
+        const long long n = ((long long)win_blocks(d, p.pair != 0) * p.splits + units - 1) / units;
+        p.deep = n >= 10 ? 2 : (n + 2) / 3 > (n + 3) / 4 ? 1 : 0;
     }
 }
 
@@ -2449,17 +2479,23 @@ static hipError_t bp_launch(const Dims &d, const ProjFrame *frames, const float 
             hipLaunchKernelGGL(kernel, grid, dim3(256), p.lds, st, yf, frames, bop, t.Bu, d.S, d.nx, d.ny, d.nz, d.nj,
                                d.nk, d.C, d.Cp, d.step, g, beta, c, partials, p.wr, p.wc, s_per, sp);
         };
-        // (the bf16 Joseph kernel runs four waves with two pairs as well)
-        constexpr int unpaired_pb = UP == 4 && MT == 3 && !(BF16 && JOS) ? 1 : kPairs<UP, MT>;
-        constexpr int many_pb = UP == 4 && MT == 3 ? 1 : kPairs<UP, MT>;
-        if (!JOS && p.many)
-            p.pair ? launch(k_backproject_win<UP, MT, BF16, false, true, many_pb, true>)
-                   : launch(k_backproject_win<UP, MT, BF16, false, false, many_pb, true>);
-        else if (p.pair)
+        constexpr bool deep = UP == 4 && MT == 3 && !(BF16 && JOS);  // (that one fits four waves by itself)
+        const bool many = !JOS && p.many;
+        if constexpr (!JOS) {
+            if (many && p.pair && p.deep == 1)
+                launch(k_backproject_win<UP, MT, BF16, false, true, deep, true>);
+            else if (many && p.pair)
+                launch(k_backproject_win<UP, MT, BF16, false, true, false, true>);
+            else if (many && p.deep)
+                launch(k_backproject_win<UP, MT, BF16, false, false, deep, true>);
+            else if (many)
+                launch(k_backproject_win<UP, MT, BF16, false, false, false, true>);
+        }
+        if (!many && p.pair)
             launch(k_backproject_win<UP, MT, BF16, JOS, true>);
-        else if (p.deep)
-            launch(k_backproject_win<UP, MT, BF16, JOS, false, unpaired_pb>);
-        else
+        else if (!many && p.deep)
+            launch(k_backproject_win<UP, MT, BF16, JOS, false, deep>);
+        else if (!many)
             launch(k_backproject_win<UP, MT, BF16, JOS, false>);
         // (the sum must not run over scratch that was not written)
         if (hipError_t e = hipGetLastError(); e != hipSuccess || !sp) return e;

@@ -1,6 +1,6 @@
 """Which adjoint kernel a geometry runs, from its launches on a stand-in runtime
 (template arguments: unique segments, 16-coefficient tiles, bf16 tier, Joseph, paired,
-projection pairs per contraction)."""
+four waves per SIMD, many samples per ray)."""
 import pytest
 
 import oracle
@@ -27,16 +27,17 @@ def _kernel(names, up, mt, *flags):
 
 
 @pytest.mark.parametrize("model", ["trilinear", "joseph"])
-@pytest.mark.parametrize("n, pairs", [(48, 2), (56, 2), (64, 1), (72, 1)])
-def test_unpaired_adjoints_of_four_segments_and_48_coefficients(n, pairs, model):
-    # more than three blocks of 4 x 8 x 8 voxels per compute unit (256): one pair per contraction
+@pytest.mark.parametrize("n, deep", [(48, False), (56, False), (64, True), (72, False), (80, True), (96, True)])
+def test_unpaired_adjoints_of_four_segments_and_48_coefficients(n, deep, model):
+    # blocks of 4 x 8 x 8 voxels per compute unit: 2, 3, 4, 6, 8, 14; four at a time where that
+    # saves a round or there are many
     names = scenario("test_adjoint_plan", "adjoint_launches", n, 8, 30, 8, model, True, 1.0)
-    _kernel(names, 4, 3, False, model == "joseph", False, pairs)
+    _kernel(names, 4, 3, False, model == "joseph", False, deep)
 
 
-def test_paired_adjoints_keep_two_pairs():
+def test_paired_adjoints_keep_three_waves():
     names = scenario("test_adjoint_plan", "adjoint_launches", 64, 8, 30, 8, "trilinear", False, 1.0)
-    _kernel(names, 4, 3, False, False, True, 2)
+    _kernel(names, 4, 3, False, False, True, False)
 
 
 def random_frames(F, n_seg, nx, model):
@@ -60,13 +61,13 @@ def test_windows_of_any_orientation_fit(n_seg, nx, model):
     assert rc == 0 and any("k_backproject_win" in k for k in names)
 
 
-@pytest.mark.parametrize("n_seg, up, pairs", [(8, 4, 1), (16, 8, 1)])
+@pytest.mark.parametrize("n_seg, up, deep", [(8, 4, True), (16, 8, False)])
 @pytest.mark.parametrize("offsets", [False, True])
-def test_small_steps_unroll_the_samples_of_a_ray(offsets, n_seg, up, pairs):
+def test_small_steps_unroll_the_samples_of_a_ray(offsets, n_seg, up, deep):
     names = scenario("test_adjoint_plan", "adjoint_launches", 64, 8, 30, n_seg, "trilinear", offsets, 0.25)
-    _kernel(names, up, 3, False, False, not offsets, pairs, True)
+    _kernel(names, up, 3, False, False, not offsets, deep, True)
     names = scenario("test_adjoint_plan", "adjoint_launches", 64, 8, 30, n_seg, "trilinear", offsets, 0.8)
-    assert not any("Li1ELb1EEEv" in k or "Li2ELb1EEEv" in k for k in names), names
+    assert not any("Lb0ELb1EEEv" in k or "Lb1ELb1EEEv" in k for k in names), names
 
 
 def edge_shape(F, name, ell, n_seg, model):
@@ -81,10 +82,10 @@ def edge_shape(F, name, ell, n_seg, model):
 
 
 @pytest.mark.parametrize("model", ["trilinear", "joseph"])
-@pytest.mark.parametrize("ell, n_seg, up, mt, pairs", [(4, 8, 4, 1, 1), (8, 8, 4, 3, 2), (8, 16, 8, 3, 1)])
+@pytest.mark.parametrize("ell, n_seg, up, mt", [(4, 8, 4, 1), (8, 8, 4, 3), (8, 16, 8, 3)])
 @pytest.mark.parametrize("name, paired, split", [("paired_129", True, True), ("unpaired_129", False, True),
                                                  ("offsets_131", False, True), ("one_projection", True, False)])
-def test_edge_shapes_run_what_they_are_for(name, paired, split, ell, n_seg, up, mt, pairs, model):
+def test_edge_shapes_run_what_they_are_for(name, paired, split, ell, n_seg, up, mt, model):
     names = scenario("test_adjoint_plan", "edge_shape", name, ell, n_seg, model)
-    _kernel(names, up, mt, False, model == "joseph", paired, pairs)
+    _kernel(names, up, mt, False, model == "joseph", paired, False)
     assert any("k_add_splits" in k for k in names) == split
