@@ -137,7 +137,7 @@ __global__ __launch_bounds__(256) void k_map_fp32(const float *__restrict__ c, c
     }
 }
 
-// Register-resident variant for Cp <= 64 (ell_max <= 12): each wave keeps
+// Register-resident variant for Cp <= 64 (ell_max <= 8): each wave keeps
 // its B operands for every k-step in registers, and the block walks a range
 // of consecutive voxel tiles, prefetching the next tile's coefficients
 // into registers while the current tile's MFMAs run, so coefficient loads,
@@ -1006,8 +1006,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((UP == 4 &&
 // took about as many VALU instructions as the samples.  Here a thread's elements of a
 // plane are the same for all planes, so inside the volume a copy is one add.  March in ms,
 // slabs -> rings: 32^3 x 4 unique segments 0.062 -> 0.043, 100^3 x 4 1.59 -> 1.37,
-// 128^3 x 8 7.71 -> 6.38, 256^3 x 8 73.1 -> 62.1.  What bounds it now is the LDS: eight
-// corner reads of 16 bytes per sample and four segments.
+// 128^3 x 8 7.71 -> 6.38, 256^3 x 8 73.1 -> 62.1.  What bounds it now is latency: at 128^3
+// VALU issue takes 52% of the cycles and the LDS 50% (half of that bank conflicts of the
+// corner reads, 16 bytes per corner and four segments), and the two blocks that fit a
+// compute unit (1.9 waves per SIMD) do not cover one with the other.
 //
 // A plane's float4 halves (eight segments) lie one after the other, so that neighbouring
 // voxels are 16 bytes apart and a wave's reads spread over all banks (interleaved by
@@ -1813,7 +1815,7 @@ __global__ __launch_bounds__(256) void k_backproject(const float *__restrict__ y
 // 128^3 / 300 / 8 11.3 -> 7.3; 100^3 / 240 / 4 2.89 -> 2.22 (Joseph 1.95 -> 1.61);
 // 97 x 89 x 107 / 220 / 8 with detector offsets (unpaired) 4.79 -> 3.39; relative
 // error against float64 4.7e-7 -> 1.3e-7 (100^3), 7.2e-7 -> 3.9e-7 (128^3, with the
-// forward's).  Now bound by VALU issue alone (89% of the cycles at 128^3).
+// forward's).  Now bound by VALU issue: 95% of the cycles at 128^3, with 84% of the lanes.
 // ---------------------------------------------------------------------------
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 typedef float f2 __attribute__((ext_vector_type(2)));
@@ -2360,7 +2362,9 @@ __global__ __launch_bounds__(256) void k_add_splits(const float *__restrict__ sp
 // writes and reads a coefficient volume, at about 4 TB/s, against about 1.2 us per
 // block and pair of projections.  Adjoint with its fold, unsplit -> split: 32^3 / 60
 // projections / 15 coefficients (128 blocks, six splits) 81 -> 52 us, 48^3 / 120 / 28
-// (432 blocks, three) 180 -> 172 us.
+// (432 blocks, three) 180 -> 172 us.  Over 60 random shapes of 10^3 to 76^3 the choice is
+// 1.00 to 6.4 times as fast as no split, but for one with 66 coefficients, whose kernels run
+// two blocks at a time (62^3 / 312 projections, unpaired: 1657 -> 1688 us).
 static int adjoint_splits(const Dims &d, int blocks, int units, double &gain)
 {
     const double vol_us = 4.0 * d.nx * d.ny * d.nz * d.C / 4e6;
